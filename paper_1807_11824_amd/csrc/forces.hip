@@ -4,6 +4,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 // A_i = sum_j p_ij w_ij (y_i - y_j), w_ij = 1/(1+|y_i-y_j|^2).  LPR lanes share one CSR row:
 // col/val are read as contiguous segments, y_j is an 8-byte gather, and the two partial sums
 // are combined with xor-shuffles inside the LPR-lane group.  No atomics: the result is
@@ -635,28 +637,41 @@ __global__ __launch_bounds__(256) void exact_z_k(const float2 *__restrict__ Y, i
         }
         // (a squared distance that overflows has weight 0, but would turn its partner's term into a NaN)
         const int both = __syncthreads_or(wide) ? 0 : cnt / 2;
+        const float2 *one = reinterpret_cast<const float2 *>(tile);
+        auto weight = [](float2 p, float2 q) {
+            const float dx = p.x - q.x, dy = p.y - q.y;
+            return __builtin_amdgcn_rcpf(fmaf(dy, dy, fmaf(dx, dx, 1.0f)));
+        };
+        // (diagonal: a point meets itself, whose 1 is left out -- taken off afterwards it would leave its rounding behind,
+        // which is more than the sum once the points are far apart; its partner in the pair is added behind the loop)
+        auto meet = [&](auto diagonal) {
 #pragma unroll 4
-        for (int t = 0; t < both; ++t) {
-            const float4 y2 = tile[t];
+            for (int t = 0; t < both; ++t) {
+                const float4 y2 = tile[t];
 #pragma unroll
-            for (int q = 0; q < KL_PT; ++q) {
-                const float ax = yi[q].x - y2.x, ay = yi[q].y - y2.y, bx = yi[q].x - y2.z, by = yi[q].y - y2.w;
-                const float a = fmaf(ay, ay, fmaf(ax, ax, 1.0f)), b = fmaf(by, by, fmaf(bx, bx, 1.0f));
-                z[q] = fmaf(a + b, __builtin_amdgcn_rcpf(a * b), z[q]);
+                for (int q = 0; q < KL_PT; ++q) {
+                    const float ax = yi[q].x - y2.x, ay = yi[q].y - y2.y, bx = yi[q].x - y2.z, by = yi[q].y - y2.w;
+                    const float a = fmaf(ay, ay, fmaf(ax, ax, 1.0f)), b = fmaf(by, by, fmaf(bx, bx, 1.0f));
+                    const float sum = fmaf(a + b, __builtin_amdgcn_rcpf(a * b), z[q]);
+                    z[q] = diagonal && t == q * 128 + (int)(threadIdx.x >> 1) ? z[q] : sum;
+                }
             }
-        }
-        for (int t = 2 * both; t < cnt; ++t) {
-            const float2 y1 = reinterpret_cast<const float2 *>(tile)[t];
+            for (int t = 2 * both; t < cnt; ++t)
 #pragma unroll
-            for (int q = 0; q < KL_PT; ++q) {
-                const float ax = yi[q].x - y1.x, ay = yi[q].y - y1.y;
-                z[q] += __builtin_amdgcn_rcpf(fmaf(ay, ay, fmaf(ax, ax, 1.0f)));
+                for (int q = 0; q < KL_PT; ++q)
+                    z[q] += diagonal && t == q * 256 + (int)threadIdx.x ? 0.f : weight(yi[q], one[t]);
+            if (diagonal) {
+#pragma unroll
+                for (int q = 0; q < KL_PT; ++q) {
+                    const int own = q * 256 + (int)threadIdx.x;
+                    if (own < 2 * both) z[q] += weight(yi[q], one[own ^ 1]);
+                }
             }
-        }
+        };
+        if (it == jt) meet(std::true_type()); else meet(std::false_type());
 #pragma unroll
         for (int q = 0; q < KL_PT; ++q)
-            if (it * KL_TILE + q * 256 + (int)threadIdx.x < n)
-                acc += it == jt ? (double)z[q] - 1.0 : 2.0 * (double)z[q];     // (the point itself contributed 1)
+            if (it * KL_TILE + q * 256 + (int)threadIdx.x < n) acc += it == jt ? (double)z[q] : 2.0 * (double)z[q];
     }
     acc = wave_sum(acc);
     if (lane_id() == 0) ws[threadIdx.x >> 6] = acc;
