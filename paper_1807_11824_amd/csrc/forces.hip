@@ -609,6 +609,7 @@ hipError_t launch_fill_state(tsne_ctx *c, hipStream_t s)
 // above in double.  60,000 points: 2565 us with a division per ordered pair, 287 us now (the instructions alone: 275 us).
 constexpr int KL_BLOCKS = 1024;
 constexpr int KL_PT = 2, KL_TILE = 256 * KL_PT;
+constexpr float KL_WIDE = 1e9f;      // coordinates up to here: a and b below 8.1e18, a b below 2^126, its reciprocal normal
 
 __global__ __launch_bounds__(256) void exact_z_k(const float2 *__restrict__ Y, int n, double *__restrict__ part)
 {
@@ -633,9 +634,9 @@ __global__ __launch_bounds__(256) void exact_z_k(const float2 *__restrict__ Y, i
             reinterpret_cast<float2 *>(tile)[q * 256 + (int)threadIdx.x] = yj;
             yi[q] = Y[min(it * KL_TILE + q * 256 + (int)threadIdx.x, n - 1)];
             z[q] = 0.f;
-            wide |= fmaxf(fmaxf(fabsf(yj.x), fabsf(yj.y)), fmaxf(fabsf(yi[q].x), fabsf(yi[q].y))) > 1e18f;
+            wide |= fmaxf(fmaxf(fabsf(yj.x), fabsf(yj.y)), fmaxf(fabsf(yi[q].x), fabsf(yi[q].y))) > KL_WIDE;
         }
-        // (a squared distance that overflows has weight 0, but would turn its partner's term into a NaN)
+        // (beyond, the product of two squared distances may overflow, and a near point would lose its weight to a far one)
         const int both = __syncthreads_or(wide) ? 0 : cnt / 2;
         const float2 *one = reinterpret_cast<const float2 *>(tile);
         auto weight = [](float2 p, float2 q) {
