@@ -604,11 +604,13 @@ hipError_t launch_fill_state(tsne_ctx *c, hipStream_t s)
 // the diagonal.  A workgroup goes through its share of the pairs of tiles (i-tile <= j-tile, numbered along the lower
 // triangle); a thread keeps KL_PT points of the i-tile in registers and meets the points of the j-tile two at a time
 // from LDS (broadcast reads).
-// Bound by vector issue: two points share one reciprocal, 1/a + 1/b = (a + b) / (a b), which is 12 instructions for two
-// terms (a reciprocal of its own per term: 343 us at 60,000 points).  Sums of KL_TILE terms in single precision, everything
-// above in double.  60,000 points: 2565 us with a division per ordered pair, 287 us now (the instructions alone: 275 us).
+// Bound by vector issue: two points share one reciprocal, 1/a + 1/b = (a + b) / (a b), which with a Newton step on it is 14
+// instructions for two terms.  (The bare v_rcp_f32 is low on average: Z came out 7e-9 too small at any n, where a division
+// per term is off by 1e-9; with the step, and sums of KL_RUN terms below those of KL_TILE in single precision and everything
+// above in double, it is off by no more than that.)  tsne_kl_static at 60,000 points, one entry of P a row: 2530 us with a
+// division per ordered pair, 302 us now, 264 without the Newton step.
 constexpr int KL_BLOCKS = 1024;
-constexpr int KL_PT = 2, KL_TILE = 256 * KL_PT;
+constexpr int KL_PT = 2, KL_TILE = 256 * KL_PT, KL_RUN = 128;
 constexpr float KL_WIDE = 1e9f;      // coordinates up to here: a and b below 8.1e18, a b below 2^126, its reciprocal normal
 
 __global__ __launch_bounds__(256) void exact_z_k(const float2 *__restrict__ Y, int n, double *__restrict__ part)
@@ -641,21 +643,27 @@ __global__ __launch_bounds__(256) void exact_z_k(const float2 *__restrict__ Y, i
         const float2 *one = reinterpret_cast<const float2 *>(tile);
         auto weight = [](float2 p, float2 q) {
             const float dx = p.x - q.x, dy = p.y - q.y;
-            return __builtin_amdgcn_rcpf(fmaf(dy, dy, fmaf(dx, dx, 1.0f)));
+            return 1.0f / fmaf(dy, dy, fmaf(dx, dx, 1.0f));
         };
         // (diagonal: a point meets itself, whose 1 is left out -- taken off afterwards it would leave its rounding behind,
         // which is more than the sum once the points are far apart; its partner in the pair is added behind the loop)
         auto meet = [&](auto diagonal) {
+            for (int t0 = 0; t0 < both; t0 += KL_RUN / 2) {
+                float run[KL_PT] = {};
 #pragma unroll 4
-            for (int t = 0; t < both; ++t) {
-                const float4 y2 = tile[t];
+                for (int t = t0; t < min(both, t0 + KL_RUN / 2); ++t) {
+                    const float4 y2 = tile[t];
 #pragma unroll
-                for (int q = 0; q < KL_PT; ++q) {
-                    const float ax = yi[q].x - y2.x, ay = yi[q].y - y2.y, bx = yi[q].x - y2.z, by = yi[q].y - y2.w;
-                    const float a = fmaf(ay, ay, fmaf(ax, ax, 1.0f)), b = fmaf(by, by, fmaf(bx, bx, 1.0f));
-                    const float sum = fmaf(a + b, __builtin_amdgcn_rcpf(a * b), z[q]);
-                    z[q] = diagonal && t == q * 128 + (int)(threadIdx.x >> 1) ? z[q] : sum;
+                    for (int q = 0; q < KL_PT; ++q) {
+                        const float ax = yi[q].x - y2.x, ay = yi[q].y - y2.y, bx = yi[q].x - y2.z, by = yi[q].y - y2.w;
+                        const float a = fmaf(ay, ay, fmaf(ax, ax, 1.0f)), b = fmaf(by, by, fmaf(bx, bx, 1.0f));
+                        const float p = a * b, r = __builtin_amdgcn_rcpf(p);
+                        const float sum = fmaf(a + b, fmaf(fmaf(-p, r, 1.0f), r, r), run[q]);
+                        run[q] = diagonal && t == q * 128 + (int)(threadIdx.x >> 1) ? run[q] : sum;
+                    }
                 }
+#pragma unroll
+                for (int q = 0; q < KL_PT; ++q) z[q] += run[q];
             }
             for (int t = 2 * both; t < cnt; ++t)
 #pragma unroll
