@@ -2342,6 +2342,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
             const double delta = ldexp(1.0, -14) / (double)scale;
             e_add = 2.0 * (delta * 2.0 * sqrt((double)d) * sqrt((double)norm_max) + (double)d * delta * delta);
             hipLaunchKernelGGL(split_high, wide_grid((size_t)n * dph), dim3(256), 0, s, d_X, L.mu, n, d, dph, scale, L.xh);
+            HIPCHK(hipMemsetAsync(L.fail2_count, 0, 4, s));
         }
     }
     // equal blocks of whole tiles (a short last one would leave most compute units idle)
@@ -2398,24 +2399,26 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
         hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, d_X, n, d, (const int *)nullptr, d_X, n,
                            (const int *)nullptr, (const int *)nullptr, (const int *)nullptr, q0, rows, k, kp, n - 1,
                            high ? tile_error_coeff(d, false, true) : tile_error_coeff(d, d > KFLUSH), high ? e_add : 0.0, L.norms, norm_max,
-                           L.tau, L.cnt, L.cand, cap, L.knn_idx, L.knn_d2, L.fail_count, L.fail_rows);
+                           L.tau, L.cnt, L.cand, cap, L.knn_idx, L.knn_d2, high == high_first ? L.fail_count : L.fail2_count,
+                           high == high_first ? L.fail_rows : L.fail2_rows);
         HIPCHK(hipGetLastError());
         if (high && q0 == 0 && qend < n) {
-            // half precision that certifies less than half of the first block's rows is no use for the others
+            // half precision that certifies less than half of the first block's rows is no use for the others (whose rows
+            // without a certificate the second sweep, the same tiles once more, could not help: they go on its list of those)
             int failed = 0;
             HIPCHK(hipMemcpyAsync(&failed, L.fail_count, 4, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
             if (failed > rows / 2) high = false;
         }
     }
-    int nfail = 0;
+    int nfail = 0, nfail2 = 0;
     HIPCHK(hipMemcpyAsync(&nfail, L.fail_count, 4, hipMemcpyDeviceToHost, s));
+    if (high != high_first) HIPCHK(hipMemcpyAsync(&nfail2, L.fail2_count, 4, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     const int *exact_rows = L.fail_rows;
-    if (high_first && nfail > 0) {
+    if (high_first && nfail + nfail2 > 0) {
         // second sweep: the rows the first one could not certify, QB at a time, as queries of their own (a split
         // copy of just these rows) against all rows
-        HIPCHK(hipMemsetAsync(L.fail2_count, 0, 4, s));
         for (int f0 = 0; f0 < nfail; f0 += QB) {
             const int rows = nfail - f0 < QB ? nfail - f0 : QB;
             const int *fr = L.fail_rows + f0;

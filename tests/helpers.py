@@ -39,3 +39,23 @@ def random_symmetric_csr(n, deg, seed=0):
     M.sort_indices()
     M.data /= M.data.sum()
     return M.indptr.astype(np.int32), M.indices.astype(np.int32), M.data.astype(np.float32)
+
+
+def launches(fn):
+    """fn() and how often it launched which of the library's kernels (template arguments dropped, and kept): a Counter."""
+    import re
+    from collections import Counter
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        out = fn()
+        torch.cuda.synchronize()
+    count = Counter()
+    for e in prof.key_averages():
+        m = re.search(r"(\w+)(<[^()]*>)?\(", e.key.replace("(anonymous namespace)::", ""))
+        if m:
+            count[m.group(1)] += e.count
+            if m.group(2):
+                count[m.group(1) + m.group(2).replace(" ", "")] += e.count
+    return out, count

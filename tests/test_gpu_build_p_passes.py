@@ -69,3 +69,20 @@ def test_half_precision_sweep_of_shorter_rows(n, d, spread):
     X[100:500] = X[rng.integers(1000, 1004, 400)]
     rows = np.concatenate([np.arange(100, 500, 50), np.arange(0, n, n // 40)])
     _check_against_oracle(X.astype(np.float32), 10.0, 40, rows=np.unique(rows))
+
+
+def test_rows_that_three_products_cannot_certify_are_not_swept_twice():
+    """Two blocks of query rows.  Half precision certifies none of the first block's (groups far apart against the steps
+    between neighbours), so the second block goes through three products, which cannot certify its rows either (a hundred
+    copies of each): those are for the exact pass.  The second sweep is for the first block's rows only: one pass, not two."""
+    from helpers import launches
+    rng = np.random.default_rng(5)
+    n, d, k, split = 66000, 256, 20, 33024
+    X = 8.0 * rng.standard_normal((8, d))[rng.integers(0, 8, n)] + rng.standard_normal((n, d))
+    X[split:] = X[split:][rng.permutation(np.arange(n - split) % 329)]
+    X = X.astype(np.float32)
+    rows = np.concatenate([np.arange(0, split, split // 30), np.arange(split, n, (n - split) // 10)])
+    _, count = launches(lambda: _check_against_oracle(X, 5.0, k, rows=rows))
+    assert count["knn_tile_half"] == (n + 2047) // 2048         # the first block's launches
+    assert count["knn_exact_select"] > 100                      # (2 k rows a launch)
+    assert count["knn_rerank"] == 3                             # two blocks, one pass of the second sweep
