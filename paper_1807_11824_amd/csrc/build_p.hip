@@ -24,8 +24,11 @@
 //   sym_count / sym_fill / sym_sort_rows   p_ij = (p_j|i + p_i|j) / 2N as CSR, columns ascending
 #include "tsne_internal.h"
 
+#include <algorithm>
+
 #include <math.h>
 #include <stdio.h>
+#include <string.h>
 
 namespace {
 
@@ -205,6 +208,70 @@ __host__ __device__ inline double tile_error_coeff(int d, bool two_level, bool h
                                    : 3.0 * (1.0 + 3.814697265625e-06) * 3.814697265625e-06;
     const double accum = 1.0079 * R * u / (1.0 - R * u);
     return 1.05 * (split + accum + (16.0 + 4.2) * 5.9604644775390625e-08);
+}
+
+// Are the k-th and the k'-th neighbour farther apart than half precision can be off?  Asked of a few query rows, a workgroup
+// each, spread evenly over X, among an even sample of GAP_SAMPLE rows, where the two have the ranks r1 and r2; counts the
+// query rows that say no.  (Of points near a plane, close to their neighbours and far from the mean, hardly a row gets a
+// certificate, and without the question both sweeps are paid for.  50 to 90 us, bound by the latency of the sample's rows,
+// eight of which a lane has on their way.  33,000 x 100, 50,000 x 100 and 65,000 x 200 near a plane: 9.7 -> 6.0, 16.5 -> 10.3,
+// 27.4 -> 17.5 ms; 33,000 x 100 in clusters 4.50 -> 4.56.)
+constexpr int GAP_QUERIES = 32, GAP_SAMPLE = 4096;
+
+__global__ __launch_bounds__(1024) void half_gap_sample(const float *__restrict__ X, int n, int d, int m, int r1, int r2,
+                                                        const float *__restrict__ norms, float norm_max, double coeff,
+                                                        int *__restrict__ narrow)
+{
+    __shared__ float dist[GAP_SAMPLE];
+    __shared__ int below[2][2][16];
+    const int i = (int)(((long long)blockIdx.x * n) / gridDim.x), g = threadIdx.x / 16, sub = threadIdx.x % 16;
+    const float *x = X + (size_t)i * d;
+    for (int c0 = g; c0 < m; c0 += 64 * 8) {
+        const float *y[8];
+        float a[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            y[u] = X + (size_t)(((long long)min(c0 + 64 * u, m - 1) * n) / m) * d;
+            a[u] = 0.f;
+        }
+#pragma unroll 2
+        for (int t = sub; t < d; t += 16)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) { const float df = x[t] - y[u][t]; a[u] = fmaf(df, df, a[u]); }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) a[u] += __shfl_xor(a[u], o, WAVE);
+            if (sub == 0 && c0 + 64 * u < m) dist[c0 + 64 * u] = y[u] == x ? INFINITY : a[u];
+        }
+    }
+    __syncthreads();
+    // the values of the two ranks, from their leading bits down (squares: the bit patterns are ordered)
+    uint32_t v[GAP_SAMPLE / 1024], at[2] = {0u, 0u};
+#pragma unroll
+    for (int u = 0; u < GAP_SAMPLE / 1024; ++u) {
+        const int c = u * 1024 + (int)threadIdx.x;
+        v[u] = c < m ? __float_as_uint(dist[c]) : 0xFFFFFFFFu;
+    }
+    for (int bit = 30; bit >= 0; --bit) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            int here = 0;
+#pragma unroll
+            for (int u = 0; u < GAP_SAMPLE / 1024; ++u) here += (int)__popcll(__ballot(v[u] < (at[r] | (1u << bit))));
+            if (lane_id() == 0) below[bit & 1][r][threadIdx.x >> 6] = here;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            int all = 0;
+#pragma unroll
+            for (int w = 0; w < 16; ++w) all += below[bit & 1][r][w];
+            if (all < (r == 0 ? r1 : r2)) at[r] |= 1u << bit;
+        }
+    }
+    const double gap = (double)__uint_as_float(at[1]) - (double)__uint_as_float(at[0]);
+    if (threadIdx.x == 0 && !(gap > coeff * ((double)norms[i] + (double)norm_max))) atomicAdd(narrow, 1);
 }
 
 // A wave's queue of accepted pairs lives in LDS.
@@ -1902,7 +1969,7 @@ size_t carve(Layout *L, int n, int d, int k, char *base)
         L->high_fits = d >= HIGH_FIRST_MIN_D;
         if (!L->high_fits) {
             // the half-precision sweep of shorter rows lives where the rows of P are sorted later (its last list where
-            // their extra entries are counted off), if that is large enough
+            // their extra entries are counted off), if that is large enough: 2 n dph + 4 min(n, QB) dp bytes in 16 n k
             const size_t dp = (size_t)(d + SLAB - 1) / SLAB * SLAB, dph = (size_t)(d + 2 * SLAB - 1) / (2 * SLAB) * (2 * SLAB);
             char *p = (char *)L->sort_scratch;
             L->xh = (uint16_t *)p; p += up(2 * (size_t)n * dph);
@@ -2312,25 +2379,37 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
             else tiles(knn_tile_mfma<KNN_MB, false, false>, 64 * KNN_MB);
         }
     };
-    // Long rows: a first sweep with the high parts alone (a third of the matrix work, half the bytes, a coarser
-    // bound: 2^-8 of the norms instead of 2^-16); its certificate still holds wherever the k-th and the k'-th
+    // Long rows: a first sweep with the values rounded to half precision (a third of the matrix work, half the bytes, a
+    // coarser bound: 2^-10 of the norms instead of some 2^-15); its certificate still holds wherever the k-th and the k'-th
     // neighbour are farther apart than that, and only the rows it fails go through the three-product tiles.
-    // From HIGH_FIRST_MIN_D columns on always; shorter rows beyond the resident kernel's where the tiles go query tile by query
-    // tile (50,000 rows of 72 and 200 coordinates: 9.3 -> 6.5 and 11.3 -> 7.4 ms, 33,000 of 100: 5.7 -> 4.5; 8000, where they do not: 1.0 -> 1.2).
+    // From HIGH_FIRST_MIN_D columns on always.  Shorter rows beyond the resident kernel's take it if three things hold: the
+    // tiles go query tile by query tile (k = 90: 50,000 rows of 72 and 200 coordinates 9.3 -> 6.5 and 11.3 -> 7.4 ms, 33,000 of
+    // 100: 5.7 -> 4.5; 8000, where they do not: 1.0 -> 1.2); its buffers fit where the rows of P are sorted later, which
+    // depends on k (see carve(): up to 65,536 rows that is k >= 0.375 d or so, d rounded up to 64, beyond it falls
+    // to 0.125 d); and a sample's neighbours are far enough apart.
     const int nblocks = (n + QB - 1) / QB, block = ((n + nblocks - 1) / nblocks + HT - 1) / HT * HT;   // see the loop below
     bool high_first = d >= HIGH_FIRST_MIN_D || (dp > 2 * SLAB && (n < block ? n : block) >= HALF_OWN_MIN_ROWS && L.high_fits);
     const int dph = (d + 2 * SLAB - 1) / (2 * SLAB) * (2 * SLAB);
     float dot_scale = 1.0f;
     double e_add = 0.0;
     if (high_first) {
-        HIPCHK(hipMemsetAsync(L.fail2_count, 0, 4, s));            // (borrowed for the largest magnitude)
+        HIPCHK(hipMemsetAsync(L.fail2_count, 0, 8, s));            // (borrowed for the largest magnitude and the sample's vote)
         hipLaunchKernelGGL(max_abs_centred, dim3(2048), dim3(256), 0, s, d_X, L.mu, (size_t)n * d, d,
                            reinterpret_cast<unsigned int *>(L.fail2_count));
-        float xmax = 0.f;
-        HIPCHK(hipMemcpyAsync(&xmax, L.fail2_count, 4, hipMemcpyDeviceToHost, s));
+        if (d < HIGH_FIRST_MIN_D) {
+            const int m = n < GAP_SAMPLE ? n : GAP_SAMPLE;
+            const int r1 = (int)std::max<int64_t>(1, (int64_t)k * m / n), r2 = std::max(r1 + 1, (int)(((int64_t)kp * m + n - 1) / n));
+            hipLaunchKernelGGL(half_gap_sample, dim3(GAP_QUERIES), dim3(1024), 0, s, d_X, n, d, m, r1, r2, L.norms, norm_max,
+                               tile_error_coeff(d, false, true), L.fail2_count + 1);
+        }
+        int found[2] = {0, 0};
+        HIPCHK(hipMemcpyAsync(found, L.fail2_count, 8, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
-        if (!(xmax > 0.f) || !(xmax < 1e15f)) {
-            high_first = false;                                     // all rows equal, or values half precision cannot scale
+        float xmax;
+        memcpy(&xmax, &found[0], 4);
+        if (!(xmax > 0.f) || !(xmax < 1e15f) || found[1] > GAP_QUERIES / 2) {
+            // all rows equal, values half precision cannot scale, or neighbours it cannot tell apart
+            high_first = false;
         } else {
             int e = 0;
             (void)frexpf(xmax, &e);                                 // xmax < 2^e

@@ -86,3 +86,14 @@ def test_rows_that_three_products_cannot_certify_are_not_swept_twice():
     assert count["knn_tile_half"] == (n + 2047) // 2048         # the first block's launches
     assert count["knn_exact_select"] > 100                      # (2 k rows a launch)
     assert count["knn_rerank"] == 3                             # two blocks, one pass of the second sweep
+
+
+def test_half_precision_is_not_tried_on_points_near_a_plane():
+    """Neighbours closer together than half precision can tell: the sweep would certify no row, and the lists need the
+    three-product tiles anyway."""
+    from helpers import launches
+    rng = np.random.default_rng(7)
+    n, d = 33000, 72
+    X = (rng.random((n, 2)) @ rng.standard_normal((2, d))).astype(np.float32)
+    _, count = launches(lambda: _check_against_oracle(X, 30.0, 90, rows=np.arange(0, n, n // 40)))
+    assert count["knn_tile_half"] == 0 and count["knn_tile_mfma"] == (n + 2047) // 2048
