@@ -61,14 +61,42 @@ def test_hub_rows(n):
     assert np.diff(g["row_ptr"])[[n // 3, n // 2]].min() >= n - 50
 
 
-@pytest.mark.parametrize("n,d,spread", [(33000, 72, 4.0), (33000, 200, 4.0), (33000, 72, 400.0), (66000, 80, 400.0)])
-def test_half_precision_sweep_of_shorter_rows(n, d, spread):
-    """From 32,768 rows on; far groups leave it without certificates (second sweep), copies those without any (exact pass)."""
-    rng = np.random.default_rng(n + d)
-    X = spread * rng.standard_normal((8, d))[rng.integers(0, 8, n)] + rng.standard_normal((n, d))
-    X[100:500] = X[rng.integers(1000, 1004, 400)]
-    rows = np.concatenate([np.arange(100, 500, 50), np.arange(0, n, n // 40)])
-    _check_against_oracle(X.astype(np.float32), 10.0, 40, rows=np.unique(rows))
+def _three_kinds(n, d, tight, seed):
+    """Rows of eight wide groups (half precision certifies them: the k-th and the k'-th neighbour are some ten times as far
+    apart as its bound), a share `tight` of rows of eight groups a fifth as wide (it does not, three products do), and two
+    rows with 200 copies each, more than k' (the exact pass).  tight: the shares of the two halves."""
+    rng = np.random.default_rng(seed)
+    narrow = rng.random(n) < np.where(np.arange(n) < n // 2, *tight)
+    X = rng.standard_normal((16, d))[rng.integers(0, 8, n) + 8 * narrow]
+    X += np.where(narrow, 0.2, 1.0)[:, None] * rng.standard_normal((n, d))
+    copies = rng.choice(np.flatnonzero(~narrow), 400, replace=False)
+    X[copies] = X[copies[np.arange(400) % 2]]
+    rows = np.concatenate([copies[:10], np.flatnonzero(narrow)[::500], np.arange(0, n, n // 40)])
+    return X.astype(np.float32), np.unique(rows)
+
+
+@pytest.mark.parametrize("n,d,tight,half_launches,passes", [
+    (33000, 72, (0.3, 0.3), 17, 2),      # one block of query rows, and the second sweep
+    (33000, 200, (0.3, 0.3), 17, 2),
+    (33000, 300, (0.3, 0.3), 17, 2),     # (buffers of its own)
+    (66000, 80, (0.3, 0.3), 66, 3),      # two blocks
+    (66000, 80, (0.6, 0.0), 33, 3),      # a first block that is mostly narrow: the next one does without
+])
+def test_half_precision_sweep(n, d, tight, half_launches, passes):
+    """Query tile by query tile, from 32,768 rows on; what it cannot certify goes on to three products and the exact pass."""
+    from helpers import launches
+    k = 90
+    if d < 256:     # the buffers have to fit where rows of P are sorted later, or the sweep is not taken
+        block = min(n, 65536)
+        assert 2 * n * ((d + 63) // 64 * 64) + 4 * block * ((d + 31) // 32 * 32) + 4 * block + 768 <= 16 * n * k
+    X, rows = _three_kinds(n, d, tight, seed=n + d)
+    _, count = launches(lambda: _check_against_oracle(X, 30.0, k, rows=rows))
+    assert count["knn_tile_half"] == half_launches
+    blocks = half_launches // ((n + 2047) // 2048)
+    assert count["knn_tile_half<true,false>"] == blocks         # the first launch of a block keeps every pair
+    assert count["knn_tile_half<false,true>"] == half_launches - blocks
+    assert count["knn_rerank"] == passes
+    assert count["knn_exact_select"] >= 400 // (2 * k)
 
 
 def test_rows_that_three_products_cannot_certify_are_not_swept_twice():
