@@ -263,7 +263,7 @@ __global__ __launch_bounds__(64) void ivf_probe(const float *__restrict__ X, int
 // mean does not depend on the order in which the atomics land.
 // The sample's rows come grouped by their centroid (order[0 .. m)): a lane takes one coordinate of KM_ROWS consecutive ones,
 // adds in a register as long as the centroid stays the same and goes to memory once per run.  (One 64-bit atomic per row
-// and coordinate: 3.4 ms a round for 290,000 rows of 2048 coordinates, now 0.76.))
+// and coordinate: 3.4 ms a round for 290,000 rows of 2048 coordinates, now 0.76.)
 constexpr int KM_ROWS = 64;
 
 __global__ __launch_bounds__(256) void kmeans_accum(const float *__restrict__ X, int n, int d, const int32_t *__restrict__ probe,
@@ -1040,11 +1040,11 @@ static int ivf_knn_impl(const float *X, int n, int d, const float *C, int nlist,
         return ivf_search_tiles(X, n, d, k, nlist, tau, L.probe, L.lorder, L.cellptr, max_list, mmax, knn_idx, knn_d2,
                                 L.tiles_ws, L.tiles_bytes, s);
     }
-    // (the lists' rows as doubles, for the vector kernels)
-    hipLaunchKernelGGL(gather_double, (blocks((size_t)n * dp)), dim3(256), 0, s, X, n, d, dp, L.lorder, L.Xl);
     const long long d_cap = (long long)(L.d_bytes / 4);
     if (rc == TSNE_OK && mmax > d_cap) rc = TSNE_ENOSPC;
     if (rc != TSNE_OK) { free(mp); return rc; }
+    // the lists' rows as doubles, for ivf_score
+    if (!pq.codes) hipLaunchKernelGGL(gather_double, (blocks((size_t)n * dp)), dim3(256), 0, s, X, n, d, dp, L.lorder, L.Xl);
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ivf_score<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)chunk_lds(IVF_DC + 1, IVF_QW));
     if (e != hipSuccess) { free(mp); return TSNE_EHIP; }

@@ -261,3 +261,17 @@ def test_P_from_product_quantised_neighbours(d):
     assert P["unconverged"] == bad
     exact_idx, _ = oracle.knn(X, k)
     print(f"recall at k = {k} against the exact lists: {ivf.recall(got_idx, exact_idx):.4f}", flush=True)
+
+
+@pytest.mark.parametrize("pq_m,copies", [(0, 1), (4, 0)])
+def test_the_copy_of_the_lists_is_made_where_it_is_read(pq_m, copies):
+    """A search that has to be repeated with more lists (four of some 20 rows each hold fewer than 100 others) copies the
+    lists' rows once, for the attempt that reads them; product-quantised codes are scored without them."""
+    import torch
+    from helpers import launches
+    from paper_1807_11824_amd import build_P_approx
+    X = torch.from_numpy(np.random.default_rng(3).standard_normal((400, 24)).astype(np.float32)).to("cuda:0")
+    P, count = launches(lambda: build_P_approx(X, 20.0, 100, 2, pq_m=pq_m))
+    assert P["tau_used"] > 2
+    assert count["gather_double"] == copies
+    assert count["ivf_select"] == 1
