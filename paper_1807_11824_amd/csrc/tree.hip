@@ -1061,11 +1061,11 @@ static int bbox_blocks(int n)
 // -> 4.26 ms, 30,011 4.68 -> 4.25, 512,000 13.53 -> 13.23.)
 int sort_items(int n, int num_cu)
 {
+    const int cu = num_cu > 0 ? num_cu : 256, fine = cu < SORT_FINE_TILES ? cu : SORT_FINE_TILES;
     for (int items = 2; items <= 4; items += 2)
-        if (((long long)n + SORT_THREADS * items - 1) / (SORT_THREADS * items) <= SORT_FINE_TILES) return items;
+        if (((long long)n + SORT_THREADS * items - 1) / (SORT_THREADS * items) <= fine) return items;
     int best = 8;
     long long best_cost = -1;
-    const int cu = num_cu > 0 ? num_cu : 256;
     for (int items = 8; items <= 12; items += 2) {
         const long long nblk = ((long long)n + SORT_THREADS * items - 1) / (SORT_THREADS * items);
         const long long cost = ((nblk + cu - 1) / cu) * items;
