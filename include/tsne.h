@@ -128,8 +128,9 @@ void tsne_destroy(tsne_ctx *ctx);
  * *n_unconverged (host, may be NULL) receives the number of rows whose entropy could not be
  * brought within 1e-5 of the target (e.g. all neighbours equidistant).
  * X must be finite with |x| < 1e38.  Candidate neighbours are found with reduced-precision products
- * (each value, minus its column's mean, as two bf16 parts; rows of 256 and more coordinates first as one
- * half-precision value), every row's list is then re-ranked in double precision from X itself and checked
+ * (each value, minus its column's mean, as two bf16 parts; rows of 256 and more coordinates, and from 32,768
+ * rows on shorter ones of more than 64 where the sorting space below can hold their half-precision copies, first as
+ * one half-precision value), every row's list is then re-ranked in double precision from X itself and checked
  * against a bound on the candidate search's error; rows that cannot be certified go on to the next finer
  * search and finally (ties at the k-th distance) are redone exactly against all n rows, 2k rows a launch, so
  * the lists do not depend on the reduced precision.

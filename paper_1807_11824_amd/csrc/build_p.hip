@@ -46,7 +46,7 @@ constexpr int COMPACT_EVERY = 2;   // after the resident tile kernel a compactio
                                    // costs a third of a slab; cut-offs one slab older let a few more pairs through)
 constexpr int KFLUSH = 64;      // columns summed on the matrix cores before a flush into the running sum
 constexpr int HALF_OWN_MIN_ROWS = 128 * 256, HALF_OWN_MAX_D = 2048;     // where the half-precision tiles go query tile by query tile
-constexpr int HIGH_FIRST_MIN_D = 256;   // from this many columns on the exact search sweeps with the high parts first
+constexpr int HIGH_FIRST_MIN_D = 256;   // from this many columns on the exact search always sweeps in half precision first
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
@@ -331,7 +331,7 @@ __device__ __noinline__ int queue_pairs(bool near, int j, int ql, int qa, int q0
 // itself, a distance that is no finite number) leaves NO_PAIR, which the compaction behind the launch drops; the row's
 // count is the launch's width.  (Through the queue every wave of a first slab of 256 rows made 128 trips to memory one
 // after the other, each for the answer of an atomic: 1.05 ms of the build of 2000 points, 1.43 -> 0.39 in all;
-// 60,000 x 784 21.4 -> 18.7 ms, 512,000 x 50 unchanged, 1,281,167 x 2048 from lists 812 -> 723.))
+// 60,000 x 784 21.4 -> 18.7 ms, 512,000 x 50 unchanged, 1,281,167 x 2048 from lists 812 -> 723.)
 constexpr uint64_t NO_PAIR = ~0ull;
 __device__ __forceinline__ uint64_t dense_pair(float nq, float nj, float dot, bool self, int j)
 {
@@ -1180,7 +1180,8 @@ __global__ __launch_bounds__(256) void knn_compact(float *__restrict__ tau, int 
     }
 }
 
-// (registers for at least twice k' pairs, so that a round makes headway; kp <= MAX_KP)
+// (beside k' survivors a round takes in 192 new pairs at least: 512 - 320, 1024 - 832, 4096 - 1920; an ordinary pass has
+// some COMPACT_SLACK of them, one or two rounds)
 // dense: the pass behind a first launch, up to DBC pairs a row
 static void launch_compact(float *tau, int *cnt, uint64_t *cand, int cap, int kp, int rows, const int *list, const int *count,
                            bool dense, hipStream_t s)
@@ -1196,7 +1197,7 @@ static void launch_compact(float *tau, int *cnt, uint64_t *cand, int cap, int kp
         hipLaunchKernelGGL(knn_compact<64>, grid, dim3(256), 0, s, tau, cnt, cand, cap, kp, rows, list, count);
 }
 
-// Exact distances of the candidates, final order, certificate.  One block per query.
+// Exact distances of the candidates, final order, certificate.  One workgroup per query.
 // Query number i = q0 + row is row qmap[i] of X (row i if qmap is null); candidate number j is row cmap[j] of Y
 // (row j); distances are taken from those rows, equal distances are ordered by the candidates' row numbers, which
 // are also what is written, to row omap[i] (row i) of the result.  n_all: how many candidates a query can have at
@@ -1703,7 +1704,7 @@ __global__ __launch_bounds__(128) void sym_sort_rows(const int32_t *__restrict__
 // The rows on the list, a workgroup of 1024 lanes each: runs of SORT_CAP entries are sorted in LDS and left in scratch,
 // then an entry's place is its place in its own run plus, by binary search, the number of smaller entries in every other
 // run (columns are different, so places are).  (Ranking by one comparison per pair of entries let the longest row of
-// 512,000 points in four wide clusters hold the whole launch up: 20.5 of 205 ms, now 193 in all.))
+// 512,000 points in four wide clusters hold the whole launch up: 20.5 of 205 ms, now 193 in all.)
 __global__ __launch_bounds__(1024) void sym_sort_long(const int32_t *__restrict__ row_ptr, int n, int32_t *__restrict__ col,
                                                       float *__restrict__ val, uint64_t *__restrict__ scratch,
                                                       const int *__restrict__ long_rows, const int *__restrict__ long_count)
