@@ -32,30 +32,13 @@
 #include <math.h>
 
 constexpr int WALK_STACK = 512;      // stack entries
-constexpr int WALK_STACK_SHARED = 256;   // the same for one of several waves of a group
 constexpr int WALK_SLACK = 3 * MAX_GRID_BITS;   // head room for a depth-first descent (3 entries per level)
 constexpr int WALK_PEND = 128;       // pending list entries
 constexpr int WALK_FAST_LEAF = 8;    // leaves up to this size are copied by their own lane
 constexpr int WALK_CLIST = 96;       // accepted cells waiting for the drain (16 B each), >= 64
-constexpr int WALK_CLIST_SHARED = 64;
-constexpr int WALK_SHARE = 4;        // waves of a shared group
-constexpr int WALK_SPLIT = 20;       // waiting cells per wave at which the waves of a shared group part (12 and 32: both 2 % longer)
 constexpr int WALK_PLIST = 512;      // points of opened leaves waiting (8 B each), >= 64 * WALK_FAST_LEAF
 static_assert(WALK_CLIST >= WAVE && WALK_PLIST >= WAVE * WALK_FAST_LEAF, "one round must fit");
 static_assert(WAVE * WALK_FAST_LEAF < 65536, "two counts share one prefix sum");
-
-// Orders a wave's own LDS accesses.  A workgroup of one wave uses the workgroup barrier (no instruction at all); the
-// waves of a larger one walk at their own pace, and a wave's LDS instructions execute in program order anyway.
-template <int WAVES>
-__device__ __forceinline__ void lds_turn()
-{
-    if (WAVES == 1) {
-        __syncthreads();
-    } else {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
-}
 
 // side^2 < theta^2 * d2, with d2 = fma(dy, dy, dx*dx): one rounding per operation.
 __device__ __forceinline__ float dist2_rounded(float dx, float dy)
@@ -70,21 +53,6 @@ __device__ __forceinline__ bool passes(float side2, float theta2, float d2)
 #pragma clang fp contract(off)
     float rhs = theta2 * d2;
     return side2 < rhs;
-}
-
-// Smallest / largest value of the wave, the same in every lane (shifts inside the rows of sixteen lanes, then the rows'
-// last lanes; a lane without a partner keeps its own value).  All lanes must be active.
-template <bool MAX>
-__device__ __forceinline__ float wave_extreme(float v)
-{
-    auto with = [&](int o) { v = MAX ? fmaxf(v, __int_as_float(o)) : fminf(v, __int_as_float(o)); };
-    with(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x111, 0xF, 0xF, false));
-    with(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x112, 0xF, 0xF, false));
-    with(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x114, 0xF, 0xF, false));
-    with(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x118, 0xF, 0xF, false));
-    with(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x142, 0xA, 0xF, false));
-    with(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x143, 0xC, 0xF, false));
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), WAVE - 1));
 }
 
 // One interaction: y_cell (c.x, c.y) with weight c.z = N_cell.
@@ -111,11 +79,10 @@ __device__ __forceinline__ float wave_extreme(float v)
 
 // lanes = points: every lane adds the listed cells' (points') contributions for its own point.
 // Two register sets take turns: one is filled from LDS while the other is used.
-template <int WAVES>
 __device__ __forceinline__ void drain_cells(const float4 *__restrict__ list, int cnt, float x, float y, float &fx,
                                             float &fy, float &z)
 {
-    lds_turn<WAVES>();
+    __syncthreads();
     int e = 0;
     if (cnt >= 8) {
         float4 a0 = list[0], a1 = list[1], a2 = list[2], a3 = list[3];
@@ -131,14 +98,13 @@ __device__ __forceinline__ void drain_cells(const float4 *__restrict__ list, int
         const float4 c = list[e];
         TSNE_INTERACT(c)
     }
-    lds_turn<WAVES>();
+    __syncthreads();
 }
 
-template <int WAVES>
 __device__ __forceinline__ void drain_points(const float2 *__restrict__ list, int cnt, float x, float y, float &fx,
                                              float &fy, float &z)
 {
-    lds_turn<WAVES>();
+    __syncthreads();
     int e = 0;
     if (cnt >= 8) {
         float2 a0 = list[0], a1 = list[1], a2 = list[2], a3 = list[3];
@@ -154,30 +120,10 @@ __device__ __forceinline__ void drain_points(const float2 *__restrict__ list, in
         const float2 c = list[e];
         TSNE_INTERACT1(c)
     }
-    lds_turn<WAVES>();
-}
-
-// Of `count` waiting cells a wave keeps the ones whose place is its own number modulo WAVES, moved to the front in order.
-template <int WAVES>
-__device__ __forceinline__ int keep_share(uint32_t *list, int count, int lane, int wv)
-{
-    const int kept = (count - wv + WAVES - 1) / WAVES;       // (count >= wv: otherwise 0 or less)
-    for (int base = 0; base < kept; base += WAVE) {          // place i comes from i WAVES + wv >= i
-        const int i = base + lane;
-        const uint32_t v = i < kept ? list[i * WAVES + wv] : 0u;
-        lds_turn<WAVES>();
-        if (i < kept) list[i] = v;
-        lds_turn<WAVES>();
-    }
-    return max(kept, 0);
+    __syncthreads();
 }
 
 // The walk of one group g.  stack / pend / pts / clist / plist are the wave's LDS arrays.
-// WAVES > 1: that many waves of one workgroup share the group.  Until WALK_SPLIT cells per wave are waiting they all do
-// the same rounds, and what a round decides is put on the lists of the wave that its lane belongs to; then each keeps its
-// share of the waiting cells, which are the roots of disjoint subtrees, and walks on alone.  The decisions about a cell
-// do not depend on who takes it, so forces and Z are sums of the same terms.
-template <int WAVES>
 __device__ __forceinline__ void walk_group(const int g, uint32_t *stack, uint32_t *pend, float2 *pts, float4 *clist,
                                            float2 *plist,
                                            const Cell *__restrict__ cells, const float2 *__restrict__ Ys,
@@ -185,36 +131,33 @@ __device__ __forceinline__ void walk_group(const int g, uint32_t *stack, uint32_
                                            float theta2, const uint32_t *__restrict__ ncells, uint32_t cap_cells,
                                            float2 *__restrict__ R, double *__restrict__ zpart, uint32_t *status)
 {
-    constexpr int STACK = WAVES > 1 ? WALK_STACK_SHARED : WALK_STACK, CLIST = WAVES > 1 ? WALK_CLIST_SHARED : WALK_CLIST;
-    static_assert(STACK - WALK_SLACK >= 4 && CLIST >= WAVE, "a round must fit");
-    const int lane = (int)threadIdx.x & (WAVE - 1), wv = WAVES > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
+    const int lane = (int)threadIdx.x;
     const int p = g * WAVE + lane;
     const bool valid = p < n;
     const uint32_t m_cells = *ncells;
     if (m_cells > cap_cells || m_cells == 0u) {   // tree did not fit: flagged by the build, produce zeros
-        if (valid && wv == 0) R[min(perm[p], (uint32_t)n - 1u)] = make_float2(0.f, 0.f);
-        if (lane == 0 && wv == 0) zpart[g] = 0.0;
+        if (valid) R[min(perm[p], (uint32_t)n - 1u)] = make_float2(0.f, 0.f);
+        if (lane == 0) zpart[g] = 0.0;
         return;
     }
-    lds_turn<WAVES>();   // the previous group of this wave is done with the LDS arrays
+    __syncthreads();   // the previous group of this wave is done with the LDS arrays
     // own point; idle lanes of the last group shadow its first point and are never written out
     const float2 me = Ys[valid ? p : g * WAVE];
     const float x = me.x, y = me.y;
     pts[lane] = me;
-    const float bx0 = wave_extreme<false>(x), bx1 = wave_extreme<true>(x);
-    const float by0 = wave_extreme<false>(y), by1 = wave_extreme<true>(y);
+    const float bx0 = wave_min(x), bx1 = wave_max(x), by0 = wave_min(y), by1 = wave_max(y);
     const float W = root->z;
     // z: the terms of one batch in single precision, moved to the double zsum after every batch (a point's sum over
     // tens of thousands of nearly equal terms -- theta = 0, or Y0 where every q is close to 1 -- otherwise picks up
     // the same rounding error at every addition: 1e-4 of Z at 20,000 points).  Starts at -1: the point meets itself
     // among the members of its own leaf.
     float fx = 0.f, fy = 0.f, z = 0.f;
-    double zsum = wv == 0 ? -1.0 : 0.0;
+    double zsum = -1.0;
     int sp = 1, np = 0, icc = 0, icp = 0;   // wave-uniform; kept in scalar registers via readfirstlane
-    bool overflow = false, split = WAVES == 1;
+    bool overflow = false;
     uint32_t rounds = 0;
     if (lane == 0) stack[0] = 0u;
-    lds_turn<WAVES>();
+    __syncthreads();
     // four members of the group used as quick witnesses: if Eq. (14) fails for one of them the
     // cell is rejected for the group without looking at the other 60
     const float2 w0 = pts[0], w1 = pts[21], w2 = pts[42], w3 = pts[63];
@@ -227,8 +170,8 @@ __device__ __forceinline__ void walk_group(const int g, uint32_t *stack, uint32_
         // cells as still leave WALK_SLACK entries free afterwards whatever they push; when not
         // even one cell fits that rule the wave takes the single top cell per round -- plain
         // depth-first search, which adds at most 3 entries per level below the popped cell
-        // (<= 69 for 24 levels) before it shrinks again.  So sp never passes STACK - 3.
-        const int room = STACK - WALK_SLACK - sp;
+        // (<= 69 for 24 levels) before it shrinks again.  So sp never passes WALK_STACK - 3.
+        const int room = WALK_STACK - WALK_SLACK - sp;
         const bool pressure = room < 3;
         const bool from_pending = room >= 4 && (np >= WAVE || sp == 0);
         // (np >= 64 in a stack round only happens when the stack is nearly full: settle at once,
@@ -274,10 +217,9 @@ __device__ __forceinline__ void walk_group(const int g, uint32_t *stack, uint32_
                                    fminf(dist2_rounded(w2.x - cx, w2.y - cy), dist2_rounded(w3.x - cx, w3.y - cy)));
             decided = pass || !passes(side2, theta2, dw);
         }
-        const bool mine = WAVES == 1 || split || lane % WAVES == wv;
-        const bool acc = act && pass && mine;
+        const bool acc = act && pass;
         const bool und = act && !decided;
-        const bool open = act && decided && !pass && leaf && mine;
+        const bool open = act && decided && !pass && leaf;
         const bool desc = act && decided && !pass && !leaf;
         const bool ofast = open && cnt <= (uint32_t)WALK_FAST_LEAF;
         const uint64_t macc = __ballot(acc);
@@ -289,10 +231,10 @@ __device__ __forceinline__ void walk_group(const int g, uint32_t *stack, uint32_
         both_tot = __builtin_amdgcn_readfirstlane(both_tot);
         const int moff = both_off & 0xFFFF, mtot = both_tot & 0xFFFF;
         const int nacc = __popcll(macc);
-        if (icc + nacc > CLIST) { drain_cells<WAVES>(clist, icc, x, y, fx, fy, z); icc = 0; zsum += (double)z; z = 0.f; }
+        if (icc + nacc > WALK_CLIST) { drain_cells(clist, icc, x, y, fx, fy, z); icc = 0; zsum += (double)z; z = 0.f; }
         if (acc) clist[icc + __popcll(macc & lanemask_lt())] = make_float4(cx, cy, (float)cnt, 0.f);
         icc = __builtin_amdgcn_readfirstlane(icc + nacc);
-        if (icp + mtot > WALK_PLIST) { drain_points<WAVES>(plist, icp, x, y, fx, fy, z); icp = 0; zsum += (double)z; z = 0.f; }
+        if (icp + mtot > WALK_PLIST) { drain_points(plist, icp, x, y, fx, fy, z); icp = 0; zsum += (double)z; z = 0.f; }
         if (ofast) {
             float2 q[WALK_FAST_LEAF];
 #pragma unroll
@@ -318,7 +260,7 @@ __device__ __forceinline__ void walk_group(const int g, uint32_t *stack, uint32_
             const int boff = wave_excl_scan(big ? (int)cnt : 0, &tbig);
             tbig = __builtin_amdgcn_readfirstlane(tbig);
             for (int base = 0; base < tbig;) {
-                if (WALK_PLIST - icp < WAVE) { drain_points<WAVES>(plist, icp, x, y, fx, fy, z); icp = 0; zsum += (double)z; z = 0.f; }
+                if (WALK_PLIST - icp < WAVE) { drain_points(plist, icp, x, y, fx, fy, z); icp = 0; zsum += (double)z; z = 0.f; }
                 const int take = min(tbig - base, WALK_PLIST - icp);
                 for (int k = 0; k < take; k += WAVE) {
                     const int t = base + k + lane;
@@ -340,7 +282,7 @@ __device__ __forceinline__ void walk_group(const int g, uint32_t *stack, uint32_
         }
         // children of rejected inner cells
         const int coff = both_off >> 16, ctot = both_tot >> 16;
-        if (sp + ctot > STACK) { overflow = true; break; }   // unreachable for a well-formed tree
+        if (sp + ctot > WALK_STACK) { overflow = true; break; }   // unreachable for a well-formed tree
         if (desc) {
             int o = sp + coff;
             stack[o++] = id + 1u;
@@ -349,36 +291,16 @@ __device__ __forceinline__ void walk_group(const int g, uint32_t *stack, uint32_
             if (cb.w != TSNE_NONE) stack[o++] = cb.w;
         }
         sp = __builtin_amdgcn_readfirstlane(sp + ctot);
-        lds_turn<WAVES>();
-        if (WAVES > 1 && !split && sp + np >= WALK_SPLIT * WAVES) {
-            sp = __builtin_amdgcn_readfirstlane(keep_share<WAVES>(stack, sp, lane, wv));
-            np = __builtin_amdgcn_readfirstlane(keep_share<WAVES>(pend, np, lane, wv));
-            split = true;
-        }
+        __syncthreads();
     }
     if (overflow) {
         if (lane == 0) atomicOr(status, TSNE_STATUS_WALK_OVERFLOW);
         fx = fy = 0.f; z = 0.f; zsum = 0.0; icc = icp = 0;
     }
-    drain_cells<WAVES>(clist, icc, x, y, fx, fy, z);
+    drain_cells(clist, icc, x, y, fx, fy, z);
     zsum += (double)z; z = 0.f;
-    drain_points<WAVES>(plist, icp, x, y, fx, fy, z);
+    drain_points(plist, icp, x, y, fx, fy, z);
     zsum += (double)z;
-    if constexpr (WAVES > 1) {
-        // the waves' sums, added in the order of the waves (their lists of cells are free by now)
-        float4 *out = clist;
-        out[lane] = make_float4(fx, fy, __int_as_float(__double2loint(zsum)), __int_as_float(__double2hiint(zsum)));
-        const bool lost = __syncthreads_or(overflow);
-        if (wv != 0) return;
-#pragma unroll
-        for (int k = 1; k < WAVES; ++k) {
-            const float4 o = clist[k * CLIST + lane];
-            fx += o.x;
-            fy += o.y;
-            zsum += __hiloint2double(__float_as_int(o.w), __float_as_int(o.z));
-        }
-        if (lost) { fx = fy = 0.f; zsum = 0.0; }
-    }
     if (valid) R[min(perm[p], (uint32_t)n - 1u)] = make_float2(fx, fy);
     double zd = wave_sum(valid ? zsum : 0.0);
     if (lane == 0) zpart[g] = zd;
@@ -401,7 +323,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(5))) __launch_bounds__(WAVE) void 
     __shared__ float2 plist[WALK_PLIST];
     const int ngroups = (n + WAVE - 1) / WAVE;
     if (!counter) {
-        walk_group<1>((int)blockIdx.x, stack, pend, pts, clist, plist, cells, Ys, perm, n, root, theta2, ncells, cap_cells, R,
+        walk_group((int)blockIdx.x, stack, pend, pts, clist, plist, cells, Ys, perm, n, root, theta2, ncells, cap_cells, R,
                    zpart, status);
         return;
     }
@@ -416,7 +338,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(5))) __launch_bounds__(WAVE) void 
     const uint32_t cls = blockIdx.x % WALK_COUNTERS, dealt = gridDim.x / WALK_COUNTERS;
     uint32_t g = blockIdx.x;
     while (g < (uint32_t)ngroups) {
-        walk_group<1>((int)g, stack, pend, pts, clist, plist, cells, Ys, perm, n, root, theta2, ncells, cap_cells, R, zpart,
+        walk_group((int)g, stack, pend, pts, clist, plist, cells, Ys, perm, n, root, theta2, ncells, cap_cells, R, zpart,
                    status);
         // lane 0 draws the next group of the class; every lane reads the number back from LDS
         __syncthreads();
@@ -424,23 +346,6 @@ __global__ __attribute__((amdgpu_waves_per_eu(5))) __launch_bounds__(WAVE) void 
         __syncthreads();
         g = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_group);
     }
-}
-
-// WAVES waves a group, for embeddings with so few groups that one wave each would leave most of the chip idle.
-template <int WAVES>
-__global__ __attribute__((amdgpu_waves_per_eu(5))) __launch_bounds__(WAVE * WAVES) void bh_walk_shared(
-    const Cell *__restrict__ cells, const float2 *__restrict__ Ys, const uint32_t *__restrict__ perm, int n,
-    const float4 *__restrict__ root, float theta2, const uint32_t *__restrict__ ncells, uint32_t cap_cells,
-    float2 *__restrict__ R, double *__restrict__ zpart, uint32_t *status)
-{
-    __shared__ uint32_t stack[WAVES][WALK_STACK_SHARED];
-    __shared__ uint32_t pend[WAVES][WALK_PEND];
-    __shared__ float2 pts[WAVES][WAVE];
-    __shared__ float4 clist[WAVES][WALK_CLIST_SHARED];
-    __shared__ float2 plist[WAVES][WALK_PLIST];
-    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    walk_group<WAVES>((int)blockIdx.x, stack[w], pend[w], pts[w], clist[w], plist[w], cells, Ys, perm, n, root, theta2,
-                      ncells, cap_cells, R, zpart, status);
 }
 
 // Z = sum of the per-group partial sums, in a fixed order (thread t takes groups t, t + 1024, ...,
@@ -474,18 +379,9 @@ hipError_t launch_walk(tsne_ctx *c, hipStream_t s)
     const bool resident = c->p.walk_resident > 0 && ngroups > c->p.walk_resident * c->num_cu &&
                           c->p.walk_resident * c->num_cu >= WALK_COUNTERS;
     const int grid = resident ? c->p.walk_resident * c->num_cu / WALK_COUNTERS * WALK_COUNTERS : ngroups;
-    // Few points: a wave's walk is a chain of some fifteen dependent rounds, 0.5 to 1 us each, that nothing hides while
-    // a compute unit holds less than a wave a SIMD.  Four waves a group, as long as all of them are resident at once
-    // beside the attraction (27 KB of LDS a group, four groups a unit): an iteration of 2000 points takes 96 -> 90 us,
-    // of 30,011 174 -> 157, of 60,000 170 -> 158; of 100,000, beyond the line, 174 -> 185.  (Two waves 93 / 173 / 177,
-    // eight 91 / 169 / 197.)
-    if (!resident && ngroups <= 4 * c->num_cu)
-        hipLaunchKernelGGL(bh_walk_shared<WALK_SHARE>, dim3(ngroups), dim3(WAVE * WALK_SHARE), 0, s, c->cells, c->Ys, c->perm, n,
-                           c->root, theta2, c->ncells, (uint32_t)c->cap_cells, c->R, c->zpart, c->status);
-    else
-        hipLaunchKernelGGL(bh_walk, dim3(grid), dim3(WAVE), 0, s, c->cells, c->Ys, c->perm, n, c->root,
-                           theta2, c->ncells, (uint32_t)c->cap_cells, c->R, c->zpart, c->status,
-                           resident ? c->walk_counter : (uint32_t *)nullptr);
+    hipLaunchKernelGGL(bh_walk, dim3(grid), dim3(WAVE), 0, s, c->cells, c->Ys, c->perm, n, c->root,
+                       theta2, c->ncells, (uint32_t)c->cap_cells, c->R, c->zpart, c->status,
+                       resident ? c->walk_counter : (uint32_t *)nullptr);
     hipLaunchKernelGGL(z_final, dim3(1), dim3(1024), 0, s, c->zpart, ngroups, c->Z);
     return hipGetLastError();
 }
