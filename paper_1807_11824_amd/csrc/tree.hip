@@ -5,7 +5,7 @@
 //   bbox_partial / bbox_final   step 1   min/max reduction -> root square (power-of-two side)
 //   morton_encode_hist          step 2a  grid coordinates (up to 24 bits per axis), bit-interleaved key
 //   radix_hist / _scan / _scatter  step 4  stable LSD radix sort, 11 bits a pass
-//   small_root_keys_sort        steps 1, 2a, 4 in one launch of one workgroup, for few points
+//   rank_tiles / _samples / _merge  steps 1, 2a, 4 by counting smaller keys, for up to 131,072 points
 //   gather_levels               step 2b  which cells start at each sorted position
 //   downsweep                   step 3   prefix sums: cell numbering and running coordinate sums
 //   write_cells                 steps 2c+3  cell records: members, count, centre of mass, children
@@ -21,6 +21,8 @@
 // sum over "cells opened at p" numbers the whole tree, and the centre of mass of any cell is a
 // difference of two entries of the double-precision running sum of the sorted coordinates.
 #include "tsne_internal.h"
+
+#include <algorithm>
 
 #include <math.h>
 
@@ -126,121 +128,244 @@ __device__ __forceinline__ uint64_t grid_key(float2 y, float4 r, uint32_t qmax)
     return spread24(grid_coord(y.x, r.x, r.w, qmax)) | (spread24(grid_coord(y.y, r.y, r.w, qmax)) << 1);
 }
 
-// ------------------------------------------------------------------ few points: one workgroup does it all
-// Root square, keys and the sort in one launch, for n <= SMALL_SORT_MAX: the words (key, slot) sit
-// in LDS (all different, so any sorting network gives the order of a stable sort by key), padded
-// with all-ones to m, the power of two >= n.  Same root, same keys and same order as bbox_final +
-// morton_encode_hist + the radix passes.
+// ------------------------------------------------------------------ few points: order by counting
+// Up to RANK_MAX points the radix passes would be a dozen launches that are far too short to fill the chip.  The words
+// are all different, so a word's place is the number of smaller words, and counting is what an idle chip has room for:
 //
-// The network is the bitonic one.  A thread holds E = 2^LOGE pairs that differ in LOGE
-// neighbouring index bits, so one trip through LDS serves LOGE exchange distances; one padding
-// slot after every eight keeps the lanes of a wave on different banks whichever bits they are.
-__device__ __forceinline__ int small_sort_slot(int i) { return i + (i >> 3); }
+//   rank_tiles     root square, keys and the order inside tiles of RANK_TILE points (n <= SMALL_SORT_MAX: all points are
+//                  one tile, and this is the whole sort).  A workgroup holds its tile's words in LDS and counts for
+//                  `points` of them; a thread compares one word with one segment of the tile.
+//   rank_samples   every RANK_GAP-th word of the sorted tiles, in order, by the same count
+//   rank_merge     a bucket of the sorted samples per workgroup: finds the piece of every tile that falls into it,
+//                  collects the pieces, counts again, and writes its stretch of the order.  The number of words below
+//                  the bucket is the sum of the pieces' starts, so no bucket waits for another.
+//
+// A tile's words between two of its samples are at most RANK_GAP - 1, so a bucket of s samples holds at most
+// RANK_GAP s + (RANK_GAP - 1) tiles words, whatever the embedding looks like.  Where the samples of a tile start
+// differs from tile to tile (rank_offset): with equal starts tiles of the same distribution would all have their
+// samples at the same quantiles and nothing in between, and a few buckets would hold most of the words.
+// Same root, keys and order as bbox_final + morton_encode_hist + the radix passes.  25 iterations of a run: 60,000 points
+// 4.28 -> 3.46 ms, 30,011 4.25 -> 3.35, 100,000 4.35 -> 3.85 (three launches where there were fourteen); 2000 points 2.42
+// -> 2.27 (before, one workgroup sorted up to 8192 words in LDS).  Beyond RANK_MAX there are more tiles than a wave scans, the counting grows with the
+// number of tiles, and the radix passes have enough to do.
+constexpr int RANK_THREADS = 512, RANK_TILE = 1024, RANK_GAP = 64, RANK_PER_TILE = RANK_TILE / RANK_GAP;
+constexpr int RANK_BUCKETS = 256;              // most workgroups of rank_merge: about one per compute unit
+constexpr int RANK_MAX = RANK_SORT_MAX;
+static_assert(RANK_MAX <= 2 * WAVE * RANK_TILE, "rank_merge scans two tiles a lane of one wave");
 
-template <int LOGE>
-__device__ __forceinline__ void bitonic_trip(unsigned long long *pairs, int t, int b_lo, int nsteps, int k)
+__host__ __device__ inline int rank_offset(int tile) { return (tile * 39) & (RANK_GAP - 1); }   // (64 / golden ratio, odd)
+
+// words[seg * len .. + len) below `own`; len is even, the words are 16-byte aligned
+__device__ __forceinline__ uint32_t count_below(const uint64_t *words, int len, uint64_t own)
 {
-    constexpr int E = 1 << LOGE;
-    const int base = ((t >> b_lo) << (b_lo + LOGE)) | (t & ((1 << b_lo) - 1));
-    unsigned long long v[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = pairs[small_sort_slot(base | (e << b_lo))];
-    // direction of the run of length k a pair belongs to: one per thread unless k's bit is among the E's
-    if ((k >> (b_lo + LOGE)) != 0) {
-        const bool up = (base & k) == 0;
-#pragma unroll
-        for (int c = LOGE - 1; c >= 0; --c) {
-            if (c < nsteps) {
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    if (e & (1 << c)) continue;
-                    unsigned long long a = v[e], b = v[e | (1 << c)];
-                    const bool sw = (a > b) == up;
-                    v[e] = sw ? b : a;
-                    v[e | (1 << c)] = sw ? a : b;
-                }
-            }
-        }
-    } else {
-#pragma unroll
-        for (int c = LOGE - 1; c >= 0; --c) {
-            if (c < nsteps) {
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    if (e & (1 << c)) continue;
-                    const bool up = ((e << b_lo) & k) == 0;
-                    unsigned long long a = v[e], b = v[e | (1 << c)];
-                    const bool sw = (a > b) == up;
-                    v[e] = sw ? b : a;
-                    v[e | (1 << c)] = sw ? a : b;
-                }
-            }
-        }
+    uint32_t below = 0;
+#pragma unroll 8
+    for (int j = 0; j < len; j += 2) {
+        const ulonglong2 w = *reinterpret_cast<const ulonglong2 *>(words + j);
+        below += w.x < own ? 1u : 0u;
+        below += w.y < own ? 1u : 0u;
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e) pairs[small_sort_slot(base | (e << b_lo))] = v[e];
+    return below;
 }
 
-// blockDim.x = m >> LOGE
-template <int LOGE>
-__global__ __launch_bounds__(1024) void small_root_keys_sort(const float2 *__restrict__ Y, int n, int m,
-                                                             const float4 *__restrict__ part, int nparts, int bits,
-                                                             int ks, float4 *__restrict__ root,
-                                                             uint64_t *__restrict__ words_out, uint32_t *status)
+// Length of one of `segs` equal, even segments that cover len words (the array is padded to segs times this).
+__host__ __device__ inline int rank_segment(int len, int segs) { return ((len + segs - 1) / segs + 1) & ~1; }
+
+// The workgroup's words are in LDS at `words`, padded with all-ones to whole segments; writes those numbered
+// p0 .. p0 + points - 1 to out[their rank].  rk: `points` counters.
+__device__ __forceinline__ void rank_and_write(const uint64_t *words, int len, uint32_t *rk, int p0, int points,
+                                               uint64_t *__restrict__ out)
 {
-    extern __shared__ unsigned long long pairs[];
-    __shared__ float4 smn[16], smx[16];
+    const int tid = (int)threadIdx.x, segs = RANK_THREADS / points, seg = tid / points, p = tid % points;
+    const int slen = rank_segment(len, segs);
+    if (tid < points) rk[tid] = 0u;
+    __syncthreads();
+    const uint64_t own = words[min(p0 + p, len - 1)];
+    atomicAdd(&rk[p], count_below(words + seg * slen, slen, own));
+    __syncthreads();
+    if (tid < points && p0 + tid < len) out[min(rk[tid], (uint32_t)len - 1u)] = own;     // (seg 0: own is word p0 + tid)
+}
+
+__global__ __launch_bounds__(RANK_THREADS) void rank_tiles(const float2 *__restrict__ Y, int n, int tile, int points,
+                                                           const float4 *__restrict__ part, int nparts, int bits, int ks,
+                                                           float4 *__restrict__ root, uint64_t *__restrict__ out,
+                                                           uint32_t *status)
+{
+    extern __shared__ __align__(16) uint64_t rank_words[];
+    __shared__ float4 smm[RANK_THREADS / WAVE];
     __shared__ float4 sroot;
-    const int tid = threadIdx.x, nthr = blockDim.x;
-    {
+    __shared__ uint32_t rk[RANK_THREADS];
+    const int tid = (int)threadIdx.x;
+    const int pieces = (tile + points - 1) / points, t = (int)blockIdx.x / pieces, p0 = ((int)blockIdx.x % pieces) * points;
+    const int tile0 = t * tile, len = min(tile, n - tile0);
+    if (p0 >= len) return;                       // the same for every thread of the workgroup
+    if (nparts > 0) {
         float mnx = INFINITY, mny = INFINITY, mxx = -INFINITY, mxy = -INFINITY;
-        for (int i = tid; i < nparts; i += nthr) {
-            float4 a = part[2 * i], b = part[2 * i + 1];
+        for (int i = tid; i < nparts; i += RANK_THREADS) {
+            const float4 a = part[2 * i], b = part[2 * i + 1];
             mnx = fminf(mnx, a.x); mny = fminf(mny, a.y);
             mxx = fmaxf(mxx, b.x); mxy = fmaxf(mxy, b.y);
         }
         mnx = wave_min(mnx); mny = wave_min(mny); mxx = wave_max(mxx); mxy = wave_max(mxy);
-        const int w = tid >> 6, nw = nthr >> 6;
-        if (lane_id() == 0) { smn[w] = make_float4(mnx, mny, 0, 0); smx[w] = make_float4(mxx, mxy, 0, 0); }
+        if (lane_id() == 0) smm[tid >> 6] = make_float4(mnx, mny, mxx, mxy);
         __syncthreads();
         if (tid == 0) {
-            for (int k = 1; k < nw; ++k) {
-                mnx = fminf(mnx, smn[k].x); mny = fminf(mny, smn[k].y);
-                mxx = fmaxf(mxx, smx[k].x); mxy = fmaxf(mxy, smx[k].y);
+            for (int k = 1; k < RANK_THREADS / WAVE; ++k) {
+                mnx = fminf(mnx, smm[k].x); mny = fminf(mny, smm[k].y);
+                mxx = fmaxf(mxx, smm[k].z); mxy = fmaxf(mxy, smm[k].w);
             }
-            float4 r = root_square(mnx, mny, mxx, mxy, bits, status);
-            sroot = r;
-            *root = r;
+            sroot = root_square(mnx, mny, mxx, mxy, bits, status);
+            if (blockIdx.x == 0) *root = sroot;
         }
-        __syncthreads();
-    }
-    const float4 r = sroot;
-    const uint32_t qmax = (1u << bits) - 1u;
-    for (int i = tid; i < m; i += nthr) {
-        unsigned long long v = ~0ull;
-        if (i < n) v = (grid_key(Y[i], r, qmax) << ks) | (uint32_t)i;
-        pairs[small_sort_slot(i)] = v;
+    } else if (tid == 0) {
+        sroot = *root;                           // already in place
     }
     __syncthreads();
-    // stage s makes sorted runs of length 2^s out of pairs of runs of opposite direction: exchanges at
-    // distances 2^(s-1) .. 1, taken LOGE at a time from the top
-    for (int st = 1; (1 << st) <= m; ++st) {
-        for (int rem = st; rem > 0;) {
-            const int ns = rem < LOGE ? rem : LOGE;
-            bitonic_trip<LOGE>(pairs, tid, rem - ns, ns, 1 << st);
-            rem -= ns;
-            __syncthreads();
-        }
-    }
-    for (int i = tid; i < n; i += nthr) words_out[i] = pairs[small_sort_slot(i)];
+    const float4 r = sroot;
+    const uint32_t qmax = (1u << bits) - 1u;
+    const int segs = RANK_THREADS / points, padded = segs * rank_segment(len, segs);
+    for (int i = tid; i < padded; i += RANK_THREADS)
+        rank_words[i] = i < len ? (grid_key(Y[tile0 + i], r, qmax) << ks) | (uint32_t)(tile0 + i) : ~0ull;
+    rank_and_write(rank_words, len, rk, p0, points, out + tile0);
 }
 
-static size_t small_sort_lds(int m) { return 8 * (size_t)(m + (m >> 3)); }
-
-hipError_t small_sort_prepare()
+// number of samples of n words in tiles
+static int rank_sample_count(int n)
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&small_root_keys_sort<3>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_sort_lds(SMALL_SORT_MAX));
+    const int last = (n - 1) / RANK_TILE, left = n - last * RANK_TILE - rank_offset(last);
+    return last * RANK_PER_TILE + (left > 0 ? (left + RANK_GAP - 1) / RANK_GAP : 0);
+}
+
+__global__ __launch_bounds__(RANK_THREADS) void rank_samples(const uint64_t *__restrict__ tiles, int n, int count, int points,
+                                                             uint64_t *__restrict__ out)
+{
+    extern __shared__ __align__(16) uint64_t rank_words[];
+    __shared__ uint32_t rk[RANK_THREADS];
+    const int segs = RANK_THREADS / points, padded = segs * rank_segment(count, segs);
+    for (int i = (int)threadIdx.x; i < padded; i += RANK_THREADS) {
+        const int t = i / RANK_PER_TILE, at = t * RANK_TILE + (i % RANK_PER_TILE) * RANK_GAP + rank_offset(t);
+        rank_words[i] = i < count && at < n ? tiles[at] : ~0ull;
+    }
+    rank_and_write(rank_words, count, rk, (int)blockIdx.x * points, points, out);
+}
+
+// Most words of one of nb buckets (see above).
+static int rank_bucket_cap(int n, int nb)
+{
+    const int m = (n + RANK_TILE - 1) / RANK_TILE, q = rank_sample_count(n);
+    return RANK_GAP * ((q + nb - 1) / nb) + (RANK_GAP - 1) * m;
+}
+
+// cap: words that fit the LDS arrays (rank_bucket_cap), padded to whole segments of eight waves.
+__global__ __launch_bounds__(RANK_THREADS) void rank_merge(const uint64_t *__restrict__ tiles, int n,
+                                                           const uint64_t *__restrict__ samples, int count, int cap,
+                                                           uint64_t *__restrict__ out)
+{
+    constexpr int NW = RANK_THREADS / WAVE;
+    extern __shared__ __align__(16) uint64_t rank_words[];
+    uint32_t *rk = reinterpret_cast<uint32_t *>(rank_words + cap);
+    __shared__ int lb[2][RANK_MAX / RANK_TILE];     // first word of the bucket in every tile, first word behind it
+    __shared__ int off[RANK_MAX / RANK_TILE + 1];   // where the tile's piece starts in the bucket
+    __shared__ uint32_t sbase;
+    const int tid = (int)threadIdx.x, lane = tid & 63, w = tid >> 6, m = (n + RANK_TILE - 1) / RANK_TILE;
+    const int b = (int)blockIdx.x, nb = (int)gridDim.x;
+    const int s0 = (int)((long long)b * count / nb), s1 = (int)((long long)(b + 1) * count / nb);
+    const uint64_t lo = b == 0 ? 0ull : samples[s0], hi = b + 1 == nb ? ~0ull : samples[s1];
+    // Sixteen lanes a search, in three rounds: every 64th, every 4th, every word.  (The last bucket takes what is left,
+    // by its side and not by a comparison: a word may be all-ones.)
+    for (int g = tid >> 4; g < 2 * m; g += RANK_THREADS / 16) {
+        const int t = g >> 1, sub = lane & 15, len = min(RANK_TILE, n - t * RANK_TILE);
+        const uint64_t *words = tiles + (size_t)t * RANK_TILE;
+        const uint64_t want = (g & 1) ? hi : lo;
+        const bool rest = (g & 1) && b + 1 == nb;
+        int at = 0;
+#pragma unroll
+        for (int step = 64; step > 0; step = step == 64 ? 4 : step == 4 ? 1 : 0) {
+            const int q = at + (sub + 1) * step - 1;
+            const bool below = q < len && (step > 1 || sub < 4) && (rest || words[q] < want);
+            at += step * __popcll((__ballot(below) >> (lane & 48)) & 0xFFFFull);
+        }
+        if (sub == 0) lb[g & 1][t] = min(at, len);
+    }
+    __syncthreads();
+    if (w == 0) {
+        int v[2], base = 0;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int t = 2 * lane + k;
+            v[k] = t < m ? max(lb[1][t] - lb[0][t], 0) : 0;
+            base += t < m ? lb[0][t] : 0;
+        }
+        int total;
+        const int ex = wave_excl_scan(v[0] + v[1], &total);
+        base = wave_sum(base);
+        if (2 * lane < m) off[2 * lane] = ex;
+        if (2 * lane + 1 < m) off[2 * lane + 1] = ex + v[0];
+        if (lane == 0) { off[m] = total; sbase = (uint32_t)base; }
+    }
+    __syncthreads();
+    const int c = min(off[m], cap), slen = rank_segment(c, NW), padded = min(NW * slen, cap);
+    for (int i = tid; i < padded; i += RANK_THREADS) {
+        uint64_t v = ~0ull;
+        if (i < c) {
+            int t0 = 0, t1 = m;                    // off[t0] <= i < off[t1]
+            while (t1 - t0 > 1) {
+                const int mid = (t0 + t1) >> 1;
+                if (off[mid] <= i) t0 = mid; else t1 = mid;
+            }
+            v = tiles[min(t0 * RANK_TILE + min(lb[0][t0] + (i - off[t0]), RANK_TILE - 1), n - 1)];
+        }
+        rank_words[i] = v;
+        rk[i] = 0u;
+    }
+    __syncthreads();
+    for (int e = 0; e < c; e += WAVE) {
+        const uint64_t own = rank_words[min(e + lane, c - 1)];
+        const uint32_t below = count_below(rank_words + w * slen, slen, own);
+        if (e + lane < c) atomicAdd(&rk[e + lane], below);
+    }
+    __syncthreads();
+    for (int i = tid; i < c; i += RANK_THREADS) out[min(sbase + rk[i], (uint32_t)n - 1u)] = rank_words[i];
+}
+
+static size_t rank_lds(int len, int points) { const int segs = RANK_THREADS / points; return 8 * (size_t)(segs * rank_segment(len, segs)); }
+static int rank_merge_cap(int n, int nb) { return 8 * rank_segment(rank_bucket_cap(n, nb), 8); }
+// Points a workgroup counts for: a sixteenth of its threads' where all points are one tile, so that a few thousand of
+// them reach most of the chip; a quarter in tiles, where every workgroup of a tile works all its keys out again.
+constexpr int RANK_POINTS_ONE = 32, RANK_POINTS_TILED = 128;
+
+hipError_t rank_sort_prepare()
+{
+    hipError_t e;
+    if ((e = hipFuncSetAttribute(reinterpret_cast<const void *>(&rank_tiles), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)rank_lds(SMALL_SORT_MAX, RANK_POINTS_ONE))) != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&rank_merge), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               12 * rank_merge_cap(RANK_MAX, RANK_BUCKETS));
+}
+
+// The order of the points of c->Yi in c->words[c->sorted_buf], for n <= RANK_MAX (nparts = 0: the root square is in place).
+static hipError_t launch_rank_sort(tsne_ctx *c, hipStream_t s)
+{
+    const int n = c->p.n, B = c->p.morton_bits, ks = c->key_shift, nparts = c->root_fresh ? 0 : c->bbox_nparts;
+    c->root_fresh = 0;
+    if (n <= SMALL_SORT_MAX) {
+        hipLaunchKernelGGL(rank_tiles, dim3((n + RANK_POINTS_ONE - 1) / RANK_POINTS_ONE), dim3(RANK_THREADS),
+                           rank_lds(n, RANK_POINTS_ONE), s, c->Yi, n, n, RANK_POINTS_ONE, c->bbox_part, nparts, B, ks, c->root,
+                           c->words[0], c->status);
+        c->sorted_buf = 0;
+        return hipGetLastError();
+    }
+    const int m = (n + RANK_TILE - 1) / RANK_TILE, q = rank_sample_count(n);
+    const int nb = std::min(RANK_BUCKETS, (n + 127) / 128), cap = rank_merge_cap(n, nb);
+    uint64_t *samples = reinterpret_cast<uint64_t *>(c->hist);
+    hipLaunchKernelGGL(rank_tiles, dim3(m * (RANK_TILE / RANK_POINTS_TILED)), dim3(RANK_THREADS),
+                       rank_lds(RANK_TILE, RANK_POINTS_TILED), s, c->Yi, n, RANK_TILE, RANK_POINTS_TILED, c->bbox_part, nparts, B,
+                       ks, c->root, c->words[0], c->status);
+    hipLaunchKernelGGL(rank_samples, dim3((q + RANK_POINTS_ONE - 1) / RANK_POINTS_ONE), dim3(RANK_THREADS),
+                       rank_lds(q, RANK_POINTS_ONE), s, c->words[0], n, q, RANK_POINTS_ONE, samples);
+    hipLaunchKernelGGL(rank_merge, dim3(nb), dim3(RANK_THREADS), 12 * (size_t)cap, s, c->words[0], n, samples, q, cap, c->words[1]);
+    c->sorted_buf = 1;
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ radix sort (stable, LSD, 11 bits a pass)
@@ -1141,14 +1266,7 @@ hipError_t launch_tree_sort(tsne_ctx *c, hipStream_t s)
 {
     const int n = c->p.n, B = c->p.morton_bits, ks = c->key_shift;
     const float2 *Y = c->Yi;
-    if (n <= SMALL_SORT_MAX) {
-        int m = 512;
-        while (m < n) m <<= 1;
-        hipLaunchKernelGGL(small_root_keys_sort<3>, dim3(1), dim3(m >> 3), small_sort_lds(m), s, Y, n, m, c->bbox_part,
-                           c->bbox_nparts, B, ks, c->root, c->words[0], c->status);
-        c->sorted_buf = 0;
-        return hipGetLastError();
-    }
+    if (n <= RANK_MAX) return launch_rank_sort(c, s);
     if (!c->root_fresh)
         hipLaunchKernelGGL(bbox_final, dim3(1), dim3(c->bbox_nparts > 1024 ? 1024 : 256), 0, s, c->bbox_part, c->bbox_nparts, B,
                            c->root, c->status);

@@ -33,7 +33,8 @@ constexpr int SORT_THREADS = 512;
 constexpr int SORT_TILE_MIN = SORT_THREADS * 8;   // smallest tile of the sort (words per thread: 8, 10 or 12) ...
 constexpr int SORT_FINE_TILES = 256;              // ... unless tiles of 2 or 4 words a thread are no more than these
 constexpr int MAX_GRID_BITS = 24;        // a float has 24 significant bits
-constexpr int SMALL_SORT_MAX = 8192;  // up to here one workgroup finds root, keys and order in LDS
+constexpr int SMALL_SORT_MAX = 8192;  // up to here root, keys and order come out of one launch
+constexpr int RANK_SORT_MAX = 131072; // up to here the order is found by counting (rank_tiles and its kin)
 constexpr int LEVEL_THREADS = 256;
 constexpr int LEVEL_ITEMS = 4;
 constexpr int LEVEL_TILE = LEVEL_THREADS * LEVEL_ITEMS;
@@ -140,7 +141,7 @@ inline bool ft_possible(const tsne_params *p)
     return p->far_tiles != 1 && nrt * nct <= FT_MAX_TILES;
 }
 hipError_t attract_far_tiled_prepare();   // once per process, before the first launch
-hipError_t small_sort_prepare();          // likewise
+hipError_t rank_sort_prepare();           // likewise
 
 // inverted-file neighbour search (ivf.hip); return a tsne_error
 size_t ivf_workspace(int n, int d, int k, int nlist, int tau);

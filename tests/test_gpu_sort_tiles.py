@@ -9,7 +9,7 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [9217, 60000, 262144, 262145, 524288, 524289])
+@pytest.mark.parametrize("n", [8192, 8193, 9217, 32768, 60000, 131072, 131073, 262144, 262145, 524288, 524289])
 def test_order(n):
     Y = synth.clustered_embedding(n, n_clusters=40, seed=n)
     want = oracle.tree(Y, bits=22, leaf_cap=8)
