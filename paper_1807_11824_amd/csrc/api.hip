@@ -159,10 +159,11 @@ constexpr int NEV = 9;
 // on the second stream: the small far part beside the tree build (the tree kernels are short and
 // latency-bound; a few gathering workgroups do not slow them much) and the streaming part beside
 // the walk, whose arithmetic and the attraction's memory traffic use different parts of the chip.
-int enqueue_forces(tsne_ctx *c, const float *d_Y, hipEvent_t *ev, bool cached = false)
+int enqueue_forces(tsne_ctx *c, const float *d_Y, hipEvent_t *ev, bool cached, bool sum_z)
 {
     hipError_t e;
-    const bool two = c->p.overlap && c->stream2;
+    const bool together = walk_takes_attraction(c);   // few points: the attraction is part of the walk's launch
+    const bool two = c->p.overlap && c->stream2 && !together;
     hipStream_t sa = two ? c->stream2 : c->stream;   // where the attraction runs
     auto fork = [&](hipEvent_t evt) -> int {
         if ((e = hipEventRecord(evt, c->stream)) != hipSuccess) return fail_hip(c, e, "event record");
@@ -173,12 +174,20 @@ int enqueue_forces(tsne_ctx *c, const float *d_Y, hipEvent_t *ev, bool cached = 
     // (which hides behind it), not behind the walk.
     const bool tiles_early = two && c->ft_active && c->p.n > SMALL_SORT_MAX;
     auto farpart = [&]() -> int {
+        if (together) {                              // (nothing of its own to time)
+            if (ev) for (int q : {6, 7}) (void)hipEventRecord(ev[q], sa);
+            return TSNE_OK;
+        }
         if (ev) (void)hipEventRecord(ev[6], sa);
         if ((e = launch_attract_far(c, sa, tiles_early)) != hipSuccess) return fail_hip(c, e, "attract (far part)");
         if (ev) (void)hipEventRecord(ev[7], sa);
         return TSNE_OK;
     };
     auto mainpart = [&]() -> int {
+        if (together) {
+            if (ev) for (int q : {3, 4}) (void)hipEventRecord(ev[q], sa);
+            return TSNE_OK;
+        }
         if (ev) (void)hipEventRecord(ev[3], sa);
         if ((e = launch_attract_main(c, sa, !tiles_early)) != hipSuccess) return fail_hip(c, e, "attract");
         if (ev) (void)hipEventRecord(ev[4], sa);
@@ -196,7 +205,7 @@ int enqueue_forces(tsne_ctx *c, const float *d_Y, hipEvent_t *ev, bool cached = 
     if ((e = launch_tree_cells(c, c->stream)) != hipSuccess) return fail_hip(c, e, "tree cells");
     if (ev) (void)hipEventRecord(ev[1], c->stream);
     if (two && ((rc = fork(c->ev_fork2)) != TSNE_OK || (rc = mainpart()) != TSNE_OK)) return rc;
-    if ((e = launch_walk(c, c->stream)) != hipSuccess) return fail_hip(c, e, "walk");
+    if ((e = launch_walk(c, c->stream, together, sum_z)) != hipSuccess) return fail_hip(c, e, "walk");
     if (ev) (void)hipEventRecord(ev[2], c->stream);
     if (two) {
         if ((e = hipStreamWaitEvent(c->stream, c->ev_join, 0)) != hipSuccess) return fail_hip(c, e, "stream wait");
@@ -204,12 +213,9 @@ int enqueue_forces(tsne_ctx *c, const float *d_Y, hipEvent_t *ev, bool cached = 
         if ((rc = farpart()) != TSNE_OK || (rc = mainpart()) != TSNE_OK) return rc;
     }
     // Without renumbering, the attractive kernel of the NEXT call visits rows in this call's
-    // spatial order (the kernel has finished by now on either stream, so the array is free to
-    // overwrite).  With renumbering the slots themselves are ordered and rows go in slot order.
-    if (!c->reorder_on &&
-        (e = hipMemcpyAsync(c->row_order, c->perm, 4 * (size_t)c->p.n, hipMemcpyDeviceToDevice,
-                            c->stream)) != hipSuccess)
-        return fail_hip(c, e, "copy row order");
+    // spatial order (the kernel has finished by then on either stream, so the next tree build is free to
+    // overwrite the array it used).  With renumbering the slots themselves are ordered and rows go in slot order.
+    if (!c->reorder_on) std::swap(c->row_order, c->perm);
     c->tree_valid = 1;
     return TSNE_OK;
 }
@@ -446,7 +452,8 @@ int step_impl(tsne_ctx *c, float *d_Y, int32_t iter, bool cached, bool keep)
     if (c->tev && c->t_used < c->t_cap && (c->t_seen++ % c->t_every) == 0) ev = c->tev + NEV * c->t_used;
     const bool use = cached && c->yi_fresh;
     c->yi_fresh = 0;
-    int rc = enqueue_forces(c, d_Y, ev, use);
+    const bool sum_z = (c->p.n + WAVE - 1) / WAVE > UPDATE_Z_GROUPS;    // (otherwise the update adds Z up itself)
+    int rc = enqueue_forces(c, d_Y, ev, use, sum_z);
     if (rc != TSNE_OK) return rc;
     const float alpha = iter < c->p.exaggeration_iters ? c->p.exaggeration : 1.0f;
     const float mom = iter < c->p.momentum_switch_iter ? c->p.momentum_early : c->p.momentum_late;
@@ -454,7 +461,7 @@ int step_impl(tsne_ctx *c, float *d_Y, int32_t iter, bool cached, bool keep)
     // an iteration whose successor reads the embedding from the library's own copy (keep) need not
     // write the caller's array -- unless the slots are about to be renumbered, which starts from it
     const bool renumber_next = c->reorder_on && c->p.reorder_every > 0 && c->steps_since_reorder + 1 >= c->p.reorder_every;
-    hipError_t e = launch_update(c, d_Y, alpha, mom, keep ? 1 : 0, (!keep || renumber_next) ? 1 : 0, c->stream);
+    hipError_t e = launch_update(c, d_Y, alpha, mom, keep ? 1 : 0, (!keep || renumber_next) ? 1 : 0, !sum_z, c->stream);
     if (ev) { (void)hipEventRecord(ev[5], c->stream); c->t_used += 1; }
     if (e != hipSuccess) return fail_hip(c, e, "update");
     c->yi_fresh = keep ? 1 : 0;
@@ -549,7 +556,7 @@ int tsne_gradient(tsne_ctx *c, const float *d_Y, float *d_attr, float *d_rep, do
 {
     if (!c || !d_Y) return TSNE_EINVAL;
     if (!c->have_P) return fail(c, TSNE_ESTATE, "tsne_gradient: no P (call tsne_set_P first)");
-    int rc = enqueue_forces(c, d_Y, nullptr);
+    int rc = enqueue_forces(c, d_Y, nullptr, false, true);
     if (rc != TSNE_OK) return rc;
     const uint32_t *orig = c->orig[c->cur_state];
     hipError_t e = hipSuccess;

@@ -511,12 +511,14 @@ __device__ __forceinline__ int sign3(float v) { return v > 0.f ? 1 : (v < 0.f ? 
 // With `part` set the kernel also leaves what the next iteration starts from: the new point in
 // slot order (Yi) and the workgroup's bounding box, so that a run of several iterations neither
 // gathers Y again nor makes a separate pass for the box (Sec. III-C step 1).
+// SUM_Z: Z is added up from the groups' sums in every workgroup.
+template <bool SUM_Z>
 __global__ __launch_bounds__(256) void update_k(float2 *__restrict__ Y, const uint32_t *__restrict__ orig, float2 *Yi,
                                                 float2 *__restrict__ uY, float2 *__restrict__ gains,
                                                 const float2 *__restrict__ A, const float2 *__restrict__ R,
-                                                const double *__restrict__ Z, int n, float alpha, float momentum,
-                                                float lr, float gain_inc, float gain_dec, float gain_min,
-                                                float4 *__restrict__ part, uint32_t *status, int write_user)
+                                                const double *__restrict__ Z, const double *__restrict__ zpart,
+                                                int ngroups, int n, float alpha, float momentum, float lr,
+                                                float gain_inc, float gain_dec, float gain_min, float4 *__restrict__ part, uint32_t *status, int write_user)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = s < n;
@@ -525,8 +527,22 @@ __global__ __launch_bounds__(256) void update_k(float2 *__restrict__ Y, const ui
     const bool frozen = *status != 0u;
     float2 y = make_float2(0.f, 0.f);
     if (live) y = Yi[s];
+    double Zsum = 0.0;
+    if (SUM_Z) {
+        // z_final's sum, operation for operation: there thread t has the partial sum t and a wave adds its 64; here a
+        // wave stands for four of those.  8 KB at most, cheaper than one more launch between the walk and this one.
+        __shared__ double zs[UPDATE_Z_GROUPS / WAVE];
+#pragma unroll
+        for (int k = 0; k < UPDATE_Z_GROUPS / 256; ++k) {
+            const int g = 256 * k + (int)threadIdx.x;
+            const double v = wave_sum(g < ngroups ? zpart[g] : 0.0);
+            if (lane_id() == 0) zs[4 * k + (int)(threadIdx.x >> 6)] = v;
+        }
+        __syncthreads();
+        for (int k = 0; k < UPDATE_Z_GROUPS / WAVE; ++k) Zsum += zs[k];
+    }
     if (live && !frozen) {
-        const double Zd = *Z;
+        const double Zd = SUM_Z ? Zsum : *Z;
         const float invZ = Zd > 0.0 ? (float)(1.0 / Zd) : 0.f;    // a single point has no pairs: Z = 0, R = 0
         const float2 a = A[s], r = R[s];
         float2 g = gains[s], u = uY[s];
@@ -562,12 +578,13 @@ __global__ __launch_bounds__(256) void update_k(float2 *__restrict__ Y, const ui
     }
 }
 
-hipError_t launch_update(tsne_ctx *c, float *d_Y, float alpha, float momentum, int keep, int write_user, hipStream_t s)
+hipError_t launch_update(tsne_ctx *c, float *d_Y, float alpha, float momentum, int keep, int write_user, bool sum_z,
+                         hipStream_t s)
 {
     const int n = c->p.n, nb = (n + 255) / 256;
-    hipLaunchKernelGGL(update_k, dim3(nb), dim3(256), 0, s, (float2 *)d_Y, c->orig[c->cur_state], c->Yi,
-                       c->uYb[c->cur_state], c->gainsb[c->cur_state], c->A, c->R, c->Z, n, alpha, momentum, c->p.lr,
-                       c->p.gain_inc, c->p.gain_dec, c->p.gain_min, keep ? c->bbox_part : (float4 *)nullptr, c->status,
+    hipLaunchKernelGGL(sum_z ? update_k<true> : update_k<false>, dim3(nb), dim3(256), 0, s, (float2 *)d_Y, c->orig[c->cur_state], c->Yi,
+                       c->uYb[c->cur_state], c->gainsb[c->cur_state], c->A, c->R, c->Z, c->zpart, (n + WAVE - 1) / WAVE, n,
+                       alpha, momentum, c->p.lr, c->p.gain_inc, c->p.gain_dec, c->p.gain_min, keep ? c->bbox_part : (float4 *)nullptr, c->status,
                        write_user);
     if (keep) c->bbox_nparts = nb;
     return hipGetLastError();

@@ -160,11 +160,25 @@ hipError_t launch_gather_bbox(tsne_ctx *c, const float *d_Y, hipStream_t s);
 hipError_t launch_tree_root(tsne_ctx *c, hipStream_t s);
 hipError_t launch_tree_sort(tsne_ctx *c, hipStream_t s);
 hipError_t launch_tree_cells(tsne_ctx *c, hipStream_t s);
-hipError_t launch_walk(tsne_ctx *c, hipStream_t s);
+// What the attraction of a row needs when its workgroups share the walk's launch (walk_takes_attraction): rp, col and val
+// are the caller's P with rp_near null, otherwise the far part of the renumbered copy (val: of both parts).
+struct AttractRows {
+    const int32_t *rp, *col, *rp_near;
+    const uint16_t *col_near;
+    const float *val;
+    const float2 *Y;
+    float2 *A;
+};
+bool walk_takes_attraction(const tsne_ctx *c);
+hipError_t launch_walk_rows(tsne_ctx *c, hipStream_t s);
+constexpr int UPDATE_Z_GROUPS = 1024;   // up to so many partial sums of Z every workgroup of the update adds up for itself
+// attraction: with the rows of the attraction; sum_z: Z from the groups' sums as well (not needed if the update does that)
+hipError_t launch_walk(tsne_ctx *c, hipStream_t s, bool attraction, bool sum_z);
 // the far part of the renumbered P (no-op otherwise); tiles: the bucketed copy is summed here rather than in launch_attract_main
 hipError_t launch_attract_far(tsne_ctx *c, hipStream_t s, bool tiles);
 hipError_t launch_attract_main(tsne_ctx *c, hipStream_t s, bool tiles);
-hipError_t launch_update(tsne_ctx *c, float *d_Y, float alpha, float momentum, int keep, int write_user,
+// sum_z: Z is added up from the groups' sums (at most UPDATE_Z_GROUPS) instead of being read
+hipError_t launch_update(tsne_ctx *c, float *d_Y, float alpha, float momentum, int keep, int write_user, bool sum_z,
                          hipStream_t s);
 hipError_t launch_reorder(tsne_ctx *c, hipStream_t s, int tiles_mode);   // tiles_mode: 0 decide, 1 rows, 2 tiles
 hipError_t launch_graph_order(tsne_ctx *c, hipStream_t s);   // leaves the order in c->perm

@@ -1,0 +1,38 @@
+"""Sizes at which the launches of an iteration change: the attraction shares the walk's launch and the
+update adds Z up itself (up to 65,536 points).  Against the oracle, and one step against the update rule applied to
+tsne_gradient's forces."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import grid_bits, random_symmetric_csr, rel_l2
+from paper_1807_11824_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,renumber", [(2, False), (17, True), (4097, True), (65536, False), (65536, True), (65537, True)])
+def test_forces_and_one_step(n, renumber):
+    """Attraction and repulsion as in test_gpu_forces (1e-4); the step from the same forces in double: Y moves by
+    lr gain grad, of which every operation is one rounding (1e-5 of the largest move)."""
+    import torch
+    from paper_1807_11824_amd import Tsne
+    dev = torch.device("cuda:0")
+    Y = synth.clustered_embedding(n, n_clusters=min(n, 20), seed=n)
+    if n > 2:
+        rp, col, val = random_symmetric_csr(n, min(20, n - 1), seed=n)
+    else:
+        rp, col, val = np.array([0, 1, 2], np.int32), np.array([1, 0], np.int32), np.array([0.5, 0.5], np.float32)
+    ts = Tsne(n, max_nnz=len(col) if renumber else 0, graph_order_iters=8)
+    ts.set_P(*[torch.from_numpy(a).to(dev) for a in (rp, col, val)])
+    Yd = torch.from_numpy(Y).to(dev)
+    A, R, Z = [t.cpu().numpy().astype(np.float64) for t in ts.gradient(Yd)]
+    o = oracle.grad_bh(Y, rp, col, val.astype(np.float64), theta=0.5, leaf_cap=8, group=64, bits=grid_bits(n))
+    assert rel_l2(A, o["A"]) <= 1e-4 and rel_l2(R, o["R"]) <= 1e-4 and abs(Z[0] - o["Z"]) <= 1e-5 * o["Z"]
+    p = ts.params
+    grad = 4.0 * (p.exaggeration * A - R / Z[0])
+    move = -p.lr * np.where(grad == 0, p.gain_dec, 1.0 + p.gain_inc) * grad      # (velocity 0: the signs differ unless grad is 0)
+    ts.step(Yd, 0)
+    assert ts.status() == 0
+    assert np.abs(Yd.cpu().numpy() - (Y + move)).max() <= 1e-5 * np.abs(move).max() + 2.0 ** -23 * np.abs(Y + move).max()
+    ts.close()
