@@ -324,7 +324,7 @@ int tsne_create(tsne_ctx **out, const tsne_params *p, void *stream, void *d_work
             return TSNE_EHIP;
         }
     }
-    if (p->n <= RANK_SORT_MAX && (e = rank_sort_prepare()) != hipSuccess) {
+    if (p->n <= RANK_SORT_MAX && ((e = rank_sort_prepare()) != hipSuccess || (e = small_tree_prepare()) != hipSuccess)) {
         tsne_destroy(c);
         return TSNE_EHIP;
     }

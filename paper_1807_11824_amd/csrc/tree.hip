@@ -9,6 +9,7 @@
 //   gather_levels               step 2b  which cells start at each sorted position
 //   downsweep                   step 3   prefix sums: cell numbering and running coordinate sums
 //   write_cells                 steps 2c+3  cell records: members, count, centre of mass, children
+//   small_tree                  steps 2b, 2c, 3 in one launch of one workgroup, for up to 4096 points
 //
 // The sort works on one 64-bit word per point, (key << key_shift) | slot with key_shift = 64 - 2 bits:
 // the order of the words is the order by (key, slot), which is the stable order the tree is defined
@@ -1036,6 +1037,156 @@ __global__ __launch_bounds__(256) void write_cells(const uint64_t *__restrict__ 
     }
 }
 
+// ---- few points: levels, prefix sums and cells in one launch of one workgroup, everything the searches need in LDS.
+// (Four launches of a few microseconds each otherwise, all of them waiting for the one before: an iteration of 2000
+// points 91 -> 71 us.  Beyond SMALL_TREE_MAX points the arrays outgrow a compute unit's LDS.)  Coordinates are added up in the order
+// of gather_levels and downsweep, tile by tile, so that the centres of mass are the same to the bit.
+constexpr int SMALL_TREE_MAX = 4096, SMALL_TREE_THREADS = 1024, SMALL_TREE_MARGIN = LEVELS_WINDOW_MAXC + 1;
+static_assert(SMALL_TREE_MAX == SMALL_TREE_THREADS * LEVEL_ITEMS && SMALL_TREE_MAX == 4 * LEVEL_TILE, "four tiles");
+
+__host__ __device__ inline size_t small_tree_lds(int n)
+{
+    return 16 * (size_t)(n + 1) + 8 * (size_t)n + 4 * (size_t)(n + 1) + (size_t)(n + 2 * SMALL_TREE_MARGIN) + (size_t)n;
+}
+
+template <int CT>
+__global__ __launch_bounds__(SMALL_TREE_THREADS) void small_tree(const float2 *__restrict__ Y, const uint64_t *__restrict__ words,
+                                                                 int ks, int n, int B, int C, float2 *__restrict__ Ys,
+                                                                 uint32_t *__restrict__ perm, Cell *__restrict__ cells,
+                                                                 uint32_t cap_cells, uint32_t *__restrict__ ncells,
+                                                                 uint32_t *status)
+{
+    constexpr int MARGIN = SMALL_TREE_MARGIN, NW = SMALL_TREE_THREADS / WAVE;
+    extern __shared__ __align__(16) unsigned char tree_lds[];
+    double2 *ps = reinterpret_cast<double2 *>(tree_lds);                     // running sums of the coordinates
+    uint64_t *keys = reinterpret_cast<uint64_t *>(ps + n + 1);
+    uint32_t *seq = reinterpret_cast<uint32_t *>(keys + n);                  // first cell of every position
+    signed char *adj = reinterpret_cast<signed char *>(seq + n + 1);         // digits shared by neighbours (levels_window)
+    unsigned char *first_depth = reinterpret_cast<unsigned char *>(adj + n + 2 * MARGIN);
+    float2 *ysort = reinterpret_cast<float2 *>(ps);      // sorted points, until the running sums take their place
+    __shared__ double wx[NW], wy[NW], tx[NW], ty[NW];
+    __shared__ uint32_t wc[NW];
+    const int tid = (int)threadIdx.x, w = tid >> 6, tile = tid / LEVEL_THREADS, tt = tid % LEVEL_THREADS;
+    const int p0 = tid * LEVEL_ITEMS;
+    {
+        double gx = 0.0, gy = 0.0;
+#pragma unroll
+        for (int k = 0; k < LEVEL_ITEMS; ++k) {
+            const int p = tile * LEVEL_TILE + k * LEVEL_THREADS + tt;
+            if (p < n) {
+                const uint64_t word = words[p];
+                const uint32_t slot = min((uint32_t)(word & ((1ull << ks) - 1ull)), (uint32_t)n - 1u);
+                const float2 v = Y[slot];
+                keys[p] = word >> ks;
+                perm[p] = slot;
+                Ys[p] = v;
+                ysort[p] = v;
+                gx += (double)v.x; gy += (double)v.y;
+            }
+        }
+        gx = wave_sum(gx); gy = wave_sum(gy);
+        if (lane_id() == 0) { tx[w] = gx; ty[w] = gy; }
+    }
+    __syncthreads();
+    float2 y[LEVEL_ITEMS];
+#pragma unroll
+    for (int k = 0; k < LEVEL_ITEMS; ++k) y[k] = p0 + k < n ? ysort[p0 + k] : make_float2(0.f, 0.f);
+    for (int i = tid; i < n + 2 * MARGIN; i += SMALL_TREE_THREADS) {
+        const int q = i - MARGIN;
+        adj[i] = q < 0 || q + 1 >= n ? (signed char)-1 : (signed char)common_digits(keys[q], keys[q + 1], B);
+    }
+    __syncthreads();
+    uint32_t c[LEVEL_ITEMS];
+    double ax = 0.0, ay = 0.0;
+    uint32_t ac = 0;
+#pragma unroll
+    for (int k = 0; k < LEVEL_ITEMS; ++k) {
+        const int p = p0 + k;
+        c[k] = 0;
+        if (p < n) {
+            int tmin, tend;
+            levels_window<CT>(adj + MARGIN + p, B, C, &tmin, &tend);
+            first_depth[p] = (unsigned char)tmin;
+            c[k] = (uint32_t)(tend - tmin);
+        }
+        ax += (double)y[k].x; ay += (double)y[k].y; ac += c[k];
+    }
+    double ix = ax, iy = ay;
+    uint32_t icn = ac;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const double ux = __shfl_up(ix, o, WAVE), uy = __shfl_up(iy, o, WAVE);
+        const uint32_t uc = __shfl_up(icn, o, WAVE);
+        if (lane_id() >= o) { ix += ux; iy += uy; icn += uc; }
+    }
+    if (lane_id() == WAVE - 1) { wx[w] = ix; wy[w] = iy; wc[w] = icn; }
+    __syncthreads();
+    // the tiles before this one, as downsweep's first wave adds them (lanes 0 and 2, then 1 and 3)
+    auto before = [&](const double *v) {
+        auto of = [&](int b) { return ((v[4 * b] + v[4 * b + 1]) + v[4 * b + 2]) + v[4 * b + 3]; };
+        return tile == 0 ? 0.0 : tile == 1 ? of(0) : tile == 2 ? of(0) + of(1) : (of(0) + of(2)) + of(1);
+    };
+    double px = before(tx), py = before(ty);
+    uint32_t pc = 0, m = 0;
+    for (int k = 0; k < NW; ++k) {
+        if (k < w && k >= 4 * tile) { px += wx[k]; py += wy[k]; }
+        if (k < w) pc += wc[k];
+        m += wc[k];
+    }
+    px += ix - ax; py += iy - ay; pc += icn - ac;
+#pragma unroll
+    for (int k = 0; k < LEVEL_ITEMS; ++k) {
+        const int p = p0 + k;
+        if (p < n) {
+            seq[p] = pc;
+            ps[p] = make_double2(px, py);
+            px += (double)y[k].x; py += (double)y[k].y; pc += c[k];
+            if (p == n - 1) { seq[n] = pc; ps[n] = make_double2(px, py); }
+        }
+    }
+    if (tid == 0) {
+        *ncells = m;
+        if (m > cap_cells) atomicOr(status, TSNE_STATUS_CELL_OVERFLOW);
+    }
+    __syncthreads();
+    LdsKeys lk;
+    lk.lds = keys; lk.lo = 0u;
+    const uint32_t live = min(m, cap_cells);
+    for (uint32_t id = (uint32_t)tid; id < live; id += SMALL_TREE_THREADS) {
+        uint32_t lo = 0, hi = (uint32_t)n;      // the position that opens the cell: seq[lo] <= id < seq[lo + 1]
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (seq[mid] <= id) lo = mid; else hi = mid;
+        }
+        const uint32_t p = lo;
+        const int t = min((int)first_depth[p] + (int)(id - seq[p]), B);
+        uint32_t e, kid_pos[3];
+        bool leaf;
+        const int nk = cell_extent(lk, (uint32_t)n, (uint32_t)n, p, t, B, C, keys[p], &e, &leaf, kid_pos);
+        const double2 s0 = ps[p], s1 = ps[e];
+        const uint32_t cnt = e - p;
+        Cell q;
+        q.c1 = nk > 0 ? seq[kid_pos[0]] : TSNE_NONE;
+        q.c2 = nk > 1 ? seq[kid_pos[1]] : TSNE_NONE;
+        q.c3 = nk > 2 ? seq[kid_pos[2]] : TSNE_NONE;
+        q.cx = (float)((s1.x - s0.x) / (double)cnt);
+        q.cy = (float)((s1.y - s0.y) / (double)cnt);
+        q.cnt = cnt;
+        q.meta = (uint32_t)t | (leaf ? 0x100u : 0u);
+        q.lo = p;
+        cells[id] = q;
+    }
+}
+
+hipError_t small_tree_prepare()
+{
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&small_tree<8>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)small_tree_lds(SMALL_TREE_MAX));
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&small_tree<0>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)small_tree_lds(SMALL_TREE_MAX));
+}
+
 // First position i in [lo, n) with (key[i] >> sh) >= target (n if there is none), found by the
 // whole wave: every round the 64 lanes probe 64 evenly spaced positions of the remaining range,
 // which shrinks 64-fold, so five rounds cover any n.  All lanes must call with the same
@@ -1294,6 +1445,11 @@ hipError_t launch_tree_cells(tsne_ctx *c, hipStream_t s)
     const float2 *Y = c->Yi;
     const int nb = (n + 255) / 256;
     const uint64_t *words = c->words[c->sorted_buf];
+    if (n <= SMALL_TREE_MAX && C <= LEVELS_WINDOW_MAXC) {
+        hipLaunchKernelGGL(C == 8 ? small_tree<8> : small_tree<0>, dim3(1), dim3(SMALL_TREE_THREADS), small_tree_lds(n), s, Y,
+                           words, ks, n, B, C, c->Ys, c->perm, c->cells, (uint32_t)c->cap_cells, c->ncells, c->status);
+        return hipGetLastError();
+    }
     int nl = (n + LEVEL_TILE - 1) / LEVEL_TILE;
     if (C == 8)
         hipLaunchKernelGGL(gather_levels<8>, dim3(nl), dim3(LEVEL_THREADS), 0, s, Y, words, ks, n, B, C, c->Ys, c->perm,

@@ -1,14 +1,28 @@
-"""Sizes at which the launches of an iteration change: the attraction shares the walk's launch and the
-update adds Z up itself (up to 65,536 points).  Against the oracle, and one step against the update rule applied to
-tsne_gradient's forces."""
+"""Sizes at which the launches of an iteration change: one workgroup builds the tree (up to 4096 points), the attraction
+shares the walk's launch and the update adds Z up itself (up to 65,536).  Against the oracle, and one step against the
+update rule applied to tsne_gradient's forces."""
 import numpy as np
 import pytest
 
 import oracle
 from helpers import grid_bits, random_symmetric_csr, rel_l2
 from paper_1807_11824_amd import synth
+from test_gpu_tree import _gpu_tree
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,leaf_cap", [(1023, 8), (1025, 8), (2049, 1), (3073, 16), (4095, 8), (4096, 5), (4096, 17), (4097, 8)])
+def test_tree(n, leaf_cap):
+    Y = synth.clustered_embedding(n, n_clusters=9, seed=n)
+    Y[::7] = Y[0]
+    want = oracle.tree(Y, bits=22, leaf_cap=leaf_cap)
+    got = _gpu_tree(Y, 22, leaf_cap)
+    assert got["m"] == want["m"] and np.array_equal(got["perm"], want["perm"])
+    for key in ("depth", "lo", "hi", "leaf"):
+        assert np.array_equal(got[key][:want["m"]].astype(np.int64), np.asarray(want[key]).astype(np.int64)), key
+    side = float(np.ptp(Y, axis=0).max())
+    assert np.abs(got["com"][:want["m"]] - want["com"]).max() <= 1e-6 * max(2 * side, 1e-30)
 
 
 @pytest.mark.parametrize("n,renumber", [(2, False), (17, True), (4097, True), (65536, False), (65536, True), (65537, True)])
