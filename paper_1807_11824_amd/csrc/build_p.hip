@@ -161,15 +161,31 @@ __global__ __launch_bounds__(256) void split_bf16(const float *__restrict__ X, c
 // The values in half precision, for the first sweep over long rows: row-major, rows padded to a multiple of 64
 // columns, scaled by a power of two (`scale`) that brings the largest magnitude just below 2^15: nothing overflows,
 // and what is too small for a normal half is below 2^-28 of the largest magnitude.
+// Eight columns a thread: two 16-byte loads where rows are whole 16-byte pieces, one 16-byte store.  (rowmap: as in row_norms.)
 __global__ __launch_bounds__(256) void split_high(const float *__restrict__ X, const float *__restrict__ mu, int n, int d,
-                                                  int dph, float scale, uint16_t *__restrict__ Xh)
+                                                  int dph, float scale, const int *__restrict__ rowmap, int nsrc,
+                                                  uint16_t *__restrict__ Xh)
 {
     const size_t e = global_index();
-    if (e >= (size_t)n * dph) return;
-    const size_t row = e / dph;
-    const int k = (int)(e % dph);
-    const _Float16 h = (_Float16)(k < d ? (X[row * d + k] - mu[k]) * scale : 0.f);     // round to nearest even
-    Xh[e] = __builtin_bit_cast(uint16_t, h);
+    const int per = dph / 8;
+    if (e >= (size_t)n * per) return;
+    const size_t row = e / per;
+    const int k = (int)(e % per) * 8;
+    const float *x = X + (rowmap ? (size_t)min(max(rowmap[row], 0), nsrc - 1) : row) * d;
+    float v[8];
+    if (d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0 && k + 8 <= d) {
+        const float4 a = *reinterpret_cast<const float4 *>(x + k), b = *reinterpret_cast<const float4 *>(x + k + 4);
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] -= mu[k + q];
+    } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = k + q < d ? x[k + q] - mu[k + q] : 0.f;
+    }
+    halfx8 h;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) h[q] = (_Float16)(v[q] * scale);       // round to nearest even
+    *reinterpret_cast<halfx8 *>(Xh + row * dph + k) = h;
 }
 
 // max |x - mu| over all values, as the bits of a non-negative float (they order like the values)
@@ -274,6 +290,26 @@ __global__ __launch_bounds__(1024) void half_gap_sample(const float *__restrict_
     if (threadIdx.x == 0 && !(gap > coeff * ((double)norms[i] + (double)norm_max))) atomicAdd(narrow, 1);
 }
 
+// Scaling of the values for half precision, every one of them below xmax: by a power of two so that all are below 2^15.
+// dot_scale undoes it in a product.  A scaled value below 2^-14 may be rounded to a subnormal half or flushed to zero: off
+// by at most delta = 2^-14 / scale per value, the dot product by delta (sum |q_t| + sum |x_t|) + D delta^2, the distance by
+// twice that (e_add); sum |x_t| <= sqrt(D) |x|.
+struct HalfScale {
+    float scale, dot_scale;
+    double e_add;
+};
+inline HalfScale half_scale(float xmax, int d, double norm_max)
+{
+    HalfScale h;
+    int e = 0;
+    (void)frexpf(xmax, &e);                                 // xmax < 2^e
+    h.scale = ldexpf(1.0f, 15 - e);
+    h.dot_scale = ldexpf(1.0f, 2 * (e - 15));
+    const double delta = ldexp(1.0, -14) / (double)h.scale;
+    h.e_add = 2.0 * (delta * 2.0 * sqrt((double)d) * sqrt(norm_max) + (double)d * delta * delta);
+    return h;
+}
+
 // A wave's queue of accepted pairs lives in LDS.
 typedef __attribute__((address_space(3))) uint64_t lds_u64;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
@@ -350,7 +386,7 @@ __device__ __forceinline__ uint64_t dense_pair(float nq, float nj, float dot, bo
 // GATHER: the tiles of an inverted-file search (Eq. (11)) instead of a rectangle of the all-pairs matrix.  The
 // rows are in list order (cellptr[L] .. cellptr[L+1] hold list L); the queries of the pass that probe list L at
 // the current rank are pairq[pairptr[L] .. pairptr[L+1]) (row numbers, any order); a launch takes the rows
-// chunk * DBC .. of every list.  Workgroup t < tptr[nlist] belongs to the list L with tptr[L] <= t < tptr[L+1] and
+// chunk * DBC .. of every list.  With selfmap query q is row selfmap[q] (a second sweep over some of the rows).  Workgroup t < tptr[nlist] belongs to the list L with tptr[L] <= t < tptr[L+1] and
 // is tile (a, b) of its ceil(queries / TQ) x ceil(rows of the chunk / TN) tiles; workgroups past the end leave.
 template <int MB, bool TWO, bool GATHER, bool DENSE = false>
 __global__ __launch_bounds__(256, 2) void knn_tile_mfma(const uint4 *__restrict__ Xs, int dp, int q0, int qend, int j0,
@@ -407,7 +443,7 @@ __global__ __launch_bounds__(256, 2) void knn_tile_mfma(const uint4 *__restrict_
 #pragma unroll
     for (int it = 0; it < 2 * MB; ++it) {
         const int lr = lrow + 32 * it;
-        if (GATHER) arow[it] = lr < nq ? max(pairq[po + lr], 0) : -1;
+        if (GATHER) arow[it] = lr < nq ? (selfmap ? selfmap[max(pairq[po + lr], 0)] : max(pairq[po + lr], 0)) : -1;
         else arow[it] = qa + lr < qend ? qa + lr : -1;
     }
     auto load = [&](int slab) {
@@ -496,7 +532,7 @@ __global__ __launch_bounds__(256, 2) void knn_tile_mfma(const uint4 *__restrict_
     uint32_t *qid = reinterpret_cast<uint32_t *>(qd + TQ);
     for (int t = tid; t < TQ; t += 256) {
         const int q = GATHER ? (t < nq ? max(pairq[po + t], q0) : -1) : (qa + t < qend ? qa + t : -1);
-        const float nrm = q >= 0 ? norms[q] : 0.f;
+        const float nrm = q >= 0 ? norms[GATHER && selfmap ? selfmap[q] : q] : 0.f;
         qn[t] = nrm;
         qd[t] = q >= 0 ? tau[q - q0] - nrm : -INFINITY;     // rows past the end accept nothing
         if (GATHER) qid[t] = (uint32_t)max(q, 0);
@@ -577,23 +613,38 @@ __device__ __forceinline__ int swz(int row) { return ((row >> 1) ^ ((row & 1) <<
 // tile's first slabs are on their way during the tests of this one, the cut-offs are staged once, and since nobody else
 // appends to these rows their fill counts live in LDS, as in knn_tile_resident.  (60,000 x 784: 18.9 -> 14.8 ms for the
 // whole build, 400,000 x 300: 252 -> 194.)
+// GATHER (knn_tile_half_lists, an OWN kernel): the tiles of an inverted-file search, see knn_tile_mfma.  A workgroup takes up to 256 queries that
+// probe one list, and all rows of the chunk of that list; with `dense` set (nobody has a cut-off yet) every pair is kept, at
+// the place of its row in the list.  A list that few queries probe leaves the second half of the query tile empty: the
+// waves that own it multiply nothing, and the others, which share their SIMDs, go twice as fast.
 constexpr int HT = 256;                                 // tile: query rows = database rows
 constexpr int HALF_THREADS = 512;
 constexpr int HALF_BUF = 2 * HT * 128;                  // one buffer: the tile's query rows, then its database rows
 constexpr size_t HALF_TILE_LDS = 2 * (size_t)HALF_BUF;
 constexpr size_t HALF_OWN_LDS = HALF_TILE_LDS + 3 * HT * 4;     // and norms, cut-offs and fill counts of the query tile
+constexpr size_t HALF_GATHER_LDS = HALF_OWN_LDS + HT * 4;       // and its queries
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void glb_void;
 
-template <bool DENSE, bool OWN>
-__global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__restrict__ Xh, int dph, int q0, int qend, int j0,
-                                                                 int jend, const float *__restrict__ norms,
-                                                                 const float *__restrict__ tau, int *__restrict__ cnt,
-                                                                 uint64_t *__restrict__ cand, int cap, int *__restrict__ ccount,
-                                                                 float dot_scale)
+// (No __restrict__ here, the kernels have it: on an inlined function's parameters it makes the compiler wait for the loads
+// in flight before every access to LDS that they do not touch.)
+template <bool DENSE, bool OWN, bool GATHER, bool SELF>
+__device__ __forceinline__ void half_tiles(const uint4 *Xh, int dph, int q0, int qend, int j0, int jend,
+                                           const float *norms, const float *tau,
+                                           int *cnt, uint64_t *cand, int cap,
+                                           int *ccount, float dot_scale, const uint4 *Xb,
+                                           const float *norms_b,
+                                           const int *tptr, int nlist, const int *pairptr,
+                                           const int *pairq, const int *cellptr, int chunk, int dense)
 {
     static_assert(!(DENSE && OWN), "a first launch has no counts");
+    // SELF: the rows are searched among themselves (known to the compiler: with pointers of their own for the database rows
+    // the exact search took 2 % longer)
+    static_assert(SELF || !OWN, "the counts of a row");
+    const uint4 *Xd = SELF ? Xh : Xb;
+    const float *norms_d = SELF ? norms : norms_b;
+    static_assert(OWN || !GATHER, "nobody else appends to a gathered query's buffer");
     if (blockIdx.x == 0 && threadIdx.x == 0) *ccount = 0;   // for the compaction pass that follows
     extern __shared__ __align__(16) unsigned char hsm[];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -603,10 +654,26 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
     // database tiles of one query tile next to each other, so that the 32 workgroups an XCD runs at a time are a few
     // query tiles against all database tiles of the launch and find each other's rows in that cache (taken in plain
     // row-major order, every tile's rows came from memory: 3-4 TB/s of re-reads, which is what bounded the kernel).
+    int po = 0, nq = HT;            // GATHER: first entry of pairq and number of queries of this tile
+    if (GATHER) {
+        const int t = (int)blockIdx.x;
+        if (t >= tptr[nlist]) return;
+        int lo = 0, hi = nlist;     // tptr[lo] <= t < tptr[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (tptr[mid] <= t) lo = mid; else hi = mid;
+        }
+        const int a = t - tptr[lo], nql = pairptr[lo + 1] - pairptr[lo];
+        j0 = min(cellptr[lo] + chunk * DBC, cellptr[lo + 1]);
+        jend = min(cellptr[lo + 1], j0 + DBC);
+        po = pairptr[lo] + a * HT;
+        nq = min(HT, nql - a * HT);
+        if (nq <= 0 || jend <= j0) return;      // (no such tile is counted)
+    }
     const int nqt = (qend - q0 + HT - 1) / HT, njt = (jend - j0 + HT - 1) / HT, per = (nqt + 7) / 8;
     const int xcd = (int)(blockIdx.x & 7u), local = (int)(blockIdx.x >> 3);
     // (OWN: workgroup = query tile)
-    const int qt = OWN ? (int)blockIdx.x : xcd * per + local / njt, jt = OWN ? 0 : local % njt;
+    const int qt = GATHER ? 0 : OWN ? (int)blockIdx.x : xcd * per + local / njt, jt = OWN ? 0 : local % njt;
     if (qt >= nqt || (!OWN && local / njt >= per)) return;     // (the grid is 8 per njt workgroups; the same for all lanes)
     const int qa = q0 + qt * HT;
     int ja = j0 + jt * HT;
@@ -628,8 +695,8 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int lr = 32 * w + 8 * it + (lane >> 3), c = (lane & 7) ^ swz(lr);
-        ga[it] = Xh + (size_t)min(qa + lr, qend - 1) * row16 + c;
-        gb[it] = Xh + (size_t)min(ja + lr, jend - 1) * row16 + c;
+        ga[it] = Xh + (size_t)(GATHER ? max(pairq[po + min(lr, nq - 1)], 0) : min(qa + lr, qend - 1)) * row16 + c;
+        gb[it] = Xd + (size_t)min(ja + lr, jend - 1) * row16 + c;
     }
     // the slab that is loaded next: number lslab of the tile of database rows at lja
     int lslab = 0, lja = ja;
@@ -641,7 +708,7 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
                 const int lr = 32 * w + 8 * it + (lane >> 3), c = (lane & 7) ^ swz(lr);
-                gb[it] = Xh + (size_t)min(lja + lr, jend - 1) * row16 + c;
+                gb[it] = Xd + (size_t)min(lja + lr, jend - 1) * row16 + c;
             }
         }
     };
@@ -678,14 +745,17 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
     }                                                                                      \
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     float *own_n = reinterpret_cast<float *>(hsm + HALF_TILE_LDS), *own_d = own_n + HT;
-    int *own_c = reinterpret_cast<int *>(own_d + HT);
+    int *own_c = reinterpret_cast<int *>(own_d + HT), *own_q = own_c + HT;
+    const bool idle = GATHER && wm * 128 >= nq;
     if (OWN) {
         for (int t = tid; t < HT; t += HALF_THREADS) {
-            const int q = qa + t;
-            const float nq = q < qend ? norms[q] : 0.f;
-            own_n[t] = nq;
-            own_d[t] = q < qend ? tau[q - q0] - nq : -INFINITY;     // rows past the end accept nothing
-            own_c[t] = q < qend ? cnt[q - q0] : 0;
+            const bool in = GATHER ? t < nq : qa + t < qend;
+            const int q = !in ? -1 : GATHER ? max(pairq[po + t], q0) : qa + t;
+            const float nrm = in ? norms[q] : 0.f;
+            own_n[t] = nrm;
+            own_d[t] = in ? tau[q - q0] - nrm : -INFINITY;     // rows past the end accept nothing
+            own_c[t] = in ? cnt[q - q0] : 0;
+            if (GATHER) own_q[t] = in ? q - q0 : 0;
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
@@ -698,7 +768,7 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
     asm volatile("s_waitcnt vmcnt(8)" ::: "memory");     // (the first slab; all of them if there is only one)
     if (total == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    HALF_FRAGS(0, 0, 0)
+    if (!idle) HALF_FRAGS(0, 0, 0)
     int slab = 0;
     float njn[2] = {0.f, 0.f};
     for (int flat = 0; flat < total; ++flat) {
@@ -707,21 +777,23 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 const int j = ja + wn * 64 + b * 32 + r32;
-                njn[b] = norms[min(j, jend - 1)];
+                njn[b] = norms_d[min(j, jend - 1)];
             }
         }
-        HALF_FRAGS(cur, 1, 1)
-        HALF_PRODUCTS(0)
-        HALF_INTERLEAVE()
-        __builtin_amdgcn_sched_barrier(0);
-        HALF_FRAGS(cur, 2, 0)
-        HALF_PRODUCTS(1)
-        HALF_INTERLEAVE()
-        __builtin_amdgcn_sched_barrier(0);
-        HALF_FRAGS(cur, 3, 1)
-        HALF_PRODUCTS(0)
-        HALF_INTERLEAVE()
-        __builtin_amdgcn_sched_barrier(0);
+        if (!idle) {
+            HALF_FRAGS(cur, 1, 1)
+            HALF_PRODUCTS(0)
+            HALF_INTERLEAVE()
+            __builtin_amdgcn_sched_barrier(0);
+            HALF_FRAGS(cur, 2, 0)
+            HALF_PRODUCTS(1)
+            HALF_INTERLEAVE()
+            __builtin_amdgcn_sched_barrier(0);
+            HALF_FRAGS(cur, 3, 1)
+            HALF_PRODUCTS(0)
+            HALF_INTERLEAVE()
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // this wave's part of the next slab has arrived (OWN: so have the norms, which the compiler has to see)
         if (OWN) __builtin_amdgcn_s_waitcnt(0x0F70);
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -732,16 +804,40 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
             load_next();
         }
         // (past the last slab these fragments are read from a buffer nobody fills any more, and never used)
-        HALF_FRAGS(oth, 0, 0)
-        HALF_PRODUCTS(1)
-        HALF_INTERLEAVE()
-        __builtin_amdgcn_sched_barrier(0);
+        if (!idle) {
+            HALF_FRAGS(oth, 0, 0)
+            HALF_PRODUCTS(1)
+            HALF_INTERLEAVE()
+            __builtin_amdgcn_sched_barrier(0);
+        }
         if (!OWN || ++slab < nslab) continue;
+        if (idle) { slab = 0; ja += HT; continue; }
         // (one base per lane, the rest compile-time offsets)
         int lbase = wm * 128 + 4 * h;
         asm volatile("" : "+v"(lbase));
         const float *qd_l = own_d + lbase, *qn_l = own_n + lbase;
         int *qc_l = own_c + lbase;
+        const int *qq_l = own_q + lbase;
+        if (GATHER && dense) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int j = ja + wn * 64 + b * 32 + r32;
+                const float nj = j < jend ? njn[b] : INFINITY;
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int off = a * 32 + 8 * (i / 4) + i % 4, q = qq_l[off];
+                        if (lbase + off < nq && j < jend)
+                            cand[(size_t)q * cap + (j - j0)] = dense_pair(qn_l[off], nj, acc[a][b][i] * dot_scale, j == q0 + q, j);
+                        acc[a][b][i] = 0.f;
+                        if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);      // (four addresses at a time: there are no registers for 64)
+                    }
+            }
+            slab = 0;
+            ja += HT;
+            continue;
+        }
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             const int j = ja + wn * 64 + b * 32 + r32;
@@ -758,8 +854,8 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
                     if (__builtin_expect(__ballot(near[0] || near[1] || near[2] || near[3]) != 0, 0)) {
 #pragma unroll
                         for (int ii = 0; ii < 4; ++ii) {
-                            const int off = a * 32 + 8 * i4 + ii, q = qa + lbase + off;
-                            if (near[ii] && j != q) {
+                            const int off = a * 32 + 8 * i4 + ii, q = GATHER ? q0 + qq_l[off] : qa + lbase + off;
+                            if (near[ii] && (j != q)) {
                                 const float dist = (qn_l[off] + nj) - 2.0f * (acc[a][b][4 * i4 + ii] * dot_scale);
                                 const int pos = atomicAdd(qc_l + off, 1);
                                 if (pos < cap)
@@ -776,8 +872,10 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
     }
     __syncthreads();            // (the epilogue reuses the buffers)
     if (OWN) {
-        for (int t = tid; t < HT; t += HALF_THREADS)
-            if (qa + t < qend) cnt[qa + t - q0] = own_c[t];
+        for (int t = tid; t < HT; t += HALF_THREADS) {
+            if (!GATHER && qa + t < qend) cnt[qa + t - q0] = own_c[t];
+            if (GATHER && t < nq) cnt[own_q[t]] = dense ? jend - j0 : own_c[t];
+        }
         return;
     }
 #undef HALF_LOAD
@@ -798,14 +896,14 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             const int j = ja + wn * 64 + b * 32 + r32;
-            const float nj = j < jend ? norms[j] : INFINITY;
+            const float nj = j < jend ? norms_d[j] : INFINITY;
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int ql = wm * 128 + a * 32 + 8 * (i / 4) + 4 * h + i % 4, q = qa + ql;
                     if (q < qend && j < jend)
-                        cand[(size_t)(q - q0) * cap + (j - j0)] = dense_pair(qn[ql], nj, acc[a][b][i] * dot_scale, j == q, j);
+                        cand[(size_t)(q - q0) * cap + (j - j0)] = dense_pair(qn[ql], nj, acc[a][b][i] * dot_scale, SELF && j == q, j);
                 }
         }
         if (jt == 0)
@@ -821,7 +919,7 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         const int j = ja + wn * 64 + b * 32 + r32;
-        const float nj = j < jend ? norms[j] : INFINITY;    // rows past the end are never closer than any cut-off
+        const float nj = j < jend ? norms_d[j] : INFINITY;    // rows past the end are never closer than any cut-off
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
 #pragma unroll
@@ -835,13 +933,51 @@ __global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__
                     const bool near = fmaf(-2.0f, dot, nj) < dq[ii];
                     if (__ballot(near) != 0)
                         fill = __builtin_amdgcn_readfirstlane(queue_pairs(near, j, ql0 + ii, qa, q0, (const lds_f32 *)qn, nj, dot, fill, QCAP,
-                                                                          qkey, qrow, cnt, cand, cap, (const lds_u32 *)nullptr, 1,
+                                                                          qkey, qrow, cnt, cand, cap, (const lds_u32 *)nullptr, SELF ? 1 : 0,
                                                                           (const int *)nullptr));
                 }
             }
         }
     }
     append_queue(qrow, qkey, fill, cnt, cand, cap);
+}
+
+template <bool DENSE, bool OWN>
+__global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half(const uint4 *__restrict__ Xh, int dph, int q0, int qend, int j0,
+                                                                 int jend, const float *__restrict__ norms,
+                                                                 const float *__restrict__ tau, int *__restrict__ cnt,
+                                                                 uint64_t *__restrict__ cand, int cap, int *__restrict__ ccount,
+                                                                 float dot_scale)
+{
+    half_tiles<DENSE, OWN, false, true>(Xh, dph, q0, qend, j0, jend, norms, tau, cnt, cand, cap, ccount, dot_scale, nullptr, nullptr,
+                                        nullptr, 0, nullptr, nullptr, nullptr, 0, 0);
+}
+
+// Against other rows (centroids, pivots): Xb, norms_b.
+template <bool DENSE>
+__global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half_other(const uint4 *__restrict__ Xh, int dph, int q0, int qend, int j0,
+                                                                       int jend, const float *__restrict__ norms,
+                                                                       const float *__restrict__ tau, int *__restrict__ cnt,
+                                                                       uint64_t *__restrict__ cand, int cap,
+                                                                       int *__restrict__ ccount, float dot_scale,
+                                                                       const uint4 *__restrict__ Xb, const float *__restrict__ norms_b)
+{
+    half_tiles<DENSE, false, false, false>(Xh, dph, q0, qend, j0, jend, norms, tau, cnt, cand, cap, ccount, dot_scale, Xb, norms_b,
+                                           nullptr, 0, nullptr, nullptr, nullptr, 0, 0);
+}
+
+__global__ __launch_bounds__(HALF_THREADS, 1) void knn_tile_half_lists(const uint4 *__restrict__ Xh, int dph, int q0, int qend,
+                                                                       const float *__restrict__ norms,
+                                                                       const float *__restrict__ tau, int *__restrict__ cnt,
+                                                                       uint64_t *__restrict__ cand, int cap,
+                                                                       int *__restrict__ ccount, float dot_scale,
+                                                                       const int *__restrict__ tptr, int nlist,
+                                                                       const int *__restrict__ pairptr,
+                                                                       const int *__restrict__ pairq,
+                                                                       const int *__restrict__ cellptr, int chunk, int dense)
+{
+    half_tiles<false, true, true, true>(Xh, dph, q0, qend, 0, 0, norms, tau, cnt, cand, cap, ccount, dot_scale, nullptr, nullptr, tptr, nlist,
+                                  pairptr, pairq, cellptr, chunk, dense);
 }
 
 // ---- d <= 64: the query tile stays in LDS
@@ -1267,7 +1403,8 @@ __global__ __launch_bounds__(256) void knn_rerank(const float *__restrict__ X, i
     if (shared[1] >= 0) limit = (double)unorderable((uint32_t)(key[shared[1]] >> 32)) + 2.0 * E;
     for (int a = threadIdx.x; a < c_all; a += blockDim.x) {
         // (not "beyond": a distance that is no number stays)
-        if ((double)unorderable((uint32_t)(key[a] >> 32)) > limit) continue;
+        // (NO_PAIR: from a first launch over fewer rows than k', which nothing compacts)
+        if (key[a] == NO_PAIR || (double)unorderable((uint32_t)(key[a] >> 32)) > limit) continue;
         const int j = (int)(uint32_t)key[a];
         cid[atomicAdd(&shared[0], 1)] = min(max(cmap ? cmap[min(j, ny - 1)] : j, 0), ny - 1);
     }
@@ -1750,6 +1887,7 @@ __global__ void max_norm_k(const float *__restrict__ norms, int n, float *__rest
 {
     __shared__ float ws[16];
     float m = 0.f;
+#pragma unroll 8
     for (int i = threadIdx.x; i < n; i += blockDim.x) m = fmaxf(m, norms[i]);
     m = wave_max(m);
     if (lane_id() == 0) ws[threadIdx.x >> 6] = m;
@@ -1803,32 +1941,35 @@ __device__ __forceinline__ int wave_add(int *__restrict__ counters, int c, bool 
     return mine;
 }
 
-__global__ void rank_hist(const int32_t *__restrict__ probe_l, int q0, int rows, int tau, int r, int *__restrict__ bcnt)
+// (qmap: query q is row qmap[q] of the list order; null: row q)
+__global__ void rank_hist(const int32_t *__restrict__ probe_l, const int *__restrict__ qmap, int q0, int rows, int tau, int r,
+                          int *__restrict__ bcnt)
 {
     const size_t i = global_index();
     const bool live = i < (size_t)rows;
-    wave_add(bcnt, live ? probe_l[((size_t)q0 + i) * tau + r] : 0, live);
+    wave_add(bcnt, live ? probe_l[(qmap ? (size_t)qmap[q0 + i] : (size_t)q0 + i) * tau + r] : 0, live);
 }
 
-__global__ void rank_scatter(const int32_t *__restrict__ probe_l, int q0, int rows, int tau, int r,
+__global__ void rank_scatter(const int32_t *__restrict__ probe_l, const int *__restrict__ qmap, int q0, int rows, int tau, int r,
                              const int *__restrict__ pairptr, int *__restrict__ bcur, int *__restrict__ pairq)
 {
     const size_t i = global_index();
     const bool live = i < (size_t)rows;
-    const int L = live ? probe_l[((size_t)q0 + i) * tau + r] : 0;
+    const int L = live ? probe_l[(qmap ? (size_t)qmap[q0 + i] : (size_t)q0 + i) * tau + r] : 0;
     const int at = wave_add(bcur, L, live);
     if (live) pairq[pairptr[L] + at] = q0 + (int)i;     // any order inside a list
 }
 
 // tiles of list L in the launch that takes rows chunk * DBC .. of every list
-__global__ void tile_count(const int *__restrict__ pairptr, const int *__restrict__ cellptr, int nlist, int chunk, int tq,
+// (tr database rows a tile)
+__global__ void tile_count(const int *__restrict__ pairptr, const int *__restrict__ cellptr, int nlist, int chunk, int tq, int tr,
                            int *__restrict__ tcnt)
 {
     const int L = blockIdx.x * blockDim.x + threadIdx.x;
     if (L >= nlist) return;
     const int nq = pairptr[L + 1] - pairptr[L];
     const int rs = min(cellptr[L] + chunk * DBC, cellptr[L + 1]), re = min(cellptr[L + 1], rs + DBC);
-    tcnt[L] = ((nq + tq - 1) / tq) * ((re - rs + TN - 1) / TN);
+    tcnt[L] = ((nq + tq - 1) / tq) * ((re - rs + tr - 1) / tr);
 }
 
 // out[i] = in[0] + .. + in[i-1], i = 0 .. m (one workgroup; the sums stay below 2^31 as the callers size things)
@@ -1852,6 +1993,17 @@ __global__ __launch_bounds__(1024) void excl_scan_k(const int *__restrict__ in, 
     int pre = base + inc - a;
     for (int i = b; i < e; ++i) { const int v = in[i]; out[i] = pre; pre += v; }
     if (threadIdx.x == 1023) out[m] = pre;
+}
+
+// rows list[0 .. m) of a numbering that maps to X by map (null: itself): their rows in X, and their norms
+__global__ void pick_rows_k(const int *__restrict__ list, int m, int n, const int *__restrict__ map,
+                            const float *__restrict__ norms, int *__restrict__ xrow, float *__restrict__ norms_out)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= m) return;
+    const int p = min(max(list[i], 0), n - 1);
+    xrow[i] = map ? map[p] : p;
+    norms_out[i] = norms[p];
 }
 
 // the evenly spaced sample of m of n rows: floor(i n / m)
@@ -2011,25 +2163,27 @@ int check_args(int32_t n, int32_t d, int32_t k)
 // (distance in double, row number).  probe: n x tau list numbers (Eq. (10)), lorder: the rows in list order,
 // cellptr: where each list starts in it; max_list and max_cand (longest list, most rows in one query's lists) from the caller.
 namespace {
-// (the k-th and the (k + 16)-th neighbour of a point are much farther apart than the error of a tile distance)
-int search_kp(int n, int k) { return k + 16 < n - 1 ? k + 16 : n - 1; }
-
 struct TileSearchLayout {
     float *norms, *norm_max, *tau, *mu;
     double *mu_part;
     int *cnt, *clist, *ccount, *fail_count, *fail_rows, *bcnt, *bcur, *pairptr, *tcnt, *tptr, *pairq, *fcnt;
+    int *fail2_count, *fail2_rows, *xrow;      // a second sweep: rows it fails, and its queries' rows in X and norms
+    float *norms_f;
     int32_t *probe_l;
     uint64_t *cand;
     uint16_t *xs;
     size_t cand_bytes;
 };
 constexpr int TS_ROWS = 1 << 17;     // queries per pass
+// queries without a certificate from which on a second sweep is quicker than exact distances: those read all rows of a
+// query's lists for it alone, or compare it with every centroid (4096 queries a launch of some 0.8 ms)
+constexpr int SECOND_SWEEP_MIN = 1024, PROBE_SWEEP_MIN = 8192;
 
 size_t ts_carve(TileSearchLayout *L, int n, int d, int k, int nlist, int tau, char *base)
 {
     size_t off = 0;
     auto take = [&](size_t bytes) { char *p = base ? base + off : nullptr; off += up(bytes); return (void *)p; };
-    const int kp = search_kp(n, k);
+    const int kp = margin_kp(n, k);
     const size_t cap = (size_t)kp + COMPACT_SLACK + COMPACT_EVERY * DBC;
     const size_t qb = (size_t)(n < TS_ROWS ? n : TS_ROWS);
     const size_t dp = ((size_t)d + SLAB - 1) / SLAB * SLAB;
@@ -2044,6 +2198,10 @@ size_t ts_carve(TileSearchLayout *L, int n, int d, int k, int nlist, int tau, ch
     q = take(8); if (L) L->ccount = (int *)q;
     q = take(4); if (L) L->fail_count = (int *)q;
     q = take(4 * (size_t)n); if (L) L->fail_rows = (int *)q;
+    q = take(4); if (L) L->fail2_count = (int *)q;
+    q = take(4 * (size_t)n); if (L) L->fail2_rows = (int *)q;
+    q = take(4 * (size_t)n); if (L) L->xrow = (int *)q;
+    q = take(4 * (size_t)n); if (L) L->norms_f = (float *)q;
     q = take(4 * ((size_t)nlist + 1)); if (L) L->bcnt = (int *)q;
     q = take(4 * ((size_t)nlist + 1)); if (L) L->bcur = (int *)q;
     q = take(4 * ((size_t)nlist + 1)); if (L) L->pairptr = (int *)q;
@@ -2069,54 +2227,105 @@ int ivf_search_tiles(const float *X, int n, int d, int k, int nlist, int tau, co
     if (ws_bytes < ts_carve(nullptr, n, d, k, nlist, tau, nullptr)) return TSNE_ENOSPC;
     TileSearchLayout L;
     ts_carve(&L, n, d, k, nlist, tau, (char *)ws);
-    const int kp = search_kp(n, k), cap = kp + COMPACT_SLACK + COMPACT_EVERY * DBC;
+    const int kp = margin_kp(n, k), cap = kp + COMPACT_SLACK + COMPACT_EVERY * DBC;
     const int dp = (d + SLAB - 1) / SLAB * SLAB;
     const int rows_per_chunk = (n + MEAN_CHUNKS - 1) / MEAN_CHUNKS, nchunks_mu = (n + rows_per_chunk - 1) / rows_per_chunk;
     hipLaunchKernelGGL(col_mean_part, dim3((d + 63) / 64, nchunks_mu), dim3(256), 0, s, X, n, d, rows_per_chunk, L.mu_part);
     hipLaunchKernelGGL(col_mean_final, dim3((dp + 255) / 256), dim3(256), 0, s, L.mu_part, nchunks_mu, n, d, dp, L.mu);
     hipLaunchKernelGGL(row_norms, wide_grid((size_t)n * WAVE), dim3(256), 0, s, X, L.mu, n, d, lorder, n, L.norms);
-    hipLaunchKernelGGL(split_bf16, wide_grid((size_t)n * dp), dim3(256), 0, s, X, L.mu, n, d, dp, lorder, n, L.xs);
     hipLaunchKernelGGL(max_norm_k, dim3(1), dim3(1024), 0, s, L.norms, n, L.norm_max);
     hipLaunchKernelGGL(probe_gather, wide_grid((size_t)n * tau), dim3(256), 0, s, probe, lorder, n, tau, nlist, L.probe_l);
     HIPCHK(hipMemsetAsync(L.fail_count, 0, 4, s));
+    HIPCHK(hipMemsetAsync(L.fail2_count, 0, 4, s));
     float norm_max = 0.f;
     HIPCHK(hipMemcpyAsync(&norm_max, L.norm_max, 4, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     const size_t rerank_smem = rerank_lds_bytes(d, kp);
     const int nchunks = (max_list + DBC - 1) / DBC;
     const unsigned lb = (unsigned)((nlist + 1 + 255) / 256);
-    for (int q0 = 0; q0 < n; q0 += TS_ROWS) {
-        const int rows = n - q0 < TS_ROWS ? n - q0 : TS_ROWS;
+    // As in tsne_build_P: a first sweep with the values in half precision, whose certificate holds for nearly every query
+    // of ordinary data, the three-product tiles for the queries it fails (or for everybody, if it fails half of the first
+    // pass), exact distances for a few.  The copies take turns in L.xs (2 n dph <= 4 n dp bytes from 33 columns on).
+    // (1,281,167 x 2048, four lists a query: tiles of a pass 8.35 -> 1.6 ms, quantizer and lists together 688 -> 360 ms.)
+    const int dph = (d + 2 * SLAB - 1) / (2 * SLAB) * (2 * SLAB);
+    const bool half_first = d > KFLUSH && norm_max > 1e-30f && norm_max < 1e30f;      // (dot_scale has to be a normal float)
+    HalfScale hs = {};
+    if (half_first) {
+        // (no value is larger than its row's norm, whose square is a rounded sum)
+        hs = half_scale(sqrtf(norm_max) * 1.0001f, d, norm_max);
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&knn_tile_half_lists),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)HALF_GATHER_LDS));
+        hipLaunchKernelGGL(split_high, wide_grid((size_t)n * (dph / 8)), dim3(256), 0, s, X, L.mu, n, d, dph, hs.scale, lorder, n, L.xs);
+    }
+    auto split = [&]() {
+        hipLaunchKernelGGL(split_bf16, wide_grid((size_t)n * dp), dim3(256), 0, s, X, L.mu, n, d, dp, lorder, n, L.xs);
+    };
+    // queries q0 .. q0 + rows (of qmap, or of the list order) against their lists
+    auto pass = [&](bool half, const int *qmap, int q0, int rows, int *fail_count, int *fail_rows) {
         hipLaunchKernelGGL(knn_reset, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, rows, L.ccount);
         // an upper bound of the tiles of one launch: sum over the lists of ceil(queries / 128) x (DBC / TN)
-        const unsigned bound = (unsigned)(((size_t)rows / 128 + (size_t)nlist + 1) * (DBC / TN));
+        const int tq = half ? HT : 128, tr = half ? DBC : TN;
+        const unsigned bound = (unsigned)(((size_t)rows / tq + (size_t)nlist + 1) * (DBC / tr));
         for (int r = 0; r < tau; ++r) {
             hipLaunchKernelGGL(fill_int_k, dim3(lb), dim3(256), 0, s, L.bcnt, 0, nlist + 1);
             hipLaunchKernelGGL(fill_int_k, dim3(lb), dim3(256), 0, s, L.bcur, 0, nlist + 1);
-            hipLaunchKernelGGL(rank_hist, wide_grid((size_t)rows), dim3(256), 0, s, L.probe_l, q0, rows, tau, r, L.bcnt);
+            hipLaunchKernelGGL(rank_hist, wide_grid((size_t)rows), dim3(256), 0, s, L.probe_l, qmap, q0, rows, tau, r, L.bcnt);
             hipLaunchKernelGGL(excl_scan_k, dim3(1), dim3(1024), 0, s, L.bcnt, nlist, L.pairptr);
-            hipLaunchKernelGGL(rank_scatter, wide_grid((size_t)rows), dim3(256), 0, s, L.probe_l, q0, rows, tau, r, L.pairptr,
+            hipLaunchKernelGGL(rank_scatter, wide_grid((size_t)rows), dim3(256), 0, s, L.probe_l, qmap, q0, rows, tau, r, L.pairptr,
                                L.bcur, L.pairq);
             for (int c = 0; c < nchunks; ++c) {
-                hipLaunchKernelGGL(tile_count, dim3(lb), dim3(256), 0, s, L.pairptr, cellptr, nlist, c, 128, L.tcnt);
+                const bool dense = half && r == 0 && c == 0;
+                hipLaunchKernelGGL(tile_count, dim3(lb), dim3(256), 0, s, L.pairptr, cellptr, nlist, c, tq, tr, L.tcnt);
                 hipLaunchKernelGGL(excl_scan_k, dim3(1), dim3(1024), 0, s, L.tcnt, nlist, L.tptr);
-                hipLaunchKernelGGL((knn_tile_mfma<2, true, true>), dim3(bound), dim3(256), 0, s, (const uint4 *)L.xs, dp, q0,
-                                   q0 + rows, 0, 0, L.norms, L.tau, L.cnt, L.cand, cap, L.ccount, (const uint4 *)L.xs, L.norms, 1,
-                                   (const int *)nullptr, L.tptr, nlist, L.pairptr, L.pairq, cellptr, c);
+                if (half)
+                    hipLaunchKernelGGL(knn_tile_half_lists, dim3(bound), dim3(HALF_THREADS), HALF_GATHER_LDS, s,
+                                       (const uint4 *)L.xs, dph, q0, q0 + rows, L.norms, L.tau, L.cnt, L.cand, cap, L.ccount,
+                                       hs.dot_scale, L.tptr, nlist, L.pairptr, L.pairq, cellptr, c, dense ? 1 : 0);
+                else
+                    hipLaunchKernelGGL((knn_tile_mfma<2, true, true>), dim3(bound), dim3(256), 0, s, (const uint4 *)L.xs, dp, q0,
+                                       q0 + rows, 0, 0, L.norms, L.tau, L.cnt, L.cand, cap, L.ccount, (const uint4 *)L.xs, L.norms, 1,
+                                       qmap, L.tptr, nlist, L.pairptr, L.pairq, cellptr, c);
                 const int force = r == tau - 1 && c == nchunks - 1 ? 1 : 0;
                 hipLaunchKernelGGL(knn_compact_list, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, cap, kp, rows, force,
                                    L.clist, L.ccount);
-                launch_compact(L.tau, L.cnt, L.cand, cap, kp, rows, L.clist, L.ccount, false, s);
+                launch_compact(L.tau, L.cnt, L.cand, cap, kp, rows, L.clist, L.ccount, dense, s);
             }
         }
-        hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, X, n, d, lorder, X, n, lorder, lorder, (const int *)nullptr, q0,
-                           rows, k, kp, 0x7FFFFFFF, tile_error_coeff(d, true), 0.0, L.norms, norm_max, L.tau, L.cnt, L.cand, cap, knn_idx, knn_d2, L.fail_count,
-                           L.fail_rows);
-        HIPCHK(hipGetLastError());
-    }
+        hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, X, n, d,
+                           qmap ? (const int *)L.xrow : lorder, X, n, lorder, qmap ? (const int *)L.xrow : lorder, qmap, q0, rows, k, kp,
+                           0x7FFFFFFF, half ? tile_error_coeff(d, false, true) : tile_error_coeff(d, true), half ? hs.e_add : 0.0,
+                           qmap ? (const float *)L.norms_f : L.norms, norm_max, L.tau, L.cnt, L.cand, cap, knn_idx, knn_d2, fail_count,
+                           fail_rows);
+    };
+    bool half = half_first;
+    if (!half) split();
     int nfail = 0;
+    for (int q0 = 0; q0 < n; q0 += TS_ROWS) {
+        const int rows = n - q0 < TS_ROWS ? n - q0 : TS_ROWS;
+        // (three products after all: what those cannot certify goes to the exact pass)
+        pass(half, nullptr, q0, rows, half == half_first ? L.fail_count : L.fail2_count, half == half_first ? L.fail_rows : L.fail2_rows);
+        HIPCHK(hipGetLastError());
+        if (half && q0 == 0 && rows < n) {
+            HIPCHK(hipMemcpyAsync(&nfail, L.fail_count, 4, hipMemcpyDeviceToHost, s));
+            HIPCHK(hipStreamSynchronize(s));
+            if (nfail > rows / 2) { half = false; split(); }
+        }
+    }
     HIPCHK(hipMemcpyAsync(&nfail, L.fail_count, 4, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    const int *exact_rows = L.fail_rows;
+    // A second sweep pays from some hundreds of queries on: an exact one reads all rows of its lists by itself.
+    if (half != half_first || (half_first && nfail > SECOND_SWEEP_MIN)) {
+        if (half) split();
+        hipLaunchKernelGGL(pick_rows_k, dim3((nfail + 255) / 256 + 1), dim3(256), 0, s, L.fail_rows, nfail, n, lorder, L.norms, L.xrow,
+                           L.norms_f);
+        for (int f0 = 0; f0 < nfail; f0 += TS_ROWS)
+            pass(false, L.fail_rows, f0, nfail - f0 < TS_ROWS ? nfail - f0 : TS_ROWS, L.fail2_count, L.fail2_rows);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(&nfail, L.fail2_count, 4, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        exact_rows = L.fail2_rows;
+    }
     if (nfail > 0) {
         const size_t stride = (size_t)max_cand;
         size_t nb_max = L.cand_bytes / (12 * stride);
@@ -2126,9 +2335,9 @@ int ivf_search_tiles(const float *X, int n, int d, int k, int nlist, int tau, co
         int *ids = reinterpret_cast<int *>(okey + nb_max * stride);
         for (int f0 = 0; f0 < nfail; f0 += (int)nb_max) {
             const int nb = nfail - f0 < (int)nb_max ? nfail - f0 : (int)nb_max;
-            hipLaunchKernelGGL(ivf_exact_keys, dim3(nb), dim3(256), up((size_t)d * 4), s, X, n, d, L.fail_rows + f0, L.probe_l, tau,
+            hipLaunchKernelGGL(ivf_exact_keys, dim3(nb), dim3(256), up((size_t)d * 4), s, X, n, d, exact_rows + f0, L.probe_l, tau,
                                cellptr, lorder, stride, okey, ids, L.fcnt);
-            hipLaunchKernelGGL(knn_exact_select, dim3(nb), dim3(1024), 0, s, okey, stride, 0, L.fcnt, ids, k, L.fail_rows + f0,
+            hipLaunchKernelGGL(knn_exact_select, dim3(nb), dim3(1024), 0, s, okey, stride, 0, L.fcnt, ids, k, exact_rows + f0,
                                lorder, n, knn_idx, knn_d2);
             HIPCHK(hipGetLastError());
         }
@@ -2142,9 +2351,9 @@ int ivf_search_tiles(const float *X, int n, int d, int k, int nlist, int tau, co
 // re-ranked in double, a certificate, and all centroids in double for a query without one.
 namespace {
 struct TileProbeLayout {
-    float *norms_q, *norms_c, *norm_max, *tau, *mu;
+    float *norms_q, *norms_c, *norm_max, *norms_f, *tau, *mu;      // norm_max: of the centroids, then of the queries
     double *mu_part;
-    int *cnt, *clist, *ccount, *fail_count, *fail_rows, *qrows;
+    int *cnt, *clist, *ccount, *fail_count, *fail_rows, *fail2_count, *fail2_rows, *xrow, *qrows;
     uint64_t *cand;
     uint16_t *xs, *cs;
     size_t cand_bytes;
@@ -2163,7 +2372,8 @@ size_t tp_carve(TileProbeLayout *L, int n, int d, int nlist, int tau, char *base
     void *q;
     q = take(4 * (size_t)n); if (L) L->norms_q = (float *)q;
     q = take(4 * (size_t)nlist); if (L) L->norms_c = (float *)q;
-    q = take(4); if (L) L->norm_max = (float *)q;
+    q = take(8); if (L) L->norm_max = (float *)q;
+    q = take(4 * (size_t)n); if (L) L->norms_f = (float *)q;
     q = take(4 * qb); if (L) L->tau = (float *)q;
     q = take(4 * dp); if (L) L->mu = (float *)q;
     q = take(8 * (size_t)MEAN_CHUNKS * d); if (L) L->mu_part = (double *)q;
@@ -2172,6 +2382,9 @@ size_t tp_carve(TileProbeLayout *L, int n, int d, int nlist, int tau, char *base
     q = take(8); if (L) L->ccount = (int *)q;
     q = take(4); if (L) L->fail_count = (int *)q;
     q = take(4 * (size_t)n); if (L) L->fail_rows = (int *)q;
+    q = take(4); if (L) L->fail2_count = (int *)q;
+    q = take(4 * (size_t)n); if (L) L->fail2_rows = (int *)q;
+    q = take(4 * (size_t)n); if (L) L->xrow = (int *)q;
     q = take(4 * (size_t)n); if (L) L->qrows = (int *)q;
     q = take(4 * (size_t)n * dp); if (L) L->xs = (uint16_t *)q;
     q = take(4 * (size_t)nlist * dp); if (L) L->cs = (uint16_t *)q;
@@ -2194,50 +2407,89 @@ size_t ivf_tiles_workspace(int n, int d, int k, int nlist, int tau)
     return a > b ? a : b;
 }
 
-// reuse_queries: the workspace still holds the query side (column means, sample rows, norms and split copy) of the
-// previous call, which had the same X, n, d and m (the rounds of k-means: only the centroids change).
+// queries: what the workspace holds of the query side (column means, sample rows, norms, copy) from a previous call with
+// the same X, n, d and m (the rounds of k-means: only the centroids change); left as what it holds now.
+// As in tsne_build_P: the values in half precision first, three products for the queries that leaves without a certificate.
+// (131,072 x 1132 x 2048 products: 2.10 -> 0.80 ms.)
 int ivf_probe_tiles(const float *X, int n, int d, const float *C, int nlist, int tau, int m, int32_t *probe, void *ws,
-                    size_t ws_bytes, hipStream_t s, int reuse_queries)
+                    size_t ws_bytes, hipStream_t s, ProbeQueries *queries)
 {
     if (n < 2 || d < 1 || d > 4096 || nlist < 1 || tau < 1 || tau > nlist || m < 1 || m > n) return TSNE_EINVAL;
     if (ws_bytes < tp_carve(nullptr, n, d, nlist, tau, nullptr)) return TSNE_ENOSPC;
     TileProbeLayout L;
     tp_carve(&L, n, d, nlist, tau, (char *)ws);
     const int kp = probe_kp(nlist, tau), cap = kp + COMPACT_SLACK + COMPACT_EVERY * DBC;
-    const int dp = (d + SLAB - 1) / SLAB * SLAB;
+    const int dp = (d + SLAB - 1) / SLAB * SLAB, dph = (d + 2 * SLAB - 1) / (2 * SLAB) * (2 * SLAB);
     const int rows_per_chunk = (n + MEAN_CHUNKS - 1) / MEAN_CHUNKS, nchunks_mu = (n + rows_per_chunk - 1) / rows_per_chunk;
     const int *rowmap = m < n ? L.qrows : nullptr;
-    if (!reuse_queries) {
+    if (queries->copy == ProbeQueries::NONE) {
         hipLaunchKernelGGL(col_mean_part, dim3((d + 63) / 64, nchunks_mu), dim3(256), 0, s, X, n, d, rows_per_chunk, L.mu_part);
         hipLaunchKernelGGL(col_mean_final, dim3((dp + 255) / 256), dim3(256), 0, s, L.mu_part, nchunks_mu, n, d, dp, L.mu);
         if (m < n) hipLaunchKernelGGL(sample_rows_k, dim3((m + 255) / 256), dim3(256), 0, s, L.qrows, n, m);
         hipLaunchKernelGGL(row_norms, wide_grid((size_t)m * WAVE), dim3(256), 0, s, X, L.mu, m, d, rowmap, n, L.norms_q);
-        hipLaunchKernelGGL(split_bf16, wide_grid((size_t)m * dp), dim3(256), 0, s, X, L.mu, m, d, dp, rowmap, n, L.xs);
+        hipLaunchKernelGGL(max_norm_k, dim3(1), dim3(1024), 0, s, L.norms_q, m, L.norm_max + 1);
     }
     hipLaunchKernelGGL(row_norms, wide_grid((size_t)nlist * WAVE), dim3(256), 0, s, C, L.mu, nlist, d, (const int *)nullptr, nlist,
                        L.norms_c);
-    hipLaunchKernelGGL(split_bf16, wide_grid((size_t)nlist * dp), dim3(256), 0, s, C, L.mu, nlist, d, dp, (const int *)nullptr,
-                       nlist, L.cs);
     hipLaunchKernelGGL(max_norm_k, dim3(1), dim3(1024), 0, s, L.norms_c, nlist, L.norm_max);
     HIPCHK(hipMemsetAsync(L.fail_count, 0, 4, s));
-    float norm_max = 0.f;
-    HIPCHK(hipMemcpyAsync(&norm_max, L.norm_max, 4, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemsetAsync(L.fail2_count, 0, 4, s));
+    float norm_max2[2] = {0.f, 0.f};
+    HIPCHK(hipMemcpyAsync(norm_max2, L.norm_max, 8, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    const float norm_max = norm_max2[0];
+    auto split_queries = [&]() {
+        hipLaunchKernelGGL(split_bf16, wide_grid((size_t)m * dp), dim3(256), 0, s, X, L.mu, m, d, dp, rowmap, n, L.xs);
+        queries->copy = ProbeQueries::SPLIT;
+    };
+    auto split_centroids = [&]() {
+        hipLaunchKernelGGL(split_bf16, wide_grid((size_t)nlist * dp), dim3(256), 0, s, C, L.mu, nlist, d, dp, (const int *)nullptr, nlist, L.cs);
+    };
+    // the scale is the queries' (it has to stay what it was when they were copied); centroids are means of rows, but a
+    // caller's may be anything: 2^15 for the queries leaves them a factor of two, and 1e30 keeps everything finite
+    HalfScale hs = {};
+    bool half = d > KFLUSH && !queries->no_half && norm_max2[1] > 1e-30f && norm_max2[1] < 1e30f;
+    if (half) {
+        hs = half_scale(sqrtf(norm_max2[1]) * 1.0001f, d, std::max(norm_max, norm_max2[1]));
+        half = sqrtf(norm_max) * 1.0001f * hs.scale < 60000.f;
+    }
+    if (half) {
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&knn_tile_half_other<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)HALF_TILE_LDS));
+        HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&knn_tile_half_other<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)HALF_TILE_LDS));
+        if (queries->copy != ProbeQueries::HALF) {
+            hipLaunchKernelGGL(split_high, wide_grid((size_t)m * (dph / 8)), dim3(256), 0, s, X, L.mu, m, d, dph, hs.scale, rowmap, n, L.xs);
+            queries->copy = ProbeQueries::HALF;
+        }
+        hipLaunchKernelGGL(split_high, wide_grid((size_t)nlist * (dph / 8)), dim3(256), 0, s, C, L.mu, nlist, d, dph, hs.scale,
+                           (const int *)nullptr, nlist, L.cs);
+    } else {
+        if (queries->copy != ProbeQueries::SPLIT) split_queries();
+        split_centroids();
+    }
     const size_t rerank_smem = rerank_lds_bytes(d, kp);
-    for (int q0 = 0; q0 < m; q0 += TS_ROWS) {
-        const int rows = m - q0 < TS_ROWS ? m - q0 : TS_ROWS;
+    // queries q0 .. q0 + rows of the copy in L.xs; qmap, norms: where they are in X, their norms; omap: whose they are
+    auto pass = [&](bool half, int q0, int rows, const int *qmap, const float *norms, const int *omap, int *fail_count, int *fail_rows) {
         hipLaunchKernelGGL(knn_reset, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, rows, L.ccount);
         for (int j0 = 0, jend; j0 < nlist; j0 = jend) {
             jend = j0 + DBC < nlist ? j0 + DBC : nlist;
-            const unsigned gy = (unsigned)((jend - j0 + TN - 1) / TN);
             const int force = jend >= nlist ? 1 : 0;
             auto tiles = [&](auto kernel, int tq) {
-                hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + tq - 1) / tq), gy), dim3(256), 0, s, (const uint4 *)L.xs, dp, q0,
-                                   q0 + rows, j0, jend, L.norms_q, L.tau, L.cnt, L.cand, cap, L.ccount, (const uint4 *)L.cs,
-                                   L.norms_c, 0, (const int *)nullptr, (const int *)nullptr, 0, (const int *)nullptr,
+                hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + tq - 1) / tq), (unsigned)((jend - j0 + TN - 1) / TN)), dim3(256), 0, s,
+                                   (const uint4 *)L.xs, dp, q0, q0 + rows, j0, jend, norms, L.tau, L.cnt, L.cand, cap, L.ccount,
+                                   (const uint4 *)L.cs, L.norms_c, 0, (const int *)nullptr, (const int *)nullptr, 0, (const int *)nullptr,
                                    (const int *)nullptr, (const int *)nullptr, 0);
             };
-            if (d > KFLUSH) {
+            if (half) {
+                const unsigned nqt = (unsigned)((rows + HT - 1) / HT), njt = (unsigned)((jend - j0 + HT - 1) / HT);
+                auto half_tiles = [&](auto kernel) {
+                    hipLaunchKernelGGL(kernel, dim3(8 * ((nqt + 7) / 8) * njt), dim3(HALF_THREADS), HALF_TILE_LDS, s, (const uint4 *)L.xs, dph,
+                                       q0, q0 + rows, j0, jend, norms, L.tau, L.cnt, L.cand, cap, L.ccount, hs.dot_scale,
+                                       (const uint4 *)L.cs, L.norms_c);
+                };
+                if (j0 == 0) half_tiles(knn_tile_half_other<true>); else half_tiles(knn_tile_half_other<false>);
+            } else if (d > KFLUSH) {
                 if (j0 == 0) tiles(knn_tile_mfma<2, true, false, true>, 128);
                 else tiles(knn_tile_mfma<2, true, false>, 128);
             } else {
@@ -2248,15 +2500,32 @@ int ivf_probe_tiles(const float *X, int n, int d, const float *C, int nlist, int
                                L.clist, L.ccount);
             launch_compact(L.tau, L.cnt, L.cand, cap, kp, rows, L.clist, L.ccount, j0 == 0, s);
         }
-        hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, X, n, d, rowmap, C, nlist, (const int *)nullptr,
-                           (const int *)nullptr, (const int *)nullptr, q0, rows, tau, kp, nlist, tile_error_coeff(d, d > KFLUSH), 0.0,
-                           L.norms_q, norm_max, L.tau, L.cnt, L.cand, cap, probe,
-                           (double *)nullptr, L.fail_count, L.fail_rows);
-        HIPCHK(hipGetLastError());
-    }
+        hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, X, n, d, qmap, C, nlist, (const int *)nullptr,
+                           omap, omap, q0, rows, tau, kp, nlist, half ? tile_error_coeff(d, false, true) : tile_error_coeff(d, d > KFLUSH),
+                           half ? hs.e_add : 0.0, norms, norm_max, L.tau, L.cnt, L.cand, cap, probe,
+                           (double *)nullptr, fail_count, fail_rows);
+    };
+    for (int q0 = 0; q0 < m; q0 += TS_ROWS)
+        pass(half, q0, m - q0 < TS_ROWS ? m - q0 : TS_ROWS, rowmap, L.norms_q, nullptr, L.fail_count, L.fail_rows);
+    HIPCHK(hipGetLastError());
     int nfail = 0;
     HIPCHK(hipMemcpyAsync(&nfail, L.fail_count, 4, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    const int *exact_rows = L.fail_rows;
+    if (half && nfail > PROBE_SWEEP_MIN) {
+        // the queries without a certificate, a pass at a time in the place of the copy that just failed them
+        queries->copy = ProbeQueries::NONE;
+        if (nfail > m / 4) queries->no_half = true;       // (and no more of it in the rounds to come)
+        split_centroids();
+        hipLaunchKernelGGL(pick_rows_k, dim3((nfail + 255) / 256), dim3(256), 0, s, L.fail_rows, nfail, m, rowmap, L.norms_q, L.xrow, L.norms_f);
+        hipLaunchKernelGGL(split_bf16, wide_grid((size_t)nfail * dp), dim3(256), 0, s, X, L.mu, nfail, d, dp, L.xrow, n, L.xs);
+        for (int f0 = 0; f0 < nfail; f0 += TS_ROWS)
+            pass(false, f0, nfail - f0 < TS_ROWS ? nfail - f0 : TS_ROWS, L.xrow, L.norms_f, L.fail_rows, L.fail2_count, L.fail2_rows);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(&nfail, L.fail2_count, 4, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        exact_rows = L.fail2_rows;
+    }
     if (nfail > 0) {
         size_t nb_max = L.cand_bytes / (8 * (size_t)nlist);
         if (nb_max > 4096) nb_max = 4096;
@@ -2264,9 +2533,9 @@ int ivf_probe_tiles(const float *X, int n, int d, const float *C, int nlist, int
         for (int f0 = 0; f0 < nfail; f0 += (int)nb_max) {
             const int nb = nfail - f0 < (int)nb_max ? nfail - f0 : (int)nb_max;
             hipLaunchKernelGGL(knn_exact_dists, wide_grid((size_t)nlist * WAVE), dim3(256), 0, s, X, n, rowmap, C, nlist, d,
-                               L.fail_rows + f0, nb, 0, L.cand);
+                               exact_rows + f0, nb, 0, L.cand);
             hipLaunchKernelGGL(knn_exact_select, dim3(nb), dim3(1024), 0, s, L.cand, (size_t)nlist, nlist, (const int *)nullptr,
-                               (const int *)nullptr, tau, L.fail_rows + f0, (const int *)nullptr, m, probe, (double *)nullptr);
+                               (const int *)nullptr, tau, exact_rows + f0, (const int *)nullptr, m, probe, (double *)nullptr);
             HIPCHK(hipGetLastError());
         }
     }
@@ -2408,20 +2677,15 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
         HIPCHK(hipStreamSynchronize(s));
         float xmax;
         memcpy(&xmax, &found[0], 4);
-        if (!(xmax > 0.f) || !(xmax < 1e15f) || found[1] > GAP_QUERIES / 2) {
+        if (!(xmax > 1e-15f) || !(xmax < 1e15f) || found[1] > GAP_QUERIES / 2) {
             // all rows equal, values half precision cannot scale, or neighbours it cannot tell apart
             high_first = false;
         } else {
-            int e = 0;
-            (void)frexpf(xmax, &e);                                 // xmax < 2^e
-            const float scale = ldexpf(1.0f, 15 - e);               // |x| scale < 2^15
-            dot_scale = ldexpf(1.0f, 2 * (e - 15));
-            // a scaled value below 2^-14 may be rounded to a subnormal half or flushed to zero: off by at most
-            // delta = 2^-14 / scale per value, the dot product by delta (sum |q_t| + sum |x_t|) + D delta^2, the
-            // distance by twice that; sum |x_t| <= sqrt(D) |x|
-            const double delta = ldexp(1.0, -14) / (double)scale;
-            e_add = 2.0 * (delta * 2.0 * sqrt((double)d) * sqrt((double)norm_max) + (double)d * delta * delta);
-            hipLaunchKernelGGL(split_high, wide_grid((size_t)n * dph), dim3(256), 0, s, d_X, L.mu, n, d, dph, scale, L.xh);
+            const HalfScale h = half_scale(xmax, d, norm_max);
+            dot_scale = h.dot_scale;
+            e_add = h.e_add;
+            hipLaunchKernelGGL(split_high, wide_grid((size_t)n * (dph / 8)), dim3(256), 0, s, d_X, L.mu, n, d, dph, h.scale, (const int *)nullptr, n,
+                               L.xh);
             HIPCHK(hipMemsetAsync(L.fail2_count, 0, 4, s));
         }
     }

@@ -827,10 +827,12 @@ size_t chunk_lds(int d, int waves) { return d > IVF_DC ? 4 * (size_t)IVF_DC * WA
 // their workspace (C: the centroids as floats); Cd: the centroids as doubles, rows padded to dp.
 int launch_probe(const float *X, int n, int d, int dp, const double *Cd, int nlist, int tau, int32_t *probe, int m,
                  hipStream_t s, const float *C = nullptr, void *tiles_ws = nullptr, size_t tiles_bytes = 0,
-                 int reuse_queries = 0)
+                 ProbeQueries *queries = nullptr)
 {
-    if (d > TILES_MIN_D && C && tiles_bytes > 0)
-        return ivf_probe_tiles(X, n, d, C, nlist, tau, m, probe, tiles_ws, tiles_bytes, s, reuse_queries);
+    if (d > TILES_MIN_D && C && tiles_bytes > 0) {
+        ProbeQueries once;
+        return ivf_probe_tiles(X, n, d, C, nlist, tau, m, probe, tiles_ws, tiles_bytes, s, queries ? queries : &once);
+    }
     const size_t lists = 12 * (size_t)WAVE * tau;
     if (d > IVF_DC)
         hipLaunchKernelGGL(ivf_probe<true>, dim3((m + WAVE - 1) / WAVE), dim3(WAVE), lists + chunk_lds(d, 1), s, X, n, d, dp, Cd,
@@ -970,10 +972,11 @@ int ivf_train_device(const float *X, int n, int d, int nlist, int iters, float *
     const double scale = ldexp(1.0, 62 - ln - e), inv_scale = ldexp(1.0, -(62 - ln - e));
     // the rounds work on min(n, 256 nlist) evenly spaced rows
     const int ms = (long long)n < 256ll * nlist ? n : 256 * nlist;
+    ProbeQueries queries;
     for (int it = 0; it < iters; ++it) {
         hipLaunchKernelGGL(to_double_k, (blocks((size_t)nlist * dp)), dim3(256), 0, s, C, (size_t)nlist, d, dp, L.Cd);
         {
-            const int rc = launch_probe(X, n, d, dp, L.Cd, nlist, 1, L.probe, ms, s, C, L.tiles_ws, L.tiles_bytes, it > 0);
+            const int rc = launch_probe(X, n, d, dp, L.Cd, nlist, 1, L.probe, ms, s, C, L.tiles_ws, L.tiles_bytes, &queries);
             if (rc != TSNE_OK) return rc;
         }
         hipLaunchKernelGGL(fill_u64_k, (blocks(cd)), dim3(256), 0, s, L.sums, cd);
