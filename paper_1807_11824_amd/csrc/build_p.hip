@@ -1255,7 +1255,9 @@ __global__ __launch_bounds__(256) void knn_compact(float *__restrict__ tau, int 
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int e = lane + WAVE * r;
-                v[r] = e < total ? buf[e < have ? e : done + (e - have)] : NO_PAIR;
+                // (read whatever it is: 32 loads each behind a branch took nearly twice as long)
+                const uint64_t got = buf[min(e < have ? e : done + (e - have), c - 1)];
+                v[r] = e < total ? got : NO_PAIR;
                 const uint32_t d = (uint32_t)(v[r] >> 32);
                 valid += (int)__popcll(__ballot(d != NONE));
                 lo = min(lo, d);
@@ -1271,12 +1273,31 @@ __global__ __launch_bounds__(256) void knn_compact(float *__restrict__ tau, int 
             done += take;
             // smallest hi with at least k' distances <= hi; `all`: exactly k' are
             bool all = valid <= kp;
-            while (lo < hi && !all) {
-                const uint32_t mid = lo + ((hi - lo) >> 1);     // (below NONE)
+            int under = 0, upto = valid;        // how many are below lo, and up to hi
+            if (R >= 16 && kp <= WAVE && !all) {
+                // few of many: the k'-th smallest of the lanes' smallest is as far as the k'-th of all can be
+                uint32_t least = NONE, a = lo, b = hi;
+#pragma unroll
+                for (int r = 0; r < R; ++r) least = min(least, (uint32_t)(v[r] >> 32));
+                while (a < b) {
+                    const uint32_t mid = a + ((b - a) >> 1);
+                    if ((int)__popcll(__ballot(least <= mid)) >= kp) b = mid; else a = mid + 1;
+                }
+                hi = b;
+                upto = 0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) upto += (int)__popcll(__ballot((uint32_t)(v[r] >> 32) <= hi));
+                all = upto == kp;
+            }
+            // every other step splits the range where the counts at its ends say, the others halve it
+            for (int step = 0; lo < hi && !all; ++step) {
+                uint32_t cut = (hi - lo) >> 1;
+                if (step % 2 == 0) cut = min((uint32_t)((float)(hi - lo) * ((float)(kp - under) / (float)(upto - under))), hi - lo - 1u);
+                const uint32_t mid = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lo + cut));     // (below hi)
                 int below = 0;
 #pragma unroll
                 for (int r = 0; r < R; ++r) below += (int)__popcll(__ballot((uint32_t)(v[r] >> 32) <= mid));
-                if (below >= kp) hi = mid; else lo = mid + 1;
+                if (below >= kp) { hi = mid; upto = below; } else { lo = mid + 1; under = below; }
                 all = below == kp;
             }
             int ties = kp;              // how many of the distances equal to hi are kept
@@ -1297,6 +1318,7 @@ __global__ __launch_bounds__(256) void knn_compact(float *__restrict__ tau, int 
                                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)meq, 0u)) < ties));
                 if (!all) ties -= (int)__popcll(meq);
                 const uint64_t mk = __ballot(keep);
+                if (mk == 0) continue;
                 if (keep) {
                     buf[pos + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u))] = v[r];
                     top = max(top, d);
@@ -1318,13 +1340,17 @@ __global__ __launch_bounds__(256) void knn_compact(float *__restrict__ tau, int 
 
 // (beside k' survivors a round takes in 192 new pairs at least: 512 - 320, 1024 - 832, 4096 - 1920; an ordinary pass has
 // some COMPACT_SLACK of them, one or two rounds)
-// dense: the pass behind a first launch, up to DBC pairs a row
+// dense: the pairs of a row behind a first launch (at most DBC), 0 behind others
 static void launch_compact(float *tau, int *cnt, uint64_t *cand, int cap, int kp, int rows, const int *list, const int *count,
-                           bool dense, hipStream_t s)
+                           int dense, hipStream_t s)
 {
     const dim3 grid((unsigned)((rows < 8192 ? rows : 8192) + 3) / 4);
-    if (dense && kp <= 832)
+    if (dense > 1536 && kp <= 832)
         hipLaunchKernelGGL(knn_compact<DBC / WAVE>, grid, dim3(256), 0, s, tau, cnt, cand, cap, kp, rows, list, count);
+    else if (dense > 1024 && kp <= 832)
+        hipLaunchKernelGGL(knn_compact<24>, grid, dim3(256), 0, s, tau, cnt, cand, cap, kp, rows, list, count);
+    else if (dense > 0 && kp <= 832)
+        hipLaunchKernelGGL(knn_compact<16>, grid, dim3(256), 0, s, tau, cnt, cand, cap, kp, rows, list, count);
     else if (kp <= 320)
         hipLaunchKernelGGL(knn_compact<8>, grid, dim3(256), 0, s, tau, cnt, cand, cap, kp, rows, list, count);
     else if (kp <= 832)
@@ -2288,7 +2314,7 @@ int ivf_search_tiles(const float *X, int n, int d, int k, int nlist, int tau, co
                 const int force = r == tau - 1 && c == nchunks - 1 ? 1 : 0;
                 hipLaunchKernelGGL(knn_compact_list, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, cap, kp, rows, force,
                                    L.clist, L.ccount);
-                launch_compact(L.tau, L.cnt, L.cand, cap, kp, rows, L.clist, L.ccount, dense, s);
+                launch_compact(L.tau, L.cnt, L.cand, cap, kp, rows, L.clist, L.ccount, dense ? std::min(max_list, DBC) : 0, s);
             }
         }
         hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, X, n, d,
@@ -2498,7 +2524,7 @@ int ivf_probe_tiles(const float *X, int n, int d, const float *C, int nlist, int
             }
             hipLaunchKernelGGL(knn_compact_list, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, cap, kp, rows, force,
                                L.clist, L.ccount);
-            launch_compact(L.tau, L.cnt, L.cand, cap, kp, rows, L.clist, L.ccount, j0 == 0, s);
+            launch_compact(L.tau, L.cnt, L.cand, cap, kp, rows, L.clist, L.ccount, j0 == 0 ? jend : 0, s);
         }
         hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, X, n, d, qmap, C, nlist, (const int *)nullptr,
                            omap, omap, q0, rows, tau, kp, nlist, half ? tile_error_coeff(d, false, true) : tile_error_coeff(d, d > KFLUSH),
@@ -2631,7 +2657,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
     };
     for (const auto &a : lds) HIPCHK(hipFuncSetAttribute(a.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.bytes));
     const size_t rerank_smem = rerank_lds_bytes(d, kp);
-    auto compact = [&](int rows, const int *cc, bool dense) {
+    auto compact = [&](int rows, const int *cc, int dense) {
         launch_compact(L.tau, L.cnt, L.cand, cap, kp, rows, L.clist, cc, dense, s);
     };
     // three-product tiles of query rows q0 .. qend (row fr[q] of X if fr is given) against database rows j0 .. jend
@@ -2738,7 +2764,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
                 hipLaunchKernelGGL(knn_compact_list, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, cap, kp, rows, force,
                                    L.clist, cc);
             }
-            compact(rows, cc, dense);
+            compact(rows, cc, dense ? std::min(n, DBC) : 0);
         }
         hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, d_X, n, d, (const int *)nullptr, d_X, n,
                            (const int *)nullptr, (const int *)nullptr, (const int *)nullptr, q0, rows, k, kp, n - 1,
@@ -2775,7 +2801,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
                 mfma_tiles(L.xsf, L.norms_f, 0, rows, j0, jend, fr, L.ccount);
                 hipLaunchKernelGGL(knn_compact_list, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, cap, kp, rows, force,
                                    L.clist, L.ccount);
-                compact(rows, L.ccount, j0 == 0);
+                compact(rows, L.ccount, j0 == 0 ? jend : 0);
             }
             hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, d_X, n, d, fr, d_X, n, (const int *)nullptr, fr, fr,
                                0, rows, k, kp, n - 1, tile_error_coeff(d, true), 0.0, L.norms_f, norm_max, L.tau, L.cnt, L.cand, cap,
