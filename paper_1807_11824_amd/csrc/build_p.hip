@@ -84,14 +84,24 @@ __global__ __launch_bounds__(256) void col_mean_part(const float *__restrict__ X
     if (rg == 0 && c < d) part[(size_t)blockIdx.y * d + c] = ((acc[0][threadIdx.x] + acc[1][threadIdx.x]) + acc[2][threadIdx.x]) + acc[3][threadIdx.x];
 }
 
+// MEAN_SEGS threads a column, each a contiguous share of the chunks (one thread a column was a chain of 256 dependent
+// reads: 60 of the 382 us of a build of 2000 x 50).
+constexpr int MEAN_SEGS = 16;
 __global__ __launch_bounds__(256) void col_mean_final(const double *__restrict__ part, int nchunks, int n, int d, int dp,
                                                       float *__restrict__ mu)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= dp) return;
+    __shared__ double sum[MEAN_SEGS][256 / MEAN_SEGS];
+    const int cl = (int)threadIdx.x % (256 / MEAN_SEGS), seg = (int)threadIdx.x / (256 / MEAN_SEGS);
+    const int c = blockIdx.x * (256 / MEAN_SEGS) + cl, len = (nchunks + MEAN_SEGS - 1) / MEAN_SEGS;
     double s = 0.0;
-    if (c < d)
-        for (int q = 0; q < nchunks; ++q) s += part[(size_t)q * d + c];
+    if (c < d) {
+#pragma unroll 8
+        for (int q = seg * len; q < min(nchunks, (seg + 1) * len); ++q) s += part[(size_t)q * d + c];
+    }
+    sum[seg][cl] = s;
+    __syncthreads();
+    if (seg != 0 || c >= dp) return;
+    for (int k = 1; k < MEAN_SEGS; ++k) s += sum[k][cl];
     mu[c] = c < d ? (float)(s / (double)n) : 0.f;
 }
 
@@ -2257,7 +2267,7 @@ int ivf_search_tiles(const float *X, int n, int d, int k, int nlist, int tau, co
     const int dp = (d + SLAB - 1) / SLAB * SLAB;
     const int rows_per_chunk = (n + MEAN_CHUNKS - 1) / MEAN_CHUNKS, nchunks_mu = (n + rows_per_chunk - 1) / rows_per_chunk;
     hipLaunchKernelGGL(col_mean_part, dim3((d + 63) / 64, nchunks_mu), dim3(256), 0, s, X, n, d, rows_per_chunk, L.mu_part);
-    hipLaunchKernelGGL(col_mean_final, dim3((dp + 255) / 256), dim3(256), 0, s, L.mu_part, nchunks_mu, n, d, dp, L.mu);
+    hipLaunchKernelGGL(col_mean_final, dim3((dp + 256 / MEAN_SEGS - 1) / (256 / MEAN_SEGS)), dim3(256), 0, s, L.mu_part, nchunks_mu, n, d, dp, L.mu);
     hipLaunchKernelGGL(row_norms, wide_grid((size_t)n * WAVE), dim3(256), 0, s, X, L.mu, n, d, lorder, n, L.norms);
     hipLaunchKernelGGL(max_norm_k, dim3(1), dim3(1024), 0, s, L.norms, n, L.norm_max);
     hipLaunchKernelGGL(probe_gather, wide_grid((size_t)n * tau), dim3(256), 0, s, probe, lorder, n, tau, nlist, L.probe_l);
@@ -2450,7 +2460,7 @@ int ivf_probe_tiles(const float *X, int n, int d, const float *C, int nlist, int
     const int *rowmap = m < n ? L.qrows : nullptr;
     if (queries->copy == ProbeQueries::NONE) {
         hipLaunchKernelGGL(col_mean_part, dim3((d + 63) / 64, nchunks_mu), dim3(256), 0, s, X, n, d, rows_per_chunk, L.mu_part);
-        hipLaunchKernelGGL(col_mean_final, dim3((dp + 255) / 256), dim3(256), 0, s, L.mu_part, nchunks_mu, n, d, dp, L.mu);
+        hipLaunchKernelGGL(col_mean_final, dim3((dp + 256 / MEAN_SEGS - 1) / (256 / MEAN_SEGS)), dim3(256), 0, s, L.mu_part, nchunks_mu, n, d, dp, L.mu);
         if (m < n) hipLaunchKernelGGL(sample_rows_k, dim3((m + 255) / 256), dim3(256), 0, s, L.qrows, n, m);
         hipLaunchKernelGGL(row_norms, wide_grid((size_t)m * WAVE), dim3(256), 0, s, X, L.mu, m, d, rowmap, n, L.norms_q);
         hipLaunchKernelGGL(max_norm_k, dim3(1), dim3(1024), 0, s, L.norms_q, m, L.norm_max + 1);
@@ -2634,9 +2644,8 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
     const int dp = (d + SLAB - 1) / SLAB * SLAB;
     const int rows_per_chunk = (n + MEAN_CHUNKS - 1) / MEAN_CHUNKS, nchunks = (n + rows_per_chunk - 1) / rows_per_chunk;
     hipLaunchKernelGGL(col_mean_part, dim3((d + 63) / 64, nchunks), dim3(256), 0, s, d_X, n, d, rows_per_chunk, L.mu_part);
-    hipLaunchKernelGGL(col_mean_final, dim3((dp + 255) / 256), dim3(256), 0, s, L.mu_part, nchunks, n, d, dp, L.mu);
+    hipLaunchKernelGGL(col_mean_final, dim3((dp + 256 / MEAN_SEGS - 1) / (256 / MEAN_SEGS)), dim3(256), 0, s, L.mu_part, nchunks, n, d, dp, L.mu);
     hipLaunchKernelGGL(row_norms, wide_grid((size_t)n * WAVE), dim3(256), 0, s, d_X, L.mu, n, d, (const int *)nullptr, n, L.norms);
-    hipLaunchKernelGGL(split_bf16, wide_grid((size_t)n * dp), dim3(256), 0, s, d_X, L.mu, n, d, dp, (const int *)nullptr, n, L.xs);
     hipLaunchKernelGGL(max_norm_k, dim3(1), dim3(1024), 0, s, L.norms, n, L.norm_max);
     HIPCHK(hipMemsetAsync(L.fail_count, 0, 4, s));
     HIPCHK(hipMemsetAsync(L.unconv, 0, 4, s));
@@ -2715,8 +2724,13 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
             HIPCHK(hipMemsetAsync(L.fail2_count, 0, 4, s));
         }
     }
+    // (only where three-product tiles run: not if half precision certifies every row)
+    auto split = [&]() {
+        hipLaunchKernelGGL(split_bf16, wide_grid((size_t)n * dp), dim3(256), 0, s, d_X, L.mu, n, d, dp, (const int *)nullptr, n, L.xs);
+    };
     // equal blocks of whole tiles (a short last one would leave most compute units idle)
     bool high = high_first;
+    if (!high) split();
     for (int q0 = 0; q0 < n; q0 += block) {
         const int qend = q0 + block < n ? q0 + block : n, rows = qend - q0;
         // (a workgroup per query tile: at least half of the compute units have to get one, 41,000 rows of 300 coordinates
@@ -2778,7 +2792,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
             int failed = 0;
             HIPCHK(hipMemcpyAsync(&failed, L.fail_count, 4, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
-            if (failed > rows / 2) high = false;
+            if (failed > rows / 2) { high = false; split(); }
         }
     }
     int nfail = 0, nfail2 = 0;
@@ -2789,6 +2803,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
     if (high_first && nfail + nfail2 > 0) {
         // second sweep: the rows the first one could not certify, QB at a time, as queries of their own (a split
         // copy of just these rows) against all rows
+        if (high && nfail > 0) split();
         for (int f0 = 0; f0 < nfail; f0 += QB) {
             const int rows = nfail - f0 < QB ? nfail - f0 : QB;
             const int *fr = L.fail_rows + f0;
