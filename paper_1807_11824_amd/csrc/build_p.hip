@@ -25,7 +25,9 @@
 #include "tsne_internal.h"
 
 #include <algorithm>
+#include <functional>
 
+#include <limits.h>
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -634,6 +636,43 @@ constexpr size_t HALF_TILE_LDS = 2 * (size_t)HALF_BUF;
 constexpr size_t HALF_OWN_LDS = HALF_TILE_LDS + 3 * HT * 4;     // and norms, cut-offs and fill counts of the query tile
 constexpr size_t HALF_GATHER_LDS = HALF_OWN_LDS + HT * 4;       // and its queries
 
+constexpr int ORD_STEP = DBC / HT;        // tiles a launch takes from a list
+static_assert(ORD_STEP == 8, "eight 16-bit numbers are one load");
+// The database tiles of every query tile of a block (tile_order_k, tile_rest_k): query tile b has count[b] of them (`all` if
+// count is null), tiles[b stride ..], of which the launch takes first .. first + ORD_STEP.  And what the kernel needs to put
+// the rows that are due for compaction on the list (the rule of knn_compact_list).
+struct TileLists {
+    const uint16_t *tiles;
+    const int *count;
+    int stride, all, first, kp;
+    int *clist, *ccount, *ccount_next;
+};
+// what workgroup b takes of its list: how many tiles, and (tile_numbers) which, two 16-bit numbers a word, wave-uniform
+__device__ __forceinline__ int tile_count_of(const TileLists &t, int b)
+{
+    const int have = t.count ? t.count[b] : t.all;
+    return __builtin_amdgcn_readfirstlane(max(min(have - t.first, ORD_STEP), 0));
+}
+__device__ __forceinline__ uint4 tile_numbers(const TileLists &t, int b)
+{
+    // (lists start on 16-byte boundaries, `first` is a multiple of eight, and a list has room for whole eights)
+    const uint4 v = *reinterpret_cast<const uint4 *>(t.tiles + (size_t)b * t.stride + t.first);
+    return make_uint4((uint32_t)__builtin_amdgcn_readfirstlane((int)v.x), (uint32_t)__builtin_amdgcn_readfirstlane((int)v.y),
+                      (uint32_t)__builtin_amdgcn_readfirstlane((int)v.z), (uint32_t)__builtin_amdgcn_readfirstlane((int)v.w));
+}
+// the i-th of them (the last one beyond)
+__device__ __forceinline__ int tile_number(uint4 v, int i)
+{
+    const uint32_t a = i < 4 ? (i < 2 ? v.x : v.y) : (i < 6 ? v.z : v.w);
+    return (int)((i & 1) || i >= ORD_STEP ? a >> 16 : a & 0xFFFFu);
+}
+// a row whose buffer of cap holds c pairs is due for compaction
+__device__ __forceinline__ bool compaction_due(int c, float cut, int cap, int kp)
+{
+    const int cc = min(c, cap);
+    return cc >= kp && (!(cut < INFINITY) || cc >= kp + COMPACT_SLACK || cc + COMPACT_EVERY * DBC > cap);
+}
+
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void glb_void;
 
@@ -1026,13 +1065,15 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int NS, bool DENSE>
+// ORDER: not all tiles from j0 to jend but those on the query tile's list, see tile_order_k; a launch takes ORD_STEP of them.
+// DENSE is then every pair at the place of its tile in the launch and its row in the tile.
+template <int NS, bool DENSE, bool ORDER>
 __global__ __launch_bounds__(512, 1) void knn_tile_resident(const uint4 *__restrict__ Xs, int q0, int qend, int j0, int jend,
                                                             const float *__restrict__ norms,
                                                             const float *__restrict__ tau, int *__restrict__ cnt,
                                                             uint64_t *__restrict__ cand, int cap, int kp, int force,
                                                             int *__restrict__ clist, int *__restrict__ ccount,
-                                                            int *__restrict__ ccount_next)
+                                                            int *__restrict__ ccount_next, TileLists lists)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char *Bs = smem;                                   // [2 groups][NS][RT] rows
@@ -1041,9 +1082,19 @@ __global__ __launch_bounds__(512, 1) void knn_tile_resident(const uint4 *__restr
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int g = w >> 2, wq = w & 3;
     const int r32 = lane & 31, h = lane >> 5, sw = swz(r32);
-    const int qa = q0 + blockIdx.x * RQ;
-    constexpr int row16 = NS * 8;          // 16-byte pieces per row of Xs
+    const int per = ((qend - q0 + RQ - 1) / RQ + 7) / 8;
+    const int qt = ORDER ? (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
     if (blockIdx.x == 0 && tid == 0) *ccount_next = 0;   // the list of the next launch (nobody reads it any more)
+    uint4 nos = make_uint4(0u, 0u, 0u, 0u);
+    int nmine = 0;
+    if (ORDER) {
+        if ((int)(blockIdx.x >> 3) >= per || q0 + qt * RQ >= qend) return;       // (the grid is 8 per workgroups)
+        nmine = tile_count_of(lists, qt);
+        if (nmine == 0) return;
+        nos = tile_numbers(lists, qt);
+    }
+    const int qa = q0 + qt * RQ;
+    constexpr int row16 = NS * 8;          // 16-byte pieces per row of Xs
     // the wave's query fragments: [block][slab][step] high and low parts, as the matrix cores take them
     bf16x8 afh[2][NS][2], afl[2][NS][2];
 #pragma unroll
@@ -1067,11 +1118,13 @@ __global__ __launch_bounds__(512, 1) void knn_tile_resident(const uint4 *__restr
     }
     unsigned char *Bg = Bs + g * NS * RT * SLAB_ROW;
     const int bpiece = tid & 7, blrow = (tid & 255) >> 3;
-    const int ntile = (jend - j0 + RT - 1) / RT, npair = (ntile + 1) / 2;
+    const int ntile = (jend - j0 + RT - 1) / RT, npair = ORDER ? nmine : (ntile + 1) / 2;
+    // first database row of a trip (ORDER: two of this kernel's tiles are one of the lists')
+    auto trip_base = [=](int pair) { return ORDER ? tile_number(nos, pair) * HT : j0 + 2 * pair * RT; };
     uint4 rb[4 * NS];
     float njn[2][2];   // |x|^2 of this lane's two columns of each half of the tile in rb
     auto load_tile = [&](int pair) {
-        const int ja = j0 + (2 * pair + g) * RT;
+        const int ja = trip_base(pair) + g * RT;
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             const int r = ja + blrow + 32 * it;
@@ -1089,7 +1142,7 @@ __global__ __launch_bounds__(512, 1) void knn_tile_resident(const uint4 *__restr
     };
     floatx16 part[2][2];
     float njc[2] = {INFINITY, INFINITY};   // the same for the half in `part`
-    int jac = j0;                          // first database row of that half
+    int jac = j0, place = 0;               // first database row of that half, and its place in a dense launch
     auto test_tile = [&]() {
         // one base per lane, the rest compile-time offsets (and no addresses carried around the loop)
         int lbase = wq * 64 + 4 * h;
@@ -1106,8 +1159,9 @@ __global__ __launch_bounds__(512, 1) void knn_tile_resident(const uint4 *__restr
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const int off = a * 32 + 8 * (i / 4) + i % 4, q = qa + lbase + off;
-                        if (q < qend && j < jend)
-                            cand[(size_t)(q - q0) * cap + (j - j0)] = dense_pair(qn_l[off], nj, part[a][b][i], j == q, j);
+                        // (ORDER: a row past the end leaves no pair, at its place)
+                        if (q < qend && (ORDER || j < jend))
+                            cand[(size_t)(q - q0) * cap + (ORDER ? place + b * 32 + r32 : j - j0)] = dense_pair(qn_l[off], nj, part[a][b][i], j == q, j);
                     }
                 continue;
             }
@@ -1194,7 +1248,8 @@ __global__ __launch_bounds__(512, 1) void knn_tile_resident(const uint4 *__restr
             }
             njc[0] = njl[hf][0];
             njc[1] = njl[hf][1];
-            jac = j0 + (2 * pair + g) * RT + hf * 64;
+            jac = trip_base(pair) + g * RT + hf * 64;
+            place = (2 * pair + g) * RT + hf * 64;
             have = true;
             if (g == 0) test_tile();
         }
@@ -1206,10 +1261,9 @@ __global__ __launch_bounds__(512, 1) void knn_tile_resident(const uint4 *__restr
     for (int t = tid; t < RQ; t += 512) {
         const int q = qa + t;
         if (q < qend) {
-            const int c = DENSE ? jend - j0 : qc[t];
+            const int c = DENSE ? (ORDER ? nmine * HT : jend - j0) : qc[t];
             cnt[q - q0] = c;
-            const int cc = min(c, cap);
-            if (cc >= kp && (force || !(qd[t] < INFINITY) || cc >= kp + COMPACT_SLACK || cc + COMPACT_EVERY * DBC > cap))
+            if (compaction_due(c, qd[t], cap, kp) || (force && min(c, cap) >= kp))
                 clist[atomicAdd(ccount, 1)] = q - q0;    // any order
         }
     }
@@ -1940,6 +1994,228 @@ __global__ void d2_to_float(const double *__restrict__ in, float *__restrict__ o
     if (i < m) out[i] = (float)in[i];
 }
 
+// ---- the exact search in an order of the rows that keeps neighbours together
+// Taken as they come, a query's neighbours turn up anywhere in the sweep: its cut-off settles slowly, and some hundreds of
+// pairs beyond the k' it ends with are tested the long way, appended and compacted; and no tile can be left out.  So the rows
+// are grouped by the nearest of some evenly spaced rows (the pivots, in an order that puts each next to one near it), the
+// search works on copies in that order, and every query tile of 256 rows first meets the ORD_FIRST database tiles whose
+// centres are nearest to its own.  That settles the cut-offs.  Of the other tiles it meets, in row order, those that can
+// still hold a neighbour: with |c - c'| the distance of the centres and r, r' the tiles' radii, no pair is closer than
+// |c - c'| - r - r', and a tile where that is beyond the largest cut-off is left out (its pairs are, as the certificate
+// asks of every pair that was not kept, no closer than the cut-off).  Between clusters that are well apart nearly all tiles
+// are.  The neighbour lists are what they were: any order of the rows gives them.
+// 512,000 rows of 50 coordinates in four blobs: 187 -> 104 ms.  Where no tile can be left out the order only costs (the query tiles
+// no longer meet the same database tiles at a time, and 33,000, 60,000 and 200,000 rows in clusters that touch went from 4.6,
+// 7.5 and 48.5 to 6.0, 10.2 and 54.9 ms), so it is taken where the pivots say that the rows fall into groups well apart: at
+// least half of their pairs farther apart than ORD_APART times what a pivot is from the nearest other one (root mean square).
+// A tile's radius and a row's cut-off are about as large as the latter, which makes two radii and a cut-off.  For four blobs
+// three quarters of the pairs are, by a factor of ten; for clusters that touch at most a quarter.  And from ORD_MIN_ROWS rows
+// on: 100,000 rows in four blobs 17.1 -> 19.1 ms, 140,000 29.6 -> 26.8, 200,000 49 -> 36, 300,000 82 -> 56; with twenty blobs
+// in 8 dimensions too many query tiles straddle two, which the first block of query rows finds out in 2 ms.
+constexpr int ORD_FIRST = 16;                  // tiles taken nearest first
+constexpr int ORD_MIN_ROWS = 196608, ORD_MAX_TILES = 4096;
+constexpr int ORD_MAX_PIVOTS = 512;
+// What launches take (with the compaction behind them 120, 80 and 40 us): along the lists, over DBC of all rows, and over
+// ORD_ALONE_ROWS of all rows for one query tile by itself.
+constexpr int ORD_LAUNCH = 3, ORD_PLAIN = 2, ORD_ALONE = 1, ORD_ALONE_ROWS = COMPACT_EVERY * DBC;
+constexpr float ORD_APART = 3.f;
+static_assert(ORD_FIRST % ORD_STEP == 0 && ORD_MAX_TILES % ORD_STEP == 0 && RQ == HT, "whole launches");
+
+// label[row] = number (in the pivots' own order: prank) of the nearest pivot, from a dense launch against m pivots; a wave a row
+__global__ __launch_bounds__(256) void nearest_pivot_k(const uint64_t *__restrict__ cand, int cap, int rows, int m,
+                                                       const int *__restrict__ prank, int32_t *__restrict__ label)
+{
+    const int row = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    if (row >= rows) return;
+    uint64_t best = NO_PAIR;
+#pragma unroll 4
+    for (int j = lane_id(); j < m; j += WAVE) best = min(best, cand[(size_t)row * cap + j]);
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) best = min(best, (uint64_t)__shfl_xor((unsigned long long)best, o, WAVE));
+    // (a row without a finite distance: the first pivot)
+    if (lane_id() == 0) label[row] = prank[best == NO_PAIR ? 0 : min((int)(uint32_t)best, m - 1)];
+}
+
+// apart[0] = pairs of pivots that are farther apart than ORD_APART times a pivot's distance from the nearest other one; one
+// workgroup, a thread a pivot.  cand: their squared distances (dense).
+__global__ __launch_bounds__(ORD_MAX_PIVOTS) void pivot_apart_k(const uint64_t *__restrict__ cand, int cap, int m, int *__restrict__ apart)
+{
+    __shared__ double part[ORD_MAX_PIVOTS / WAVE];
+    __shared__ int count[ORD_MAX_PIVOTS / WAVE];
+    const int tid = (int)threadIdx.x, i = min(tid, m - 1);
+    // (column i of the symmetric table: neighbouring threads read neighbouring words; a pair that is none is no number)
+    float near = INFINITY;
+#pragma unroll 8
+    for (int j = 0; j < m; ++j) {
+        const float v = unorderable((uint32_t)(cand[(size_t)j * cap + i] >> 32));
+        if (j != i && v < near) near = v;
+    }
+    const double mine = wave_sum(tid < m ? (double)fmaxf(near, 0.f) : 0.0);
+    if (lane_id() == 0) part[tid >> 6] = mine;
+    __syncthreads();
+    double sum = 0.0;
+    for (int w = 0; w < ORD_MAX_PIVOTS / WAVE; ++w) sum += part[w];
+    const float limit = (float)(sum / m) * (ORD_APART * ORD_APART);
+    int far = 0;
+#pragma unroll 8
+    for (int j = 0; j < m; ++j) far += unorderable((uint32_t)(cand[(size_t)j * cap + i] >> 32)) > limit ? 1 : 0;
+    if (tid >= m) far = 0;
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) far += __shfl_xor(far, o, WAVE);
+    if (lane_id() == 0) count[tid >> 6] = far;
+    __syncthreads();
+    if (tid == 0) {
+        int all = 0;
+        for (int w = 0; w < ORD_MAX_PIVOTS / WAVE; ++w) all += count[w];
+        apart[0] = all / 2;
+    }
+}
+
+// The pivots in an order in which each is followed by the nearest one left; one workgroup.  cand: their distances (dense).
+__global__ __launch_bounds__(ORD_MAX_PIVOTS) void pivot_chain_k(const uint64_t *__restrict__ cand, int cap, int m, int *__restrict__ prank)
+{
+    __shared__ uint64_t best[ORD_MAX_PIVOTS / WAVE];
+    const int tid = (int)threadIdx.x;
+    bool left = tid < m && tid != 0;
+    int cur = 0;
+    if (tid == 0) prank[0] = 0;
+    for (int i = 1; i < m; ++i) {
+        // (a pair that is none, say between copies of values that are no numbers, comes last; ties by number)
+        uint64_t key = left ? ((cand[(size_t)cur * cap + tid] >> 32) << 32) | (uint32_t)tid : ~0ull;
+#pragma unroll
+        for (int o = WAVE / 2; o > 0; o >>= 1) key = min(key, (uint64_t)__shfl_xor((unsigned long long)key, o, WAVE));
+        if (lane_id() == 0) best[tid >> 6] = key;
+        __syncthreads();
+        key = best[0];
+        for (int w = 1; w < ORD_MAX_PIVOTS / WAVE; ++w) key = min(key, best[w]);
+        cur = min((int)(uint32_t)key, m - 1);
+        if (tid == cur) { left = false; prank[cur] = i; }
+        __syncthreads();
+    }
+}
+
+// Centre (relative to mu) of the rows of every tile of HT rows; a workgroup a tile, a thread a column.
+__global__ __launch_bounds__(256) void tile_centre_k(const float *__restrict__ X, const float *__restrict__ mu, int n, int d,
+                                                     const int *__restrict__ ord, float *__restrict__ centre)
+{
+    __shared__ int rows[HT];
+    const int r0 = (int)blockIdx.x * HT, m = min(HT, n - r0);
+    for (int t = (int)threadIdx.x; t < m; t += 256) rows[t] = min(max(ord[r0 + t], 0), n - 1);
+    __syncthreads();
+    for (int c = (int)threadIdx.x; c < d; c += 256) {
+        float a = 0.f;
+#pragma unroll 8
+        for (int t = 0; t < m; ++t) a += X[(size_t)rows[t] * d + c] - mu[c];
+        centre[(size_t)blockIdx.x * d + c] = a / (float)m;
+    }
+}
+
+// radius2[tile] = largest squared distance of its rows from its centre (bits of a non-negative float; zero on entry).  Any
+// point would do for a centre, as long as the radius is taken around the same one.
+__global__ __launch_bounds__(256) void tile_radius_k(const float *__restrict__ X, const float *__restrict__ mu, int n, int d,
+                                                     const int *__restrict__ ord, const float *__restrict__ centre,
+                                                     unsigned int *__restrict__ radius2)
+{
+    const int r = (int)(global_index() >> 6);
+    if (r >= n) return;
+    const float *x = X + (size_t)min(max(ord[r], 0), n - 1) * d, *c = centre + (size_t)(r / HT) * d;
+    float a = 0.f;
+#pragma unroll 4
+    for (int t = lane_id(); t < d; t += WAVE) { const float v = (x[t] - mu[t]) - c[t]; a = fmaf(v, v, a); }
+    a = wave_sum(a);
+    // (not a number: nothing is left out around it)
+    if (lane_id() == 0) atomicMax(radius2 + r / HT, a >= 0.f ? __float_as_uint(a) : 0x7F800000u);
+}
+
+// For query tile qt0 + blockIdx.x: near[tile] = what its pairs with every tile are apart at least, and the ORD_FIRST
+// tiles with the nearest centres (less their radius, so that a wide tile comes early).  The bound: each of the three
+// distances is a float sum of at most 2048 squares and a root, good to 2^-24 (2048 / 64 + 16) < 3e-6 relative, of
+// coordinates that are off by 2^-24 |x - mu| each; 1e-4 of the centres' distance and of the radii covers that as long as
+// the coordinates' own rounding is small against the distances (and where it is not, the bound of a tile distance, which
+// the certificate takes off the cut-off, is far larger).
+__global__ __launch_bounds__(1024) void tile_order_k(const float *__restrict__ centre, const float *__restrict__ radius2, int ntiles,
+                                                     int d, int qt0, float *__restrict__ near, uint16_t *__restrict__ first)
+{
+    extern __shared__ __align__(16) unsigned char osm[];
+    float *c = reinterpret_cast<float *>(osm);                // the query tile's centre
+    float *key = c + d;                                       // of every tile
+    __shared__ uint64_t best[16];
+    const int tid = (int)threadIdx.x, w = tid >> 6, me = qt0 + (int)blockIdx.x;
+    for (int t = tid; t < d; t += 1024) c[t] = centre[(size_t)me * d + t];
+    __syncthreads();
+    const float r1 = sqrtf(radius2[me]);
+    for (int t = w; t < ntiles; t += 16) {
+        const float *o = centre + (size_t)t * d;
+        float a = 0.f;
+#pragma unroll 4
+        for (int u = lane_id(); u < d; u += WAVE) { const float v = c[u] - o[u]; a = fmaf(v, v, a); }
+        a = wave_sum(a);
+        if (lane_id() == 0) {
+            const float dist = sqrtf(a), r2 = sqrtf(radius2[t]);
+            const float b = dist * (1.f - 1e-4f) - (r1 + r2) * (1.f + 1e-4f);
+            near[(size_t)blockIdx.x * ntiles + t] = b > 0.f ? b : 0.f;      // (also where it is no number)
+            const float k = t == me ? -INFINITY : dist - r2;
+            key[t] = k < INFINITY ? k : 3.0e38f;
+        }
+    }
+    __syncthreads();
+    for (int i = 0; i < ORD_FIRST; ++i) {
+        uint64_t b = ~0ull;
+        for (int t = tid; t < ntiles; t += 1024) b = min(b, ((uint64_t)orderable(key[t]) << 32) | (uint32_t)t);
+#pragma unroll
+        for (int o = WAVE / 2; o > 0; o >>= 1) b = min(b, (uint64_t)__shfl_xor((unsigned long long)b, o, WAVE));
+        if (lane_id() == 0) best[w] = b;
+        __syncthreads();
+        b = best[0];
+        for (int k = 1; k < 16; ++k) b = min(b, best[k]);
+        const int t = (int)(uint32_t)b;
+        if (tid == 0 && i < ntiles) { first[(size_t)blockIdx.x * ORD_FIRST + i] = (uint16_t)t; key[min(t, ntiles - 1)] = INFINITY; }
+        __syncthreads();
+    }
+}
+
+// The tiles that query tile blockIdx.x still has to meet, in row order: not among the first ones, and not farther than
+// the largest cut-off of its rows.
+__global__ __launch_bounds__(256) void tile_rest_k(const float *__restrict__ near, int ntiles, const uint16_t *__restrict__ first,
+                                                   const float *__restrict__ tau, int rows, uint16_t *__restrict__ rest,
+                                                   int *__restrict__ count)
+{
+    __shared__ float cuts[4];
+    __shared__ int wsum[4];
+    __shared__ uint16_t done[ORD_FIRST];
+    const int tid = (int)threadIdx.x, b = (int)blockIdx.x, row = b * HT + tid;
+    float cut = wave_max(row < rows ? tau[row] : -INFINITY);
+    if (lane_id() == 0) cuts[tid >> 6] = cut;
+    if (tid < ORD_FIRST) done[tid] = tid < min(ntiles, ORD_FIRST) ? first[(size_t)b * ORD_FIRST + tid] : 0xFFFFu;
+    __syncthreads();
+    cut = fmaxf(fmaxf(cuts[0], cuts[1]), fmaxf(cuts[2], cuts[3]));
+    int have = 0;
+    for (int t0 = 0; t0 < ntiles; t0 += 256) {
+        const int t = t0 + tid;
+        bool take = t < ntiles;
+        if (take) {
+            const float a = near[(size_t)b * ntiles + t];
+            take = !(a * a * (1.f - 1e-6f) >= cut);
+            for (int i = 0; i < ORD_FIRST; ++i) take = take && done[i] != (uint16_t)t;
+        }
+        const uint64_t m = __ballot(take);
+        if (lane_id() == 0) wsum[tid >> 6] = (int)__popcll(m);
+        __syncthreads();
+        int at = have + (int)__popcll(m & lanemask_lt());
+        for (int k = 0; k < 4; ++k) { if (k < (tid >> 6)) at += wsum[k]; have += wsum[k]; }
+        if (take) rest[(size_t)b * ORD_MAX_TILES + at] = (uint16_t)t;
+        __syncthreads();
+    }
+    if (tid == 0) count[b] = have;
+}
+
+// query tiles with more than `limit` tiles left to meet are not for the lists
+__global__ void tile_rest_limit_k(int *__restrict__ count, int m, int limit)
+{
+    const int t = (int)global_index();
+    if (t < m && count[t] > limit) count[t] = 0;
+}
+
 // ---- Eq. (10)-(11) for long rows on the same tiles: helpers of ivf_search_tiles() below
 // the probed lists of every row, rows in list order
 __global__ void probe_gather(const int32_t *__restrict__ probe, const int *__restrict__ lorder, int n, int tau, int nlist,
@@ -2109,6 +2385,11 @@ struct Layout {
     double *knn_d2, *cond;
     int kp, cap;
     bool high_fits;          // there is room for the half-precision sweep
+    // the search in an order of the rows (see ORD_MIN_ROWS); ord is null where n, d and k are not in its range
+    int *ord, *prow, *prank, *bcnt, *bcur, *bptr, *rest_count, *rest_most;
+    int32_t *label;
+    uint16_t *pivots, *first, *rest;
+    float *norms_p, *centre, *radius2, *near;
 };
 
 int margin_kp(int n, int k)
@@ -2117,6 +2398,9 @@ int margin_kp(int n, int k)
     if (kp > n - 1) kp = n - 1;
     return kp;
 }
+
+bool ordered_size(int n, int d);
+int pivot_count(int n);
 
 size_t carve(Layout *L, int n, int d, int k, char *base)
 {
@@ -2152,6 +2436,7 @@ size_t carve(Layout *L, int n, int d, int k, char *base)
         q = take(4); if (L) L->fail2_count = (int *)q;
         q = take(4 * (size_t)n); if (L) L->fail2_rows = (int *)q;
     }
+    if (L) L->ord = nullptr;
     if (L) {
         L->kp = kp;
         L->cap = cap;
@@ -2168,9 +2453,37 @@ size_t carve(Layout *L, int n, int d, int k, char *base)
             L->fail2_count = L->fail_count + 16;         // (a count has 256 bytes to itself)
             L->fail2_rows = L->cursor;
         }
+        if (ordered_size(n, d)) {
+            // what the search in an order of the rows needs lives there too, if it fits: some 8 n + 2.2 n + 2 MB (m and the
+            // query tiles are bounded) in 16 n k
+            const size_t m = (size_t)pivot_count(n), ntiles = ((size_t)n + HT - 1) / HT, qtiles = (qb + HT - 1) / HT;
+            const size_t dp = (size_t)(d + SLAB - 1) / SLAB * SLAB;
+            char *p = (char *)L->sort_scratch;
+            auto put = [&](size_t bytes) { char *at = p; p += up(bytes); return (void *)at; };
+            L->ord = (int *)put(4 * (size_t)n);
+            L->label = (int32_t *)put(4 * (size_t)n);
+            L->prow = (int *)put(4 * m);
+            L->prank = (int *)put(4 * m);
+            L->norms_p = (float *)put(4 * m);
+            L->bcnt = (int *)put(4 * (m + 1));
+            L->bcur = (int *)put(4 * (m + 1));
+            L->bptr = (int *)put(4 * (m + 1));
+            L->pivots = (uint16_t *)put(4 * m * dp);
+            L->centre = (float *)put(4 * ntiles * d);
+            L->radius2 = (float *)put(4 * ntiles);
+            L->near = (float *)put(4 * qtiles * ntiles);
+            L->first = (uint16_t *)put(2 * qtiles * ORD_FIRST);
+            L->rest = (uint16_t *)put(2 * qtiles * ORD_MAX_TILES);
+            L->rest_count = (int *)put(4 * qtiles);
+            L->rest_most = (int *)put(4);
+            if ((size_t)(p - (char *)L->sort_scratch) > 16 * (size_t)n * k) L->ord = nullptr;
+        }
     }
     return off;
 }
+
+bool ordered_size(int n, int d) { return d <= 2 * SLAB && n >= ORD_MIN_ROWS && n <= ORD_MAX_TILES * HT; }
+int pivot_count(int n) { return std::min(ORD_MAX_PIVOTS, std::max(16, n / 2048)); }
 
 int check_args(int32_t n, int32_t d, int32_t k)
 {
@@ -2656,10 +2969,14 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
 
     // more LDS than a kernel may use by default
     const struct { const void *kernel; size_t bytes; } lds[] = {
-        {reinterpret_cast<const void *>(&knn_tile_resident<1, false>), resident_lds_bytes(1)},
-        {reinterpret_cast<const void *>(&knn_tile_resident<1, true>), resident_lds_bytes(1)},
-        {reinterpret_cast<const void *>(&knn_tile_resident<2, false>), resident_lds_bytes(2)},
-        {reinterpret_cast<const void *>(&knn_tile_resident<2, true>), resident_lds_bytes(2)},
+        {reinterpret_cast<const void *>(&knn_tile_resident<1, false, false>), resident_lds_bytes(1)},
+        {reinterpret_cast<const void *>(&knn_tile_resident<1, true, false>), resident_lds_bytes(1)},
+        {reinterpret_cast<const void *>(&knn_tile_resident<2, false, false>), resident_lds_bytes(2)},
+        {reinterpret_cast<const void *>(&knn_tile_resident<2, true, false>), resident_lds_bytes(2)},
+        {reinterpret_cast<const void *>(&knn_tile_resident<1, false, true>), resident_lds_bytes(1)},
+        {reinterpret_cast<const void *>(&knn_tile_resident<1, true, true>), resident_lds_bytes(1)},
+        {reinterpret_cast<const void *>(&knn_tile_resident<2, false, true>), resident_lds_bytes(2)},
+        {reinterpret_cast<const void *>(&knn_tile_resident<2, true, true>), resident_lds_bytes(2)},
         {reinterpret_cast<const void *>(&knn_tile_half<false, false>), HALF_TILE_LDS},
         {reinterpret_cast<const void *>(&knn_tile_half<true, false>), HALF_TILE_LDS},
         {reinterpret_cast<const void *>(&knn_tile_half<false, true>), HALF_OWN_LDS},
@@ -2724,13 +3041,56 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
             HIPCHK(hipMemsetAsync(L.fail2_count, 0, 4, s));
         }
     }
+    // the order of the rows that the copies and the norms are in (null: the caller's)
+    const int *ord = nullptr;
     // (only where three-product tiles run: not if half precision certifies every row)
     auto split = [&]() {
-        hipLaunchKernelGGL(split_bf16, wide_grid((size_t)n * dp), dim3(256), 0, s, d_X, L.mu, n, d, dp, (const int *)nullptr, n, L.xs);
+        hipLaunchKernelGGL(split_bf16, wide_grid((size_t)n * dp), dim3(256), 0, s, d_X, L.mu, n, d, dp, ord, n, L.xs);
     };
+    if (!high_first) split();
+    const int ntiles = (n + HT - 1) / HT;
+    if (L.ord) {
+        // the nearest pivot of every row, from dense launches on the copies in the caller's order
+        const int m = pivot_count(n);
+        hipLaunchKernelGGL(sample_rows_k, dim3((m + 255) / 256), dim3(256), 0, s, L.prow, n, m);
+        hipLaunchKernelGGL(row_norms, wide_grid((size_t)m * WAVE), dim3(256), 0, s, d_X, L.mu, m, d, L.prow, n, L.norms_p);
+        hipLaunchKernelGGL(split_bf16, wide_grid((size_t)m * dp), dim3(256), 0, s, d_X, L.mu, m, d, dp, L.prow, n, L.pivots);
+        auto against_pivots = [&](const uint16_t *xq, const float *norms_q, int q0, int qend) {
+            hipLaunchKernelGGL((knn_tile_mfma<KNN_MB, false, false, true>), dim3((unsigned)((qend - q0 + 64 * KNN_MB - 1) / (64 * KNN_MB)), (unsigned)((m + TN - 1) / TN)),
+                               dim3(256), 0, s, (const uint4 *)xq, dp, q0, qend, 0, m, norms_q, L.tau, L.cnt, L.cand, cap, L.ccount,
+                               (const uint4 *)L.pivots, L.norms_p, 0, (const int *)nullptr, (const int *)nullptr, 0,
+                               (const int *)nullptr, (const int *)nullptr, (const int *)nullptr, 0);
+        };
+        hipLaunchKernelGGL(knn_reset, dim3((QB + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, n < QB ? n : QB, L.ccount);
+        against_pivots(L.pivots, L.norms_p, 0, m);
+        hipLaunchKernelGGL(pivot_apart_k, dim3(1), dim3(ORD_MAX_PIVOTS), 0, s, L.cand, cap, m, L.rest_most);
+        int apart = 0;
+        HIPCHK(hipMemcpyAsync(&apart, L.rest_most, 4, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        if (apart >= m * (m - 1) / 4) ord = L.ord;
+        if (ord) {
+            hipLaunchKernelGGL(pivot_chain_k, dim3(1), dim3(ORD_MAX_PIVOTS), 0, s, L.cand, cap, m, L.prank);
+            for (int q0 = 0; q0 < n; q0 += QB) {
+                const int rows = n - q0 < QB ? n - q0 : QB;
+                against_pivots(L.xs, L.norms, q0, q0 + rows);
+                hipLaunchKernelGGL(nearest_pivot_k, dim3((rows + 3) / 4), dim3(256), 0, s, L.cand, cap, rows, m, L.prank, L.label + q0);
+            }
+            hipLaunchKernelGGL(fill_int_k, dim3((m + 256) / 256), dim3(256), 0, s, L.bcnt, 0, m + 1);
+            hipLaunchKernelGGL(fill_int_k, dim3((m + 256) / 256), dim3(256), 0, s, L.bcur, 0, m + 1);
+            hipLaunchKernelGGL(rank_hist, wide_grid((size_t)n), dim3(256), 0, s, L.label, (const int *)nullptr, 0, n, 1, 0, L.bcnt);
+            hipLaunchKernelGGL(excl_scan_k, dim3(1), dim3(1024), 0, s, L.bcnt, m, L.bptr);
+            hipLaunchKernelGGL(rank_scatter, wide_grid((size_t)n), dim3(256), 0, s, L.label, (const int *)nullptr, 0, n, 1, 0, L.bptr, L.bcur, L.ord);
+            // the copy and the norms once more, in that order
+            hipLaunchKernelGGL(row_norms, wide_grid((size_t)n * WAVE), dim3(256), 0, s, d_X, L.mu, n, d, ord, n, L.norms);
+            split();
+            hipLaunchKernelGGL(tile_centre_k, dim3(ntiles), dim3(256), 0, s, d_X, L.mu, n, d, ord, L.centre);
+            hipLaunchKernelGGL(fill_int_k, dim3((ntiles + 255) / 256), dim3(256), 0, s, (int *)L.radius2, 0, ntiles);
+            hipLaunchKernelGGL(tile_radius_k, wide_grid((size_t)n * WAVE), dim3(256), 0, s, d_X, L.mu, n, d, ord, L.centre, (unsigned int *)L.radius2);
+            HIPCHK(hipGetLastError());
+        }
+    }
     // equal blocks of whole tiles (a short last one would leave most compute units idle)
     bool high = high_first;
-    if (!high) split();
     for (int q0 = 0; q0 < n; q0 += block) {
         const int qend = q0 + block < n ? q0 + block : n, rows = qend - q0;
         // (a workgroup per query tile: at least half of the compute units have to get one, 41,000 rows of 300 coordinates
@@ -2739,13 +3099,103 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
         // 58.3 -> 52.7, 70.7 -> 66.2, 96.3 -> 104.7 ms)
         const bool own = dph <= HALF_OWN_MAX_D && rows >= HALF_OWN_MIN_ROWS;
         hipLaunchKernelGGL(knn_reset, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, rows, L.ccount);
+        const bool resident = dp <= 2 * SLAB && rows >= RESIDENT_MIN_ROWS;
         int launch = 0;
-        for (int j0 = 0, jend; j0 < n; j0 = jend, ++launch) {
+        bool listed = ord && resident;
+        if (listed) {
+            // (as below: a compaction pass behind every second launch, whose own and the one before's appends it has room for)
+            const unsigned nqt = (unsigned)((rows + HT - 1) / HT), grid = 8 * ((nqt + 7) / 8);
+            TileLists lists = {L.first, nullptr, ORD_FIRST, std::min(ntiles, ORD_FIRST), 0, kp, L.clist, nullptr, nullptr};
+            bool dense = true;
+            auto step = [&](bool pass) {
+                int *cc = L.ccount + (launch & 1), *cc_next = L.ccount + ((launch + 1) & 1);
+                lists.ccount = cc;
+                lists.ccount_next = cc_next;
+                auto resident_tiles = [&](auto kernel, int ns) {
+                    hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), resident_lds_bytes(ns), s, (const uint4 *)L.xs, q0, qend, 0, n, L.norms,
+                                       L.tau, L.cnt, L.cand, cap, kp, 0, L.clist, cc, cc_next, lists);
+                };
+                if (dp == SLAB) { if (dense) resident_tiles(knn_tile_resident<1, true, true>, 1); else resident_tiles(knn_tile_resident<1, false, true>, 1); }
+                else { if (dense) resident_tiles(knn_tile_resident<2, true, true>, 2); else resident_tiles(knn_tile_resident<2, false, true>, 2); }
+                if (pass) compact(rows, cc, dense ? std::min(n, DBC) : 0);
+                dense = false;
+                lists.first += ORD_STEP;
+                ++launch;
+            };
+            const int qt0 = q0 / HT;
+            hipLaunchKernelGGL(tile_order_k, dim3(nqt), dim3(1024), 4 * ((size_t)d + ntiles), s, L.centre, L.radius2, ntiles, d, qt0, L.near, L.first);
+            while (lists.first < lists.all) step(true);
+            // every row's cut-off as low as it is by now
+            hipLaunchKernelGGL(fill_int_k, dim3(1), dim3(256), 0, s, L.ccount, 0, 2);
+            hipLaunchKernelGGL(knn_compact_list, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, cap, kp, rows, 1, L.clist, L.ccount);
+            compact(rows, L.ccount, 0);
+            hipLaunchKernelGGL(tile_rest_k, dim3(nqt), dim3(256), 0, s, L.near, ntiles, L.first, L.tau, rows, L.rest, L.rest_count);
+            hipLaunchKernelGGL(fill_int_k, dim3(1), dim3(256), 0, s, L.ccount, 0, 2);
+            int left[QB / HT], down[QB / HT];
+            HIPCHK(hipMemcpyAsync(left, L.rest_count, 4 * nqt, hipMemcpyDeviceToHost, s));
+            HIPCHK(hipStreamSynchronize(s));
+            // A launch takes as long as one workgroup's ORD_STEP tiles, however few workgroups still have any.  A query tile
+            // with rows of two groups can leave out hardly anything, so the few with the longest lists are better swept
+            // by themselves, over all rows: as many as make the sum smallest.
+            memcpy(down, left, 4 * nqt);
+            std::sort(down, down + nqt, std::greater<int>());
+            const int plain = (n + DBC - 1) / DBC;
+            int alone = 0, limit = 0, best = INT_MAX;
+            for (int x = 0; x < (int)nqt; ++x) {
+                if (x > 0 && down[x] == down[x - 1]) continue;
+                const int cost = ORD_LAUNCH * ((down[x] + ORD_STEP - 1) / ORD_STEP) + ORD_ALONE * x * ((n + ORD_ALONE_ROWS - 1) / ORD_ALONE_ROWS);
+                if (cost < best) { best = cost; alone = x; limit = down[x]; }
+            }
+            if (q0 == 0 && 10 * best > 7 * ORD_PLAIN * plain) {
+                // too little is left out: all rows against all, in the caller's order (in this one a query tile finds all its
+                // neighbours in the same few launches, which wait for its appends: 150,000 rows of 8 coordinates in twenty
+                // blobs 28 ms in the caller's order, 50 in this one)
+                ord = nullptr;
+                listed = false;
+                limit = alone = 0;
+                hipLaunchKernelGGL(row_norms, wide_grid((size_t)n * WAVE), dim3(256), 0, s, d_X, L.mu, n, d, ord, n, L.norms);
+                split();
+                hipLaunchKernelGGL(knn_reset, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, rows, L.ccount);
+            }
+            if (alone > 0) hipLaunchKernelGGL(tile_rest_limit_k, dim3(1), dim3(QB / HT), 0, s, L.rest_count, (int)nqt, limit);
+            for (int b = 0; b < (int)nqt && alone > 0; ++b) {
+                if (left[b] <= limit) continue;
+                const int r0 = b * HT, m = std::min(HT, rows - r0);
+                float *tau = L.tau + r0;
+                int *cnt = L.cnt + r0;
+                uint64_t *cand = L.cand + (size_t)r0 * cap;
+                // The pairs so far are dropped, their cut-offs stay: nothing at or beyond them is kept or needed.  (A buffer
+                // has room for k' pairs and ORD_ALONE_ROWS more; with four times the rows a launch those of the smaller group
+                // overflowed it, and the exact pass took 23 ms.)
+                hipLaunchKernelGGL(fill_int_k, dim3(1), dim3(256), 0, s, cnt, 0, m);
+                for (int j0 = 0; j0 < n; j0 += ORD_ALONE_ROWS) {
+                    const int jend = std::min(n, j0 + ORD_ALONE_ROWS);
+                    hipLaunchKernelGGL((knn_tile_mfma<KNN_MB, false, false, false>),
+                                       dim3((unsigned)((m + 64 * KNN_MB - 1) / (64 * KNN_MB)), (unsigned)((jend - j0 + TN - 1) / TN)), dim3(256), 0, s,
+                                       (const uint4 *)L.xs, dp, q0 + r0, q0 + r0 + m, j0, jend, L.norms, tau, cnt, cand, cap, L.ccount,
+                                       (const uint4 *)L.xs, L.norms, 1, (const int *)nullptr, (const int *)nullptr, 0,
+                                       (const int *)nullptr, (const int *)nullptr, (const int *)nullptr, 0);
+                    hipLaunchKernelGGL(knn_compact_list, dim3(1), dim3(256), 0, s, tau, cnt, cap, kp, m, 1, L.clist, L.ccount);
+                    launch_compact(tau, cnt, cand, cap, kp, m, L.clist, L.ccount, 0, s);
+                }
+            }
+            hipLaunchKernelGGL(fill_int_k, dim3(1), dim3(256), 0, s, L.ccount, 0, 2);
+            lists.tiles = L.rest;
+            lists.count = L.rest_count;
+            lists.stride = ORD_MAX_TILES;
+            lists.first = 0;
+            launch = 0;
+            while (lists.first < limit) step(launch % COMPACT_EVERY != 0);
+            hipLaunchKernelGGL(fill_int_k, dim3(1), dim3(256), 0, s, L.ccount, 0, 2);
+            hipLaunchKernelGGL(knn_compact_list, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, cap, kp, rows, 1, L.clist, L.ccount);
+            compact(rows, L.ccount, 0);
+            launch = 0;
+        }
+        for (int j0 = 0, jend; !listed && j0 < n; j0 = jend, ++launch) {
             jend = j0 + DBC < n ? j0 + DBC : n;
             const bool dense = j0 == 0;
             const int force = jend >= n ? 1 : 0;
             int *cc = L.ccount + (launch & 1), *cc_next = L.ccount + ((launch + 1) & 1);   // two lists take turns
-            const bool resident = dp <= 2 * SLAB && rows >= RESIDENT_MIN_ROWS;
             // (a row that is not listed has room for what two launches can append, so a pass over the rows follows every
             // second launch only: it costs a third of a launch after the resident kernel, and the two small kernels of a
             // pass are 8 % of the time between the half-precision sweep's; the rows stay listed)
@@ -2753,12 +3203,12 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
             if (resident) {
                 auto tiles = [&](auto kernel, int ns) {
                     hipLaunchKernelGGL(kernel, dim3((rows + RQ - 1) / RQ), dim3(512), resident_lds_bytes(ns), s, (const uint4 *)L.xs,
-                                       q0, qend, j0, jend, L.norms, L.tau, L.cnt, L.cand, cap, kp, force, L.clist, cc, cc_next);
+                                       q0, qend, j0, jend, L.norms, L.tau, L.cnt, L.cand, cap, kp, force, L.clist, cc, cc_next, TileLists{});
                 };
                 if (dp == SLAB) {
-                    if (dense) tiles(knn_tile_resident<1, true>, 1); else tiles(knn_tile_resident<1, false>, 1);
+                    if (dense) tiles(knn_tile_resident<1, true, false>, 1); else tiles(knn_tile_resident<1, false, false>, 1);
                 } else {
-                    if (dense) tiles(knn_tile_resident<2, true>, 2); else tiles(knn_tile_resident<2, false>, 2);
+                    if (dense) tiles(knn_tile_resident<2, true, false>, 2); else tiles(knn_tile_resident<2, false, false>, 2);
                 }
                 if (skip) continue;
             } else {
@@ -2780,8 +3230,8 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
             }
             compact(rows, cc, dense ? std::min(n, DBC) : 0);
         }
-        hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, d_X, n, d, (const int *)nullptr, d_X, n,
-                           (const int *)nullptr, (const int *)nullptr, (const int *)nullptr, q0, rows, k, kp, n - 1,
+        hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, d_X, n, d, ord, d_X, n,
+                           ord, ord, ord, q0, rows, k, kp, n - 1,
                            high ? tile_error_coeff(d, false, true) : tile_error_coeff(d, d > KFLUSH), high ? e_add : 0.0, L.norms, norm_max,
                            L.tau, L.cnt, L.cand, cap, L.knn_idx, L.knn_d2, high == high_first ? L.fail_count : L.fail2_count,
                            high == high_first ? L.fail_rows : L.fail2_rows);
