@@ -143,6 +143,7 @@ inline bool ft_possible(const tsne_params *p)
 hipError_t attract_far_tiled_prepare();   // once per process, before the first launch
 hipError_t rank_sort_prepare();           // likewise
 hipError_t small_tree_prepare();          // likewise
+hipError_t graph_smooth_prepare();        // likewise
 
 // inverted-file neighbour search (ivf.hip); return a tsne_error
 size_t ivf_workspace(int n, int d, int k, int nlist, int tau);
