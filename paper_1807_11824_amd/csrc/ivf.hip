@@ -71,47 +71,85 @@ __global__ void fill_u64_k(unsigned long long *__restrict__ a, size_t m)
 // again the one farthest from those taken so far (squared distance in double, lowest j among equals)
 __device__ __forceinline__ long long sample_row(int j, int n, int m) { return ((long long)j * n) / m; }
 
-// mind[j] = min(mind[j], |sample j - sample sel[c]|^2); one wave per sample row
-__global__ __launch_bounds__(256) void fps_update(const float *__restrict__ X, int n, int d, int m,
-                                                  const int *__restrict__ sel, int c, double *__restrict__ mind, int first)
+// The farthest sample row so far: its squared distance and its number (the lowest among equals; none: -1, 0).
+struct __align__(16) FpsBest {
+    double v;
+    int j, pad;
+};
+__device__ __forceinline__ FpsBest fps_better(FpsBest a, FpsBest b)
 {
-    const int j = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-    if (j >= m) return;
-    const float *x = X + (size_t)sample_row(j, n, m) * d;
-    const float *y = X + (size_t)sample_row(sel[c], n, m) * d;
-    double acc = 0.0;
-    for (int t = lane_id(); t < d; t += WAVE) {
-        const double df = (double)x[t] - (double)y[t];
-        acc = fma(df, df, acc);
+    return b.v > a.v || (b.v == a.v && b.j < a.j) ? b : a;
+}
+// of the workgroup of FPS_ROWS waves; every thread gets it
+constexpr int FPS_ROWS = 16;
+__device__ __forceinline__ FpsBest fps_block_best(FpsBest a, FpsBest *ws)
+{
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        FpsBest b;
+        b.v = __shfl_xor(a.v, o, WAVE);
+        b.j = __shfl_xor(a.j, o, WAVE);
+        b.pad = 0;
+        a = fps_better(a, b);
     }
-    acc = wave_sum(acc);
-    if (lane_id() == 0) mind[j] = first ? acc : fmin(mind[j], acc);
+    __syncthreads();
+    if (lane_id() == 0) ws[threadIdx.x >> 6] = a;
+    __syncthreads();
+    a = ws[0];
+    for (int w = 1; w < FPS_ROWS; ++w) a = fps_better(a, ws[w]);
+    return a;
 }
 
-// sel[c] = argmax_j mind[j], lowest j among equals; one workgroup
-__global__ __launch_bounds__(1024) void fps_argmax(const double *__restrict__ mind, int m, int *__restrict__ sel, int c)
+// Round c of the farthest-point start, c = 1 ..: row c - 1 is the farthest of the round before (prev: the workgroups' best;
+// row 0 for c = 1), mind[j] = min(mind[j], |sample j - it|^2), best[workgroup] = the farthest of its rows now.  A wave a
+// sample row, eight of its loads on their way; every workgroup finds the farthest row for itself, which is one launch a
+// round instead of two.  (1131 rounds over 9056 x 2048: 34.9 -> 26.6 ms.)
+__global__ __launch_bounds__(WAVE * FPS_ROWS) void fps_step(const float *__restrict__ X, int n, int d, int m, int *__restrict__ sel, int c,
+                                                            double *__restrict__ mind, const FpsBest *__restrict__ prev, int nprev,
+                                                            FpsBest *__restrict__ best)
 {
-    __shared__ double bv[1024];
-    __shared__ int bi[1024];
-    double v = -1.0;
-    int idx = 0x7FFFFFFF;
-    for (int j = threadIdx.x; j < m; j += 1024) {
-        const double w = mind[j];
-        if (w > v) { v = w; idx = j; }         // ascending j: a later equal value does not replace
+    extern __shared__ float fps_row[];          // the chosen row
+    __shared__ FpsBest ws[FPS_ROWS];
+    const int tid = (int)threadIdx.x;
+    int at = 0;
+    if (c > 1) {
+        FpsBest a = {-1.0, 0x7FFFFFFF, 0};
+        for (int i = tid; i < nprev; i += WAVE * FPS_ROWS) a = fps_better(a, prev[i]);
+        at = min(fps_block_best(a, ws).j, m - 1);
+        if (blockIdx.x == 0 && tid == 0) sel[c - 1] = at;
     }
-    bv[threadIdx.x] = v;
-    bi[threadIdx.x] = idx;
+    const float *y = X + (size_t)sample_row(at, n, m) * d;
+    for (int t = tid; t < d; t += WAVE * FPS_ROWS) fps_row[t] = y[t];
     __syncthreads();
-    for (int o = 512; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            const double w = bv[threadIdx.x + o];
-            const int wi = bi[threadIdx.x + o];
-            if (w > bv[threadIdx.x] || (w == bv[threadIdx.x] && wi < bi[threadIdx.x])) { bv[threadIdx.x] = w; bi[threadIdx.x] = wi; }
+    const int j = (int)blockIdx.x * FPS_ROWS + (tid >> 6);
+    FpsBest mine = {-1.0, 0x7FFFFFFF, 0};
+    if (j < m) {
+        const float *x = X + (size_t)sample_row(j, n, m) * d;
+        double acc = 0.0;
+#pragma unroll 8
+        for (int t = lane_id(); t < d; t += WAVE) {
+            const double df = (double)x[t] - (double)fps_row[t];
+            acc = fma(df, df, acc);
         }
-        __syncthreads();
+        acc = wave_sum(acc);
+        const double v = c == 1 ? acc : fmin(mind[j], acc);
+        if (lane_id() == 0) mind[j] = v;
+        if (v > -1.0) { mine.v = v; mine.j = j; }           // (not: no number)
     }
-    if (threadIdx.x == 0) sel[c] = bi[0];
+    mine = fps_block_best(mine, ws);
+    if (tid == 0) best[blockIdx.x] = mine;
 }
+
+// the last choice
+__global__ __launch_bounds__(WAVE * FPS_ROWS) void fps_last(const FpsBest *__restrict__ best, int nbest, int m, int *__restrict__ sel, int c)
+{
+    __shared__ FpsBest ws[FPS_ROWS];
+    FpsBest a = {-1.0, 0x7FFFFFFF, 0};
+    for (int i = (int)threadIdx.x; i < nbest; i += WAVE * FPS_ROWS) a = fps_better(a, best[i]);
+    a = fps_block_best(a, ws);
+    if (threadIdx.x == 0) sel[c] = min(a.j, m - 1);
+}
+
 
 __global__ void fps_gather(const float *__restrict__ X, int n, int d, int m, int nlist, const int *__restrict__ sel,
                            float *__restrict__ C)
@@ -873,6 +911,7 @@ struct IvfLayout {
     unsigned long long *sums;
     unsigned int *maxabs;
     double *mind;
+    FpsBest *best;
     int *sel;
     void *tiles_ws;          // workspace of the matrix-core search (long rows, flat second stage)
     size_t tiles_bytes;
@@ -908,6 +947,7 @@ size_t ivf_carve(IvfLayout *L, int n, int d, int nlist, int tau, char *base, siz
     q = take(8 * (size_t)nlist * d); if (L) L->sums = (unsigned long long *)q;
     q = take(4); if (L) L->maxabs = (unsigned int *)q;
     q = take(8 * 8 * (size_t)nlist); if (L) L->mind = (double *)q;
+    q = take(2 * sizeof(FpsBest) * (8 * (size_t)nlist / FPS_ROWS + 1)); if (L) L->best = (FpsBest *)q;
     q = take(4 * (size_t)nlist); if (L) L->sel = (int *)q;
     {
         const size_t tb = k_tiles >= 0 && d > TILES_MIN_D ? ivf_tiles_workspace(n, d, k_tiles, nlist, tau) : 0;
@@ -951,10 +991,12 @@ int ivf_train_device(const float *X, int n, int d, int nlist, int iters, float *
     {
         const int m = (long long)n < 8ll * nlist ? n : 8 * nlist;
         hipLaunchKernelGGL(fill_i32_k, dim3(1), dim3(256), 0, s, L.sel, 0, (size_t)1);       // the first sample row
-        for (int c = 1; c < nlist; ++c) {
-            hipLaunchKernelGGL(fps_update, dim3((m + 3) / 4), dim3(256), 0, s, X, n, d, m, L.sel, c - 1, L.mind, c == 1 ? 1 : 0);
-            hipLaunchKernelGGL(fps_argmax, dim3(1), dim3(1024), 0, s, L.mind, m, L.sel, c);
-        }
+        const int nb = (m + FPS_ROWS - 1) / FPS_ROWS;
+        for (int c = 1; c < nlist; ++c)
+            hipLaunchKernelGGL(fps_step, dim3(nb), dim3(WAVE * FPS_ROWS), 4 * (size_t)d, s, X, n, d, m, L.sel, c, L.mind,
+                               L.best + (size_t)(c & 1) * nb, nb, L.best + (size_t)((c + 1) & 1) * nb);
+        if (nlist > 1)
+            hipLaunchKernelGGL(fps_last, dim3(1), dim3(WAVE * FPS_ROWS), 0, s, L.best + (size_t)(nlist & 1) * nb, nb, m, L.sel, nlist - 1);
         hipLaunchKernelGGL(fps_gather, (blocks(cd)), dim3(256), 0, s, X, n, d, m, nlist, L.sel, C);
     }
     IVFCHK(hipMemsetAsync(L.maxabs, 0, 4, s));
