@@ -672,8 +672,21 @@ __device__ __forceinline__ bool compaction_due(int c, float cut, int cap, int kp
     const int cc = min(c, cap);
     return cc >= kp && (!(cut < INFINITY) || cc >= kp + COMPACT_SLACK || cc + COMPACT_EVERY * DBC > cap);
 }
+// The workgroup puts its rows with `due` on a list whose length is *count, with one atomic operation.  (One a wave: the
+// thousand of a launch queue up at the counter: a build of 400,000 x 300 186 -> 181 ms, of 100,000 x 100 16.3 -> 15.9.)
+// slot: two ints in LDS that nobody uses any more; all threads call.
+__device__ __forceinline__ void list_rows(bool due, int row, int *list, int *count, int *slot)
+{
+    if (threadIdx.x == 0) slot[0] = 0;
+    __syncthreads();
+    const int at = due ? atomicAdd(&slot[0], 1) : 0;
+    __syncthreads();
+    if (threadIdx.x == 0 && slot[0] > 0) slot[1] = atomicAdd(count, slot[0]);
+    __syncthreads();
+    if (due) list[slot[1] + at] = row;      // any order
+}
 // where a kernel that has the counts of its rows lists those (their number: the launch's ccount); two lists take turns, `next`
-// is the other one's number.  force: also rows with no more than k' and some pairs
+// is the other one's number.  force: also rows with no more than k' and some pairs.  list: null if no pass follows
 struct DueRows {
     int *list, *next;
     int kp, force;
@@ -929,16 +942,17 @@ __device__ __forceinline__ void half_tiles(const uint4 *Xh, int dph, int q0, int
     }
     __syncthreads();            // (the epilogue reuses the buffers)
     if (OWN) {
-        for (int t = tid; t < HT; t += HALF_THREADS) {
-            if (!GATHER && qa + t < qend) {
-                // (by the rule of knn_compact_list, whose launch behind every second one this saves: builds of 50,000 x 784 and
-                // 60,000 x 300 10.91 -> 10.80 and 8.70 -> 8.59 ms, of 400,000 x 300 no difference)
-                const int c = own_c[t];
-                cnt[qa + t - q0] = c;
-                if (compaction_due(c, own_d[t], cap, due.kp) || (due.force && min(c, cap) >= due.kp))
-                    due.list[atomicAdd(ccount, 1)] = qa + t - q0;      // any order
-            }
-            if (GATHER && t < nq) cnt[own_q[t]] = dense ? jend - j0 : own_c[t];
+        static_assert(HALF_THREADS >= HT, "a thread a row");
+        if (GATHER) {
+            if (tid < nq) cnt[own_q[tid]] = dense ? jend - j0 : own_c[tid];
+        } else {
+            // (by the rule of knn_compact_list, whose launch behind every second one this saves)
+            const bool in = tid < HT && qa + tid < qend;
+            const int c = in ? own_c[tid] : 0;
+            if (in) cnt[qa + tid - q0] = c;
+            if (due.list)
+                list_rows(in && (compaction_due(c, own_d[min(tid, HT - 1)], cap, due.kp) || (due.force && min(c, cap) >= due.kp)),
+                          qa + tid - q0, due.list, ccount, reinterpret_cast<int *>(own_n));
         }
         return;
     }
@@ -1273,15 +1287,13 @@ __global__ __launch_bounds__(512, 1) void knn_tile_resident(const uint4 *__restr
     lds_barrier();
     // the fill counts go back, and the rows whose buffers are due for compaction go on the list (the
     // rule of knn_compact_list, which this kernel makes unnecessary)
-    for (int t = tid; t < RQ; t += 512) {
-        const int q = qa + t;
-        if (q < qend) {
-            const int c = DENSE ? (ORDER ? nmine * HT : jend - j0) : qc[t];
-            cnt[q - q0] = c;
-            if (compaction_due(c, qd[t], cap, kp) || (force && min(c, cap) >= kp))
-                clist[atomicAdd(ccount, 1)] = q - q0;    // any order
-        }
-    }
+    const int q = qa + tid;
+    const bool in = tid < RQ && q < qend;
+    const int c = !in ? 0 : DENSE ? (ORDER ? nmine * HT : jend - j0) : qc[tid];
+    if (in) cnt[q - q0] = c;
+    if (clist)                  // (null: no pass follows)
+        list_rows(in && (compaction_due(c, qd[min(tid, RQ - 1)], cap, kp) || (force && min(c, cap) >= kp)), q - q0, clist, ccount,
+                  reinterpret_cast<int *>(qn));
 }
 
 // Which rows of the query block need their candidates compacted now (one thread per row; the
@@ -3128,7 +3140,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
                 lists.ccount_next = cc_next;
                 auto resident_tiles = [&](auto kernel, int ns) {
                     hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), resident_lds_bytes(ns), s, (const uint4 *)L.xs, q0, qend, 0, n, L.norms,
-                                       L.tau, L.cnt, L.cand, cap, kp, 0, L.clist, cc, cc_next, lists);
+                                       L.tau, L.cnt, L.cand, cap, kp, 0, pass ? L.clist : nullptr, cc, cc_next, lists);
                 };
                 if (dp == SLAB) { if (dense) resident_tiles(knn_tile_resident<1, true, true>, 1); else resident_tiles(knn_tile_resident<1, false, true>, 1); }
                 else { if (dense) resident_tiles(knn_tile_resident<2, true, true>, 2); else resident_tiles(knn_tile_resident<2, false, true>, 2); }
@@ -3218,7 +3230,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
             if (resident) {
                 auto tiles = [&](auto kernel, int ns) {
                     hipLaunchKernelGGL(kernel, dim3((rows + RQ - 1) / RQ), dim3(512), resident_lds_bytes(ns), s, (const uint4 *)L.xs,
-                                       q0, qend, j0, jend, L.norms, L.tau, L.cnt, L.cand, cap, kp, force, L.clist, cc, cc_next, TileLists{});
+                                       q0, qend, j0, jend, L.norms, L.tau, L.cnt, L.cand, cap, kp, force, skip ? nullptr : L.clist, cc, cc_next, TileLists{});
                 };
                 if (dp == SLAB) {
                     if (dense) tiles(knn_tile_resident<1, true, false>, 1); else tiles(knn_tile_resident<1, false, false>, 1);
@@ -3231,7 +3243,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
                     const unsigned nqt = (unsigned)((rows + HT - 1) / HT), njt = (unsigned)((jend - j0 + HT - 1) / HT);
                     auto tiles = [&](auto kernel, unsigned grid, size_t lds_bytes) {
                         hipLaunchKernelGGL(kernel, dim3(grid), dim3(HALF_THREADS), lds_bytes, s, (const uint4 *)L.xh, dph, q0, qend,
-                                           j0, jend, L.norms, L.tau, L.cnt, L.cand, cap, cc, dot_scale, DueRows{L.clist, cc_next, kp, force});
+                                           j0, jend, L.norms, L.tau, L.cnt, L.cand, cap, cc, dot_scale, DueRows{skip ? nullptr : L.clist, cc_next, kp, force});
                     };
                     if (dense) tiles(knn_tile_half<true, false>, 8 * ((nqt + 7) / 8) * njt, HALF_TILE_LDS);
                     else if (own) tiles(knn_tile_half<false, true>, nqt, HALF_OWN_LDS);
