@@ -1482,7 +1482,8 @@ __global__ __launch_bounds__(256) void knn_rerank(const float *__restrict__ X, i
                                                   const float *__restrict__ tau, const int *__restrict__ cnt,
                                                   const uint64_t *__restrict__ cand, int cap,
                                                   int32_t *__restrict__ knn_idx, double *__restrict__ knn_d2,
-                                                  int *__restrict__ fail_count, int *__restrict__ fail_rows)
+                                                  int *__restrict__ fail_count, int *__restrict__ fail_rows,
+                                                  const int *__restrict__ sched)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     float *xi = reinterpret_cast<float *>(smem);                       // d floats
@@ -1493,8 +1494,9 @@ __global__ __launch_bounds__(256) void knn_rerank(const float *__restrict__ X, i
     int *shared = cid + kp;              // candidates left; the k-th smallest tile distance
     // (the grid is 8 x ceil(rows / 8) workgroups, which go to the eight XCDs in turn)
     const int per = (rows + 7) / 8;
-    const int row = (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3);
-    if (row >= rows || (int)(blockIdx.x >> 3) >= per) return;
+    const int turn = (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3);
+    if (turn >= rows || (int)(blockIdx.x >> 3) >= per) return;
+    const int row = sched ? min(max(sched[turn], 0), rows - 1) : turn;
     const int i = q0 + row;
     const int c_all = min(cnt[row], kp);
     const int iu = min(max(qmap ? qmap[i] : i, 0), nx - 1);
@@ -2019,6 +2021,56 @@ __global__ void d2_to_float(const double *__restrict__ in, float *__restrict__ o
 {
     size_t i = global_index();
     if (i < m) out[i] = (float)in[i];
+}
+
+// ---- the order in which the rows of a block are re-ranked
+// A row's re-rank reads about k' whole rows.  Where X is larger than the second-level caches, rows that are re-ranked at
+// the same time should be near each other, so that they find each other's candidates there: they go by the nearest of the
+// first SCHED_PIVOTS rows, whose distances the first launch leaves at the first places of every buffer.
+// (60,000 x 784: the re-rank 2.63 -> 1.76 ms, the build 13.4 -> 12.5; 100,000 x 784 31.8 -> 30.1.  Rows of 300 coordinates
+// gain nothing: 60,000 8.71 -> 8.80 ms, 400,000 179.5 -> 179.7.)
+constexpr int SCHED_PIVOTS = WAVE, SCHED_ROWS = 256, SCHED_MIN_D = 512, SCHED_MIN_ROWS = 8192;
+constexpr size_t SCHED_MIN_BYTES = 32u << 20;       // (eight caches of 4 MB)
+// label[row] = the nearest of these, and how many rows each has; a wave a row
+__global__ __launch_bounds__(256) void rerank_label_k(const uint64_t *__restrict__ cand, int cap, int rows, int *__restrict__ label,
+                                                      int *__restrict__ total)
+{
+    __shared__ int hist[SCHED_PIVOTS];
+    const int tid = (int)threadIdx.x, r0 = (int)blockIdx.x * SCHED_ROWS;
+    if (tid < SCHED_PIVOTS) hist[tid] = 0;
+    __syncthreads();
+    for (int t = tid >> 6; t < SCHED_ROWS && r0 + t < rows; t += 4) {
+        uint64_t best = cand[(size_t)(r0 + t) * cap + lane_id()];
+#pragma unroll
+        for (int o = WAVE / 2; o > 0; o >>= 1) best = min(best, (uint64_t)__shfl_xor((unsigned long long)best, o, WAVE));
+        if (lane_id() == 0) {
+            const int l = (int)((uint32_t)best % SCHED_PIVOTS);         // (NO_PAIR everywhere: the last)
+            label[r0 + t] = l;
+            atomicAdd(&hist[l], 1);
+        }
+    }
+    __syncthreads();
+    if (tid < SCHED_PIVOTS && hist[tid] > 0) atomicAdd(&total[tid], hist[tid]);
+}
+
+// sched = the rows by label; taken[label] (zero on entry): how many places workgroups have taken so far
+__global__ __launch_bounds__(SCHED_ROWS) void rerank_sched_k(const int *__restrict__ label, int rows, const int *__restrict__ total,
+                                                             int *__restrict__ taken, int *__restrict__ sched)
+{
+    __shared__ int hist[SCHED_PIVOTS], base[SCHED_PIVOTS];
+    const int tid = (int)threadIdx.x, row = (int)blockIdx.x * SCHED_ROWS + tid;
+    if (tid < SCHED_PIVOTS) hist[tid] = 0;
+    __syncthreads();
+    const int l = row < rows ? label[row] % SCHED_PIVOTS : 0;
+    const int at = row < rows ? atomicAdd(&hist[l], 1) : 0;
+    __syncthreads();
+    if (tid < SCHED_PIVOTS) {
+        int before = 0;
+        for (int k = 0; k < tid; ++k) before += total[k];
+        base[tid] = before + (hist[tid] > 0 ? atomicAdd(&taken[tid], hist[tid]) : 0);
+    }
+    __syncthreads();
+    if (row < rows) sched[min(base[l] + at, rows - 1)] = row;
 }
 
 // ---- the exact search in an order of the rows that keeps neighbours together
@@ -2671,7 +2723,7 @@ int ivf_search_tiles(const float *X, int n, int d, int k, int nlist, int tau, co
                            qmap ? (const int *)L.xrow : lorder, X, n, lorder, qmap ? (const int *)L.xrow : lorder, qmap, q0, rows, k, kp,
                            0x7FFFFFFF, half ? tile_error_coeff(d, false, true) : tile_error_coeff(d, true), half ? hs.e_add : 0.0,
                            qmap ? (const float *)L.norms_f : L.norms, norm_max, L.tau, L.cnt, L.cand, cap, knn_idx, knn_d2, fail_count,
-                           fail_rows);
+                           fail_rows, (const int *)nullptr);
     };
     bool half = half_first;
     if (!half) split();
@@ -2879,7 +2931,7 @@ int ivf_probe_tiles(const float *X, int n, int d, const float *C, int nlist, int
         hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, X, n, d, qmap, C, nlist, (const int *)nullptr,
                            omap, omap, q0, rows, tau, kp, nlist, half ? tile_error_coeff(d, false, true) : tile_error_coeff(d, d > KFLUSH),
                            half ? hs.e_add : 0.0, norms, norm_max, L.tau, L.cnt, L.cand, cap, probe,
-                           (double *)nullptr, fail_count, fail_rows);
+                           (double *)nullptr, fail_count, fail_rows, (const int *)nullptr);
     };
     for (int q0 = 0; q0 < m; q0 += TS_ROWS)
         pass(half, q0, m - q0 < TS_ROWS ? m - q0 : TS_ROWS, rowmap, L.norms_q, nullptr, L.fail_count, L.fail_rows);
@@ -3118,6 +3170,9 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
     }
     // equal blocks of whole tiles (a short last one would leave most compute units idle)
     bool high = high_first;
+    // (the order and its counts are where the conditional P goes later, the labels where the re-rank writes a block's distances)
+    const bool grouped = high_first && d >= SCHED_MIN_D && 4 * (size_t)n * d > SCHED_MIN_BYTES;
+    int *sched_of = (int *)L.cond, *total = sched_of + std::min(n, QB);
     for (int q0 = 0; q0 < n; q0 += block) {
         const int qend = q0 + block < n ? q0 + block : n, rows = qend - q0;
         // (a workgroup per query tile: at least half of the compute units have to get one, 41,000 rows of 300 coordinates
@@ -3127,6 +3182,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
         const bool own = dph <= HALF_OWN_MAX_D && rows >= HALF_OWN_MIN_ROWS;
         hipLaunchKernelGGL(knn_reset, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, rows, L.ccount);
         const bool resident = dp <= 2 * SLAB && rows >= RESIDENT_MIN_ROWS;
+        const int *sched = nullptr;
         int launch = 0;
         bool listed = ord && resident;
         if (listed) {
@@ -3248,6 +3304,14 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
                     if (dense) tiles(knn_tile_half<true, false>, 8 * ((nqt + 7) / 8) * njt, HALF_TILE_LDS);
                     else if (own) tiles(knn_tile_half<false, true>, nqt, HALF_OWN_LDS);
                     else tiles(knn_tile_half<false, false>, 8 * ((nqt + 7) / 8) * njt, HALF_TILE_LDS);
+                    if (dense && grouped && rows >= SCHED_MIN_ROWS) {
+                        const unsigned nb = (unsigned)((rows + SCHED_ROWS - 1) / SCHED_ROWS);
+                        int *label = (int *)(L.knn_d2 + (size_t)q0 * k);
+                        hipLaunchKernelGGL(fill_int_k, dim3(1), dim3(256), 0, s, total, 0, 2 * SCHED_PIVOTS);
+                        hipLaunchKernelGGL(rerank_label_k, dim3(nb), dim3(256), 0, s, L.cand, cap, rows, label, total);
+                        hipLaunchKernelGGL(rerank_sched_k, dim3(nb), dim3(SCHED_ROWS), 0, s, label, rows, total, total + SCHED_PIVOTS, sched_of);
+                        sched = sched_of;
+                    }
                 } else {
                     mfma_tiles(L.xs, L.norms, q0, qend, j0, jend, nullptr, cc);
                 }
@@ -3262,7 +3326,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
                            ord, ord, ord, q0, rows, k, kp, n - 1,
                            high ? tile_error_coeff(d, false, true) : tile_error_coeff(d, d > KFLUSH), high ? e_add : 0.0, L.norms, norm_max,
                            L.tau, L.cnt, L.cand, cap, L.knn_idx, L.knn_d2, high == high_first ? L.fail_count : L.fail2_count,
-                           high == high_first ? L.fail_rows : L.fail2_rows);
+                           high == high_first ? L.fail_rows : L.fail2_rows, sched);
         HIPCHK(hipGetLastError());
         if (high && q0 == 0 && qend < n) {
             // half precision that certifies less than half of the first block's rows is no use for the others (whose rows
@@ -3298,7 +3362,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
             }
             hipLaunchKernelGGL(knn_rerank, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(256), rerank_smem, s, d_X, n, d, fr, d_X, n, (const int *)nullptr, fr, fr,
                                0, rows, k, kp, n - 1, tile_error_coeff(d, true), 0.0, L.norms_f, norm_max, L.tau, L.cnt, L.cand, cap,
-                               L.knn_idx, L.knn_d2, L.fail2_count, L.fail2_rows);
+                               L.knn_idx, L.knn_d2, L.fail2_count, L.fail2_rows, (const int *)nullptr);
             HIPCHK(hipGetLastError());
         }
         HIPCHK(hipMemcpyAsync(&nfail, L.fail2_count, 4, hipMemcpyDeviceToHost, s));
