@@ -162,9 +162,20 @@ __global__ void fps_gather(const float *__restrict__ X, int n, int d, int m, int
 
 __global__ void max_abs_k(const float *__restrict__ X, size_t m, unsigned int *__restrict__ out)
 {
+    // (16 bytes a load, four on their way: 1,281,167 x 2048 4.5 -> 2.0 ms)
+    const size_t id = global_index(), step = (size_t)gridDim.x * blockDim.x;
+    const size_t lead = min(m, (size_t)((16u - (uint32_t)(reinterpret_cast<uintptr_t>(X) & 15u)) & 15u) / 4), m4 = (m - lead) / 4;
+    const float4 *X4 = reinterpret_cast<const float4 *>(X + lead);
+    auto most = [](float4 q) { return fmaxf(fmaxf(fabsf(q.x), fabsf(q.y)), fmaxf(fabsf(q.z), fabsf(q.w))); };
     float v = 0.f;
-    for (size_t i = global_index(); i < m; i += (size_t)gridDim.x * blockDim.x)
-        v = fmaxf(v, fabsf(X[i]));
+    size_t i = id;
+    for (; i + 3 * step < m4; i += 4 * step) {
+        const float4 a = X4[i], b = X4[i + step], c = X4[i + 2 * step], d = X4[i + 3 * step];
+        v = fmaxf(v, fmaxf(fmaxf(most(a), most(b)), fmaxf(most(c), most(d))));
+    }
+    for (; i < m4; i += step) v = fmaxf(v, most(X4[i]));
+    for (i = id; i < lead; i += step) v = fmaxf(v, fabsf(X[i]));
+    for (i = lead + 4 * m4 + id; i < m; i += step) v = fmaxf(v, fabsf(X[i]));
     v = wave_max(v);
     if (lane_id() == 0) atomicMax(out, __float_as_uint(v));   // non-negative floats order like their bits
 }
