@@ -69,7 +69,8 @@ typedef struct {
     int32_t leaf_cap;             /* a cell with at most this many points is a leaf, >= 1 (8) */
     int32_t overlap;              /* 1: the attractive forces run on a second stream, the entries far from the
                                      diagonal beside the tree build and the streaming part beside the tree walk;
-                                     0: everything on one stream.  (1) */
+                                     0: everything on one stream.  (1)  Up to 65,536 points the two share one
+                                     launch either way, except with the far entries in tiles. */
     int32_t graph_order_iters;    /* > 0 (and max_nnz > 0): at tsne_set_P the library renumbers its private
                                      copy of the points and of P so that points that are neighbours in P get
                                      nearby numbers: a seeded pseudo-random value per point is averaged over
@@ -313,7 +314,7 @@ int tsne_kl_static(const float *d_Y, int32_t n, const int32_t *d_row_ptr, const 
  *   ms[0] tree build (Sec. III-C steps 1-4)   ms[1] walk + Z (step 5)
  *   ms[2] attractive forces (Eq. (5))         ms[3] update (Alg. 1 line 8)
  * With overlap on the attractive kernel runs beside other phases, so the four do not add up
- * to the step time.
+ * to the step time.  Up to 65,536 points it shares the walk's launch and ms[1] holds both.
  */
 int tsne_timing_begin(tsne_ctx *ctx, int32_t max_steps);
 /* The same, timing only every `every`-th step (the first one included) until max_steps steps have
