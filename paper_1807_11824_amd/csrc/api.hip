@@ -49,7 +49,6 @@ size_t carve(tsne_ctx *c, const tsne_params *p, char *base)
     q = take(sizeof(uint32_t));                      if (c) c->ncells = (uint32_t *)q;
     for (int k = 0; k < 2; ++k) { q = take(8 * n); if (c) c->words[k] = (uint64_t *)q; }
     q = take(4 * n);                                 if (c) c->perm = (uint32_t *)q;
-    q = take(4 * n);                                 if (c) c->row_order = (uint32_t *)q;
     q = take(4 * (size_t)RADIX * nblk_sort);         if (c) c->hist = (uint32_t *)q;
     q = take(4 * (size_t)RADIX);                     if (c) c->dtot = (uint32_t *)q;
     q = take(8 * n);                                 if (c) c->Ys = (float2 *)q;
@@ -212,10 +211,6 @@ int enqueue_forces(tsne_ctx *c, const float *d_Y, hipEvent_t *ev, bool cached, b
     } else {
         if ((rc = farpart()) != TSNE_OK || (rc = mainpart()) != TSNE_OK) return rc;
     }
-    // Without renumbering, the attractive kernel of the NEXT call visits rows in this call's
-    // spatial order (the kernel has finished by then on either stream, so the next tree build is free to
-    // overwrite the array it used).  With renumbering the slots themselves are ordered and rows go in slot order.
-    if (!c->reorder_on) std::swap(c->row_order, c->perm);
     c->tree_valid = 1;
     return TSNE_OK;
 }
@@ -228,8 +223,7 @@ int reset_slot_order(tsne_ctx *c)
     hipError_t e;
     if ((e = launch_scatter2(c->uYb[a], c->orig[a], c->uYb[b], n, c->stream)) != hipSuccess ||
         (e = launch_scatter2(c->gainsb[a], c->orig[a], c->gainsb[b], n, c->stream)) != hipSuccess ||
-        (e = launch_iota(c->orig[b], n, c->stream)) != hipSuccess ||
-        (e = launch_iota(c->row_order, n, c->stream)) != hipSuccess)
+        (e = launch_iota(c->orig[b], n, c->stream)) != hipSuccess)
         return fail_hip(c, e, "reset slot order");
     c->cur_state = b;
     c->identity = 1;
@@ -343,7 +337,6 @@ int tsne_create(tsne_ctx **out, const tsne_params *p, void *stream, void *d_work
     if ((e = hipMemsetAsync(c->status, 0, sizeof(uint32_t), c->stream)) != hipSuccess ||
         (e = hipMemsetAsync(c->ncells, 0, sizeof(uint32_t), c->stream)) != hipSuccess ||
         (e = launch_fill_state(c, c->stream)) != hipSuccess ||
-        (e = launch_iota(c->row_order, p->n, c->stream)) != hipSuccess ||
         (e = launch_iota(c->orig[0], p->n, c->stream)) != hipSuccess) {
         tsne_destroy(c);
         return TSNE_EHIP;

@@ -11,10 +11,10 @@
 // are combined with xor-shuffles inside the LPR-lane group.  No atomics: the result is
 // deterministic.
 //
-// Rows are visited in the order given by `order` (the spatial order of an earlier tree build):
-// rows that are close in the embedding share most of their neighbours, so the y_j gathers of
-// one workgroup and its neighbours on the chip keep hitting the same cache lines.  The result
-// of a row does not depend on when it is computed.
+// Rows are visited in the order given by `order`, the spatial order of the tree that was built for this Y: rows that are
+// close in the embedding share most of their neighbours, so the y_j gathers of one workgroup and its neighbours on the
+// chip keep hitting the same cache lines.  The result of a row does not depend on when it is computed.  (Of this call's
+// tree, not an earlier call's: every call writes the order before it reads it, also when it is captured and replayed.)
 // The kernel is bound by memory latency unless every lane keeps several independent loads in
 // flight: each pass of a lane covers U entries (stride LPR), issues their y_j gathers together,
 // then does the arithmetic.
@@ -497,7 +497,7 @@ hipError_t launch_attract_main(tsne_ctx *c, hipStream_t s, bool tiles)
     } else {
         const unsigned blocks = (unsigned)(((int64_t)n * AW_LPR + 255) / 256);
         hipLaunchKernelGGL((attract_csr<AW_LPR, AW_U>), dim3(blocks), dim3(256), 0, s, c->user_row_ptr, c->user_col,
-                           c->user_val, c->Yi, n, c->row_order, c->A);
+                           c->user_val, c->Yi, n, c->perm, c->A);
     }
     return hipGetLastError();
 }

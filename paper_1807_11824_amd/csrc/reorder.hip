@@ -367,8 +367,6 @@ hipError_t launch_reorder(tsne_ctx *c, hipStream_t s, int tiles_mode)
         hipLaunchKernelGGL(ft_sort_k, dim3((unsigned)std::min<int64_t>(c->ft_tiles, 1 << 20)), dim3(256), 0, s, c->ft_ptr,
                            c->ft_tiles, c->ft_nct, c->ft_col, c->ft_row, c->ft_val, c->ft_meta);
     }
-    hipError_t e = launch_iota(c->row_order, n, s);
-    if (e != hipSuccess) return e;
     c->cur_state = b;
     c->arow_valid = 0;
     c->identity = 0;

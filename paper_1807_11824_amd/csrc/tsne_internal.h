@@ -108,7 +108,6 @@ struct tsne_ctx {
     uint32_t *perm;      // spatial order: position p holds slot perm[p] (written with the sorted points)
     int32_t *arow;              // first row of each resident workgroup of the attraction kernel (+ end)
     int arow_valid;             // arow matches the current near part
-    uint32_t *row_order; // order in which the attractive kernel visits the rows (an earlier spatial order)
     uint32_t *hist, *dtot;
     float2 *Ys;
     uint16_t *lev;
