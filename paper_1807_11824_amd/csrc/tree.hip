@@ -1054,7 +1054,7 @@ __global__ __launch_bounds__(SMALL_TREE_THREADS) void small_tree(const float2 *_
                                                                  int ks, int n, int B, int C, float2 *__restrict__ Ys,
                                                                  uint32_t *__restrict__ perm, Cell *__restrict__ cells,
                                                                  uint32_t cap_cells, uint32_t *__restrict__ ncells,
-                                                                 uint32_t *status)
+                                                                 uint32_t *__restrict__ counters, uint32_t *status)
 {
     constexpr int MARGIN = SMALL_TREE_MARGIN, NW = SMALL_TREE_THREADS / WAVE;
     extern __shared__ __align__(16) unsigned char tree_lds[];
@@ -1068,6 +1068,7 @@ __global__ __launch_bounds__(SMALL_TREE_THREADS) void small_tree(const float2 *_
     __shared__ uint32_t wc[NW];
     const int tid = (int)threadIdx.x, w = tid >> 6, tile = tid / LEVEL_THREADS, tt = tid % LEVEL_THREADS;
     const int p0 = tid * LEVEL_ITEMS;
+    if (tid < 1 + WALK_COUNTERS) counters[tid] = 0u;     // as gather_levels does: a resident walk counts from zero
     {
         double gx = 0.0, gy = 0.0;
 #pragma unroll
@@ -1447,7 +1448,7 @@ hipError_t launch_tree_cells(tsne_ctx *c, hipStream_t s)
     const uint64_t *words = c->words[c->sorted_buf];
     if (n <= SMALL_TREE_MAX && C <= LEVELS_WINDOW_MAXC) {
         hipLaunchKernelGGL(C == 8 ? small_tree<8> : small_tree<0>, dim3(1), dim3(SMALL_TREE_THREADS), small_tree_lds(n), s, Y,
-                           words, ks, n, B, C, c->Ys, c->perm, c->cells, (uint32_t)c->cap_cells, c->ncells, c->status);
+                           words, ks, n, B, C, c->Ys, c->perm, c->cells, (uint32_t)c->cap_cells, c->ncells, c->big_count, c->status);
         return hipGetLastError();
     }
     int nl = (n + LEVEL_TILE - 1) / LEVEL_TILE;

@@ -50,3 +50,22 @@ def test_forces_and_one_step(n, renumber):
     assert ts.status() == 0
     assert np.abs(Yd.cpu().numpy() - (Y + move)).max() <= 1e-5 * np.abs(move).max() + 2.0 ** -23 * np.abs(Y + move).max()
     ts.close()
+
+
+@pytest.mark.parametrize("n,leaf_cap", [(1, 8), (700, 8), (4096, 1), (4096, 16)])
+def test_counters_start_at_zero(n, leaf_cap, monkeypatch):
+    """Every tree build zeroes the count of large cells and the sixteen counters of a resident walk.  With few points no walk
+    of a whole chip is resident, so they are looked for in the workspace, which holds nothing but ones before: seventeen
+    zero words and the padding behind them."""
+    import torch
+    from paper_1807_11824_amd import Tsne
+    real = torch.empty
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: real(*a, **k).fill_(255) if k.get("dtype") == torch.uint8 else real(*a, **k))
+    ts = Tsne(n, leaf_cap=leaf_cap)
+    Y = torch.from_numpy(synth.clustered_embedding(n, n_clusters=min(n, 9), seed=n)).to("cuda:0")
+    rp = torch.zeros(n + 1, dtype=torch.int32, device="cuda:0")
+    ts.set_P(rp, torch.zeros(1, dtype=torch.int32, device="cuda:0")[:0], torch.zeros(1, device="cuda:0")[:0])
+    ts.gradient(Y)
+    words = ts.workspace[:ts.workspace.numel() // 256 * 256].cpu().numpy().view(np.int32).reshape(-1, 64)
+    assert ((words[:, :17] == 0).all(axis=1) & (words[:, 17:] == -1).all(axis=1)).sum() == 1
+    ts.close()
