@@ -5,7 +5,7 @@
 //   bbox_partial / bbox_final   step 1   min/max reduction -> root square (power-of-two side)
 //   morton_encode_hist          step 2a  grid coordinates (up to 24 bits per axis), bit-interleaved key
 //   radix_hist / _scan / _scatter  step 4  stable LSD radix sort, 11 bits a pass
-//   rank_tiles / _samples / _merge  steps 1, 2a, 4 by counting smaller keys, for up to 131,072 points
+//   rank_tiles / _samples / _merge  steps 1, 2a, 4 by counting smaller keys, for up to 131,072 points (122,880 not renumbered)
 //   gather_levels               step 2b  which cells start at each sorted position
 //   downsweep                   step 3   prefix sums: cell numbering and running coordinate sums
 //   write_cells                 steps 2c+3  cell records: members, count, centre of mass, children
@@ -148,10 +148,13 @@ __device__ __forceinline__ uint64_t grid_key(float2 y, float4 r, uint32_t qmax)
 // Same root, keys and order as bbox_final + morton_encode_hist + the radix passes.  25 iterations of a run: 60,000 points
 // 4.28 -> 3.46 ms, 30,011 4.25 -> 3.35, 100,000 4.35 -> 3.85 (three launches where there were fourteen); 2000 points 2.42
 // -> 2.27 (before, one workgroup sorted up to 8192 words in LDS).  Beyond RANK_MAX there are more tiles than a wave scans, the counting grows with the
-// number of tiles, and the radix passes have enough to do.
+// number of tiles, and the radix passes have enough to do.  In the caller's numbering, which says nothing about where the
+// points are, every tile has words in every bucket: rank_merge of 131,072 points then takes 52 us instead of 24, and the
+// limit is lower (25 iterations, radix passes / counting: 106,496 points 5.41 / 5.17 ms, 114,688 5.56 / 5.36, 122,880 5.71 /
+// 5.64, 131,072 5.91 / 6.01; renumbered 131,072 4.61 / 4.21).
 constexpr int RANK_THREADS = 512, RANK_TILE = 1024, RANK_GAP = 64, RANK_PER_TILE = RANK_TILE / RANK_GAP;
 constexpr int RANK_BUCKETS = 256;              // most workgroups of rank_merge: about one per compute unit
-constexpr int RANK_MAX = RANK_SORT_MAX;
+constexpr int RANK_MAX = RANK_SORT_MAX, RANK_MAX_CALLER = 122880;
 static_assert(RANK_MAX <= 2 * WAVE * RANK_TILE, "rank_merge scans two tiles a lane of one wave");
 
 __host__ __device__ inline int rank_offset(int tile) { return (tile * 39) & (RANK_GAP - 1); }   // (64 / golden ratio, odd)
@@ -344,7 +347,7 @@ hipError_t rank_sort_prepare()
                                12 * rank_merge_cap(RANK_MAX, RANK_BUCKETS));
 }
 
-// The order of the points of c->Yi in c->words[c->sorted_buf], for n <= RANK_MAX (nparts = 0: the root square is in place).
+// The order of the points of c->Yi in c->words[c->sorted_buf], for n <= RANK_MAX (root_fresh: the root square is in place).
 static hipError_t launch_rank_sort(tsne_ctx *c, hipStream_t s)
 {
     const int n = c->p.n, B = c->p.morton_bits, ks = c->key_shift, nparts = c->root_fresh ? 0 : c->bbox_nparts;
@@ -1418,7 +1421,7 @@ hipError_t launch_tree_sort(tsne_ctx *c, hipStream_t s)
 {
     const int n = c->p.n, B = c->p.morton_bits, ks = c->key_shift;
     const float2 *Y = c->Yi;
-    if (n <= RANK_MAX) return launch_rank_sort(c, s);
+    if (n <= (c->identity ? RANK_MAX_CALLER : RANK_MAX)) return launch_rank_sort(c, s);
     if (!c->root_fresh)
         hipLaunchKernelGGL(bbox_final, dim3(1), dim3(c->bbox_nparts > 1024 ? 1024 : 256), 0, s, c->bbox_part, c->bbox_nparts, B,
                            c->root, c->status);

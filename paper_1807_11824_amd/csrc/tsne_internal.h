@@ -34,7 +34,7 @@ constexpr int SORT_TILE_MIN = SORT_THREADS * 8;   // smallest tile of the sort (
 constexpr int SORT_FINE_TILES = 256;              // ... unless tiles of 2 or 4 words a thread are no more than these
 constexpr int MAX_GRID_BITS = 24;        // a float has 24 significant bits
 constexpr int SMALL_SORT_MAX = 8192;  // up to here root, keys and order come out of one launch
-constexpr int RANK_SORT_MAX = 131072; // up to here the order is found by counting (rank_tiles and its kin)
+constexpr int RANK_SORT_MAX = 131072; // up to here at most the order is found by counting (rank_tiles and its kin)
 constexpr int LEVEL_THREADS = 256;
 constexpr int LEVEL_ITEMS = 4;
 constexpr int LEVEL_TILE = LEVEL_THREADS * LEVEL_ITEMS;
