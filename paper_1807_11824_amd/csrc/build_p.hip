@@ -331,6 +331,9 @@ struct HalfScale {
     float scale, dot_scale;
     double e_add;
 };
+// Values it is for: dot_scale is a normal float from 2^-49 on (2^-126; the rule was 1e-15, a little less, and gave 2^-128), and
+// below 1e15 the squares are far from the largest float.  Not 0 and not a number that is none.
+inline bool half_scales(float xmax) { return xmax >= 0x1p-49f && xmax < 1e15f; }
 inline HalfScale half_scale(float xmax, int d, double norm_max)
 {
     HalfScale h;
@@ -2695,11 +2698,11 @@ int ivf_search_tiles(const float *X, int n, int d, int k, int nlist, int tau, co
     // pass), exact distances for a few.  The copies take turns in L.xs (2 n dph <= 4 n dp bytes from 33 columns on).
     // (1,281,167 x 2048, four lists a query: tiles of a pass 8.35 -> 1.6 ms, quantizer and lists together 688 -> 360 ms.)
     const int dph = (d + 2 * SLAB - 1) / (2 * SLAB) * (2 * SLAB);
-    const bool half_first = d > KFLUSH && norm_max > 1e-30f && norm_max < 1e30f;      // (dot_scale has to be a normal float)
+    const float xmax = sqrtf(norm_max) * 1.0001f;      // (no value is larger than its row's norm, whose square is a rounded sum)
+    const bool half_first = d > KFLUSH && half_scales(xmax);
     HalfScale hs = {};
     if (half_first) {
-        // (no value is larger than its row's norm, whose square is a rounded sum)
-        hs = half_scale(sqrtf(norm_max) * 1.0001f, d, norm_max);
+        hs = half_scale(xmax, d, norm_max);
         HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&knn_tile_half_lists),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)HALF_GATHER_LDS));
         hipLaunchKernelGGL(split_high, wide_grid((size_t)n * (dph / 8)), dim3(256), 0, s, X, L.mu, n, d, dph, hs.scale, lorder, n, L.xs);
@@ -2893,9 +2896,10 @@ int ivf_probe_tiles(const float *X, int n, int d, const float *C, int nlist, int
     // the scale is the queries' (it has to stay what it was when they were copied); centroids are means of rows, but a
     // caller's may be anything: 2^15 for the queries leaves them a factor of two, and 1e30 keeps everything finite
     HalfScale hs = {};
-    bool half = d > KFLUSH && !queries->no_half && norm_max2[1] > 1e-30f && norm_max2[1] < 1e30f;
+    const float xmax = sqrtf(norm_max2[1]) * 1.0001f;
+    bool half = d > KFLUSH && !queries->no_half && half_scales(xmax);
     if (half) {
-        hs = half_scale(sqrtf(norm_max2[1]) * 1.0001f, d, std::max(norm_max, norm_max2[1]));
+        hs = half_scale(xmax, d, std::max(norm_max, norm_max2[1]));
         half = sqrtf(norm_max) * 1.0001f * hs.scale < 60000.f;
     }
     if (half) {
@@ -3123,7 +3127,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
         HIPCHK(hipStreamSynchronize(s));
         float xmax;
         memcpy(&xmax, &found[0], 4);
-        if (!(xmax > 1e-15f) || !(xmax < 1e15f) || found[1] > GAP_QUERIES / 2) {
+        if (!half_scales(xmax) || found[1] > GAP_QUERIES / 2) {
             // all rows equal, values half precision cannot scale, or neighbours it cannot tell apart
             high_first = false;
         } else {

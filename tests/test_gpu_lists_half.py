@@ -58,3 +58,28 @@ def test_quantizer_of_tight_groups(n, nlist):
     got, count = launches(lambda: ivf_train(_dev(X), nlist, 2).cpu().numpy())
     assert np.abs(got - want).max() <= 1e-6 * np.abs(X).max()
     assert count["knn_tile_half_other"] > 0 and (count["knn_tile_mfma"] > 0) == (n > 8192)
+
+
+@pytest.mark.parametrize("largest,half", [(1.6e-15, False), (2.0e-15, True), (0.9e15, True), (1.2e15, False)])
+def test_magnitudes(largest, half):
+    """Values that half precision is for: from 2^-49 = 1.78e-15 on the factor that undoes the scaling is a normal float, and
+    below 1e15 squares are finite.  The lists search takes the largest norm for the largest value."""
+    import oracle
+    from paper_1807_11824_amd import build_P, ivf_knn, ivf_train
+    rng = np.random.default_rng(5)
+    n, d, k = 3000, 260, 10
+    X = rng.standard_normal((12, d))[rng.integers(0, 12, n)] + rng.standard_normal((n, d))
+    X -= X.mean(axis=0)
+    exact = (X * (largest / np.abs(X).max())).astype(np.float32)
+    g, count = launches(lambda: build_P(_dev(exact), 3.0, k, want_knn=True))
+    assert (count["knn_tile_half"] > 0) == half
+    assert np.array_equal(g["knn_idx"].cpu().numpy(), oracle.knn(exact, k, rows=np.arange(n))[0])
+    lists = (X * (largest / np.sqrt((X * X).sum(axis=1).max()))).astype(np.float32)
+    C = ivf.kmeans_init(lists, 24)
+    want, _ = ivf.ivf_knn(lists, C, 3, k)
+    (idx, _), count = launches(lambda: ivf_knn(_dev(lists), _dev(C), 3, k))
+    assert (count["knn_tile_half_lists"] > 0) == half and (count["knn_tile_half_other"] > 0) == half
+    assert np.array_equal(idx.cpu().numpy(), want)
+    # (the quantizer rounds its sums of this magnitude like any other)
+    got = ivf_train(_dev(lists), 24, 2).cpu().numpy()
+    assert np.abs(got - ivf.kmeans_train(lists, 24, 2)[0]).max() <= 1e-6 * np.abs(lists).max()
