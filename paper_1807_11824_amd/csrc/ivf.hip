@@ -80,76 +80,115 @@ __device__ __forceinline__ FpsBest fps_better(FpsBest a, FpsBest b)
 {
     return b.v > a.v || (b.v == a.v && b.j < a.j) ? b : a;
 }
-// of the workgroup of FPS_ROWS waves; every thread gets it
-constexpr int FPS_ROWS = 16;
-__device__ __forceinline__ FpsBest fps_block_best(FpsBest a, FpsBest *ws)
+// of the workgroup of FPS_WAVES waves, whose lanes agree in runs of SAME; every thread gets it
+constexpr int FPS_WAVES = 16, FPS_WAVE_MAX = 4 * WAVE;
+template <int SAME>
+__device__ __forceinline__ FpsBest fps_wave_best(FpsBest a)
 {
 #pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) {
+    for (int o = WAVE / 2; o >= SAME; o >>= 1) {
         FpsBest b;
         b.v = __shfl_xor(a.v, o, WAVE);
         b.j = __shfl_xor(a.j, o, WAVE);
         b.pad = 0;
         a = fps_better(a, b);
     }
+    return a;
+}
+template <int SAME>
+__device__ __forceinline__ FpsBest fps_block_best(FpsBest a, FpsBest *ws)
+{
+    a = fps_wave_best<SAME>(a);
     __syncthreads();
     if (lane_id() == 0) ws[threadIdx.x >> 6] = a;
     __syncthreads();
     a = ws[0];
-    for (int w = 1; w < FPS_ROWS; ++w) a = fps_better(a, ws[w]);
+    for (int w = 1; w < FPS_WAVES; ++w) a = fps_better(a, ws[w]);
     return a;
 }
 
 // Round c of the farthest-point start, c = 1 ..: row c - 1 is the farthest of the round before (prev: the workgroups' best;
-// row 0 for c = 1), mind[j] = min(mind[j], |sample j - it|^2), best[workgroup] = the farthest of its rows now.  A wave a
-// sample row, eight of its loads on their way; every workgroup finds the farthest row for itself, which is one launch a
-// round instead of two.  (1131 rounds over 9056 x 2048: 34.9 -> 26.6 ms.)
-__global__ __launch_bounds__(WAVE * FPS_ROWS) void fps_step(const float *__restrict__ X, int n, int d, int m, int *__restrict__ sel, int c,
-                                                            double *__restrict__ mind, const FpsBest *__restrict__ prev, int nprev,
-                                                            FpsBest *__restrict__ best)
+// row 0 for c = 1), mind[j] = min(mind[j], |sample j - it|^2), best[workgroup] = the farthest of its rows now.  Every
+// workgroup finds the farthest row for itself, which is one launch a round instead of two.  LPR lanes a sample row, each
+// with the sums of 64 / LPR lanes of a whole wave, added up in the order in which wave_sum does it: the same bits for
+// every LPR.
+template <int LPR>
+__global__ __launch_bounds__(WAVE * FPS_WAVES) void fps_step(const float *__restrict__ X, int n, int d, int m, int *__restrict__ sel, int c,
+                                                             double *__restrict__ mind, const FpsBest *__restrict__ prev, int nprev,
+                                                             FpsBest *__restrict__ best)
 {
     extern __shared__ float fps_row[];          // the chosen row
-    __shared__ FpsBest ws[FPS_ROWS];
-    const int tid = (int)threadIdx.x;
+    __shared__ FpsBest ws[FPS_WAVES];
+    constexpr int ACC = WAVE / LPR, FIRST = 8;  // (eight columns a lane are on their way while the row is found)
+    const int tid = (int)threadIdx.x, sub = tid % LPR;
+    const int j = (int)blockIdx.x * (FPS_WAVES * ACC) + tid / LPR;
+    const float *x = X + (size_t)sample_row(min(j, m - 1), n, m) * d;
+    float xv[FIRST];
+#pragma unroll
+    for (int q = 0; q < FIRST; ++q) xv[q] = x[min(sub + LPR * q, d - 1)];
+    const double before = c > 1 ? mind[min(j, m - 1)] : 0.0;
     int at = 0;
     if (c > 1) {
         FpsBest a = {-1.0, 0x7FFFFFFF, 0};
-        for (int i = tid; i < nprev; i += WAVE * FPS_ROWS) a = fps_better(a, prev[i]);
-        at = min(fps_block_best(a, ws).j, m - 1);
+        if (nprev <= FPS_WAVE_MAX) {            // (every wave for itself: no barriers)
+#pragma unroll
+            for (int q = 0; q < FPS_WAVE_MAX / WAVE; ++q)
+                if (lane_id() + WAVE * q < nprev) a = fps_better(a, prev[lane_id() + WAVE * q]);
+            a = fps_wave_best<1>(a);
+        } else {
+            for (int i = tid; i < nprev; i += WAVE * FPS_WAVES) a = fps_better(a, prev[i]);
+            a = fps_block_best<1>(a, ws);
+        }
+        at = min(a.j, m - 1);
         if (blockIdx.x == 0 && tid == 0) sel[c - 1] = at;
     }
     const float *y = X + (size_t)sample_row(at, n, m) * d;
-    for (int t = tid; t < d; t += WAVE * FPS_ROWS) fps_row[t] = y[t];
+    for (int t = tid; t < d; t += WAVE * FPS_WAVES) fps_row[t] = y[t];
     __syncthreads();
-    const int j = (int)blockIdx.x * FPS_ROWS + (tid >> 6);
     FpsBest mine = {-1.0, 0x7FFFFFFF, 0};
     if (j < m) {
-        const float *x = X + (size_t)sample_row(j, n, m) * d;
-        double acc = 0.0;
-#pragma unroll 8
-        for (int t = lane_id(); t < d; t += WAVE) {
-            const double df = (double)x[t] - (double)fps_row[t];
-            acc = fma(df, df, acc);
+        double acc[ACC] = {};
+#pragma unroll
+        for (int q = 0; q < FIRST; ++q)
+            if (sub + LPR * q < d) {
+                const double df = (double)xv[q] - (double)fps_row[sub + LPR * q];
+                acc[q % ACC] = fma(df, df, acc[q % ACC]);
+            }
+#pragma unroll 8 / ACC
+        for (int t = sub + LPR * FIRST; t < d; t += WAVE) {
+#pragma unroll
+            for (int q = 0; q < ACC; ++q)
+                if (q == 0 || t + q * LPR < d) {
+                    const double df = (double)x[t + q * LPR] - (double)fps_row[t + q * LPR];
+                    acc[q] = fma(df, df, acc[q]);
+                }
         }
-        acc = wave_sum(acc);
-        const double v = c == 1 ? acc : fmin(mind[j], acc);
-        if (lane_id() == 0) mind[j] = v;
+        double sum = ACC == 4 ? (acc[0] + acc[ACC / 2]) + (acc[ACC / 4] + acc[ACC - 1]) : ACC == 2 ? acc[0] + acc[ACC - 1] : acc[0];
+#pragma unroll
+        for (int o = LPR / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, WAVE);
+        const double v = c == 1 ? sum : fmin(before, sum);
+        if (sub == 0) mind[j] = v;
         if (v > -1.0) { mine.v = v; mine.j = j; }           // (not: no number)
     }
-    mine = fps_block_best(mine, ws);
+    mine = fps_block_best<LPR>(mine, ws);
     if (tid == 0) best[blockIdx.x] = mine;
 }
 
+// Lanes a sample row (LPR).  A round is a launch and a chain of two reductions, so fewer and fuller workgroups pay where
+// rows are short.  All rounds and one of k-means (ms), two launches a round / 64 / 32 / 16 lanes: 9056 sample rows of 16
+// columns 14.3 / 17.4 / 12.5 / 9.1, 64: 15.8 / 18.8 / 14.0 / 10.8, 256: 14.8 / 16.8 / 12.3 / 10.2, 784: 22.8 / 21.0 / 18.3 /
+// 23.9, 2048: 40.1 / 26.7 / 34.7 / 52.6; 1128 rows of 64: 1.24 / 1.24 / 1.22 / 1.22, of 300: 1.65 / 1.39 / 1.43 / 1.56.
+static int fps_lanes(int d) { return d <= 256 ? 16 : d <= 1024 ? 32 : WAVE; }
+
 // the last choice
-__global__ __launch_bounds__(WAVE * FPS_ROWS) void fps_last(const FpsBest *__restrict__ best, int nbest, int m, int *__restrict__ sel, int c)
+__global__ __launch_bounds__(WAVE * FPS_WAVES) void fps_last(const FpsBest *__restrict__ best, int nbest, int m, int *__restrict__ sel, int c)
 {
-    __shared__ FpsBest ws[FPS_ROWS];
+    __shared__ FpsBest ws[FPS_WAVES];
     FpsBest a = {-1.0, 0x7FFFFFFF, 0};
-    for (int i = (int)threadIdx.x; i < nbest; i += WAVE * FPS_ROWS) a = fps_better(a, best[i]);
-    a = fps_block_best(a, ws);
+    for (int i = (int)threadIdx.x; i < nbest; i += WAVE * FPS_WAVES) a = fps_better(a, best[i]);
+    a = fps_block_best<1>(a, ws);
     if (threadIdx.x == 0) sel[c] = min(a.j, m - 1);
 }
-
 
 __global__ void fps_gather(const float *__restrict__ X, int n, int d, int m, int nlist, const int *__restrict__ sel,
                            float *__restrict__ C)
@@ -958,7 +997,7 @@ size_t ivf_carve(IvfLayout *L, int n, int d, int nlist, int tau, char *base, siz
     q = take(8 * (size_t)nlist * d); if (L) L->sums = (unsigned long long *)q;
     q = take(4); if (L) L->maxabs = (unsigned int *)q;
     q = take(8 * 8 * (size_t)nlist); if (L) L->mind = (double *)q;
-    q = take(2 * sizeof(FpsBest) * (8 * (size_t)nlist / FPS_ROWS + 1)); if (L) L->best = (FpsBest *)q;
+    q = take(2 * sizeof(FpsBest) * (8 * (size_t)nlist / FPS_WAVES + 1)); if (L) L->best = (FpsBest *)q;
     q = take(4 * (size_t)nlist); if (L) L->sel = (int *)q;
     {
         const size_t tb = k_tiles >= 0 && d > TILES_MIN_D ? ivf_tiles_workspace(n, d, k_tiles, nlist, tau) : 0;
@@ -1002,12 +1041,13 @@ int ivf_train_device(const float *X, int n, int d, int nlist, int iters, float *
     {
         const int m = (long long)n < 8ll * nlist ? n : 8 * nlist;
         hipLaunchKernelGGL(fill_i32_k, dim3(1), dim3(256), 0, s, L.sel, 0, (size_t)1);       // the first sample row
-        const int nb = (m + FPS_ROWS - 1) / FPS_ROWS;
+        const int lpr = fps_lanes(d), per = FPS_WAVES * WAVE / lpr, nb = (m + per - 1) / per;
         for (int c = 1; c < nlist; ++c)
-            hipLaunchKernelGGL(fps_step, dim3(nb), dim3(WAVE * FPS_ROWS), 4 * (size_t)d, s, X, n, d, m, L.sel, c, L.mind,
-                               L.best + (size_t)(c & 1) * nb, nb, L.best + (size_t)((c + 1) & 1) * nb);
+            hipLaunchKernelGGL(lpr == 16 ? fps_step<16> : lpr == 32 ? fps_step<32> : fps_step<WAVE>, dim3(nb), dim3(WAVE * FPS_WAVES),
+                               4 * (size_t)d, s, X, n, d, m, L.sel, c, L.mind, L.best + (size_t)(c & 1) * nb, nb,
+                               L.best + (size_t)((c + 1) & 1) * nb);
         if (nlist > 1)
-            hipLaunchKernelGGL(fps_last, dim3(1), dim3(WAVE * FPS_ROWS), 0, s, L.best + (size_t)(nlist & 1) * nb, nb, m, L.sel, nlist - 1);
+            hipLaunchKernelGGL(fps_last, dim3(1), dim3(WAVE * FPS_WAVES), 0, s, L.best + (size_t)(nlist & 1) * nb, nb, m, L.sel, nlist - 1);
         hipLaunchKernelGGL(fps_gather, (blocks(cd)), dim3(256), 0, s, X, n, d, m, nlist, L.sel, C);
     }
     IVFCHK(hipMemsetAsync(L.maxabs, 0, 4, s));
