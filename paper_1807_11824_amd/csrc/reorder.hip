@@ -31,7 +31,6 @@ __global__ __launch_bounds__(256) void reorder_state_k(const uint32_t *__restric
 }
 
 __global__ void zero_word_k(uint32_t *w) { *w = 0u; }
-__global__ void zero_pair_k(uint32_t *w) { w[0] = w[1] = 0u; }
 
 __device__ __forceinline__ bool in_band(uint32_t col_slot, int row_slot)
 {
@@ -389,40 +388,62 @@ __global__ __launch_bounds__(256) void graph_seed_k(float *__restrict__ x, int n
     if (i < n) x[i] = (float)(mix32((uint32_t)i + 0x9e3779b9u) >> 8) * (1.0f / 16777216.0f);
 }
 
-// Whether the passes on a copy of P go by windows (graph_smooth_window_k): counts of a sample of the copy's rows say how many
-// of their entries lie outside; with more than a quarter the gathers by lane are the quicker ones (512,000 points in four
-// blobs, nine tenths outside: 44 ms for set_P and a step by gathers, 52 by windows).
-__device__ __forceinline__ bool smooth_by_window(const uint32_t *seen) { return seen[0] <= seen[1] / 4u; }
+// Whether the passes on a copy go by windows (graph_smooth_window_k): graph_sample_k counts how many entries of a sample of the
+// copy's rows there are and how many of them lie outside, and up to `limit` percent may.  The kernel that is not to run is
+// launched all the same, and leaves.
+struct SmoothSeen {
+    const uint32_t *count;      // null: no such choice, the kernel that is launched runs
+    uint32_t limit;
+};
+__device__ __forceinline__ bool smooth_by_window(const SmoothSeen &s) { return (uint64_t)s.count[0] * 100u <= (uint64_t)s.count[1] * s.limit; }
 
-// (seen: null, or the copy's counts: the launch is for P that does not go by windows)
+// 16 U entries of a row from j on, U of them a lane's.  (Past its end: weight 0, and x of the row itself, which is near.  One
+// value for all would be a cache line that the whole chip asks for: a pass over 200,000 points in four blobs 52 -> 76 us.)
+template <int U>
+__device__ __forceinline__ void smooth_gather(const int32_t *col, const float *val, const float *x, int n, int row, int j, int e, int sub,
+                                              float &a, float &w)
+{
+    float v[U], xv[U];
+    uint32_t c[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        const int i = j + sub + 16 * q;
+        v[q] = i < e ? val[i] : 0.f;
+        c[q] = i < e ? (uint32_t)col[i] : (uint32_t)row;
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) xv[q] = x[min(c[q], (uint32_t)n - 1u)];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        a = fmaf(v[q], xv[q], a);
+        w += v[q];
+    }
+}
+
+// a row: U entries a lane on their way, or four where the rest of it is no more and U is larger than six
+template <int U>
+__device__ __forceinline__ void smooth_gather_row(const int32_t *col, const float *val, const float *x, int n, int row, int j, int e, int sub,
+                                                  float &a, float &w)
+{
+    if (U <= 6) {
+        for (; j < e; j += 16 * U) smooth_gather<U>(col, val, x, n, row, j, e, sub, a, w);
+    } else {
+        for (; e - j > 64; j += 16 * U) smooth_gather<U>(col, val, x, n, row, j, e, sub, a, w);
+        if (j < e) smooth_gather<4>(col, val, x, n, row, j, e, sub, a, w);
+    }
+}
+
+template <int U>
 __global__ __launch_bounds__(256) void graph_smooth_k(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
                                                       const float *__restrict__ val, const float *__restrict__ x, int n,
-                                                      float *__restrict__ xo, const uint32_t *__restrict__ seen)
+                                                      float *__restrict__ xo, SmoothSeen seen)
 {
-    if (seen && smooth_by_window(seen)) return;
-    const int row = (int)((blockIdx.x * 256u + threadIdx.x) / 16);
+    const int row = (int)((blockIdx.x * 256u + threadIdx.x) / 16), r = min(row, n - 1);
     const int sub = (int)(threadIdx.x % 16);
+    const int begin = row_ptr[r], end = row_ptr[r + 1];         // (on their way with the counts, not behind them)
+    if (seen.count && smooth_by_window(seen)) return;
     float a = 0.f, w = 0.f;
-    if (row < n) {
-        const int s = row_ptr[row], e = row_ptr[row + 1];
-        for (int j0 = s + sub; j0 < e; j0 += 64) {      // four entries per lane in flight
-            float v[4], xv[4];
-            int cj[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int j = j0 + 16 * q;
-                v[q] = j < e ? val[j] : 0.f;
-                cj[q] = j < e ? col[j] : row;
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) xv[q] = x[min((uint32_t)cj[q], (uint32_t)n - 1u)];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                a = fmaf(v[q], xv[q], a);
-                w += v[q];
-            }
-        }
-    }
+    if (row < n) smooth_gather_row<U>(col, val, x, n, row, begin, end, sub, a, w);
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) { a += __shfl_xor(a, o, WAVE); w += __shfl_xor(w, o, WAVE); }
     if (row < n && sub == 0) xo[row] = w > 0.f ? a / w : x[row];
@@ -431,66 +452,82 @@ __global__ __launch_bounds__(256) void graph_smooth_k(const int32_t *__restrict_
 // ---- the same passes on a copy of P in the order of the values so far
 // There a row's entries point near the row, but every gather still pays per cache line that its 64 lanes touch, some forty
 // cycles a load and twice what the entries take to arrive.  So a workgroup takes a contiguous share of the rows, with x of
-// its rows and of as many rows on either side as its LDS holds (SMOOTH_WINDOW values, one workgroup per compute unit), and
-// reads x from there; columns are stored a second time as 16-bit places in that window (SMOOTH_OUTSIDE: outside, the 32-bit
-// column says where), so that an entry is 6 bytes.  Sixteen lanes a row, every lane's entries in the order of
-// graph_smooth_k and the same operations on them: the same values to the bit.  1,281,167 points, 187 M entries: a pass
-// 0.55 -> 0.35 ms (3.3 TB/s).
-constexpr int SMOOTH_WINDOW = 38912, SMOOTH_ROWS_MAX = 8192, SMOOTH_THREADS = 1024;
+// its rows and of as many rows on either side as its LDS holds, and reads x from there; columns are stored a second time as
+// 16-bit places in that window (SMOOTH_OUTSIDE: outside, the 32-bit column says where), so that an entry is 6 bytes.  Sixteen
+// lanes a row, every lane's entries in the order of graph_smooth_k and the same operations on them: the same values to the
+// bit, whichever of the two takes a pass.  1,281,167 points, 187 M entries: a pass 0.55 -> 0.35 ms (3.3 TB/s).
+constexpr int SMOOTH_WINDOW_MAX = 38912, SMOOTH_WINDOW = 20000, SMOOTH_ROWS_MAX = 8192, SMOOTH_THREADS = 1024;
 constexpr uint32_t SMOOTH_OUTSIDE = 0xFFFFu;
-static_assert(SMOOTH_WINDOW < (int)SMOOTH_OUTSIDE && SMOOTH_WINDOW * 4 <= 160 * 1024 - 1024, "places are 16 bits, and LDS is 160 KB");
+static_assert(SMOOTH_WINDOW_MAX < (int)SMOOTH_OUTSIDE && SMOOTH_WINDOW_MAX * 4 <= 160 * 1024 - 1024 && SMOOTH_WINDOW * 4 <= 80 * 1024,
+              "places are 16 bits, and LDS is 160 KB");
 
-// rows of a workgroup's share, and the first row of the window of the share that holds a row
-static int smooth_share(int n, int num_cu)
+// Rows of a workgroup's share and length of its window; start(row): the first row of the window of the share that holds it.
+struct SmoothShape {
+    int share, window;
+    __device__ __forceinline__ int start(int row) const { return row / share * share - (window - share) / 2; }
+};
+static SmoothShape smooth_shape(int n, int num_cu, int window)
 {
-    const int by_cu = (n + num_cu - 1) / num_cu;
-    return by_cu < SMOOTH_ROWS_MAX ? by_cu : SMOOTH_ROWS_MAX;
+    const int groups = window > SMOOTH_WINDOW ? num_cu : 2 * num_cu, by_cu = (n + groups - 1) / groups;
+    return {by_cu < SMOOTH_ROWS_MAX ? by_cu : SMOOTH_ROWS_MAX, window};
 }
-__device__ __forceinline__ int smooth_window(int row, int share) { return row / share * share - (SMOOTH_WINDOW - share) / 2; }
 
-__global__ __launch_bounds__(SMOOTH_THREADS) void graph_smooth_window_k(const int32_t *__restrict__ row_ptr,
-                                                                        const uint16_t *__restrict__ place,
-                                                                        const int32_t *__restrict__ col,
-                                                                        const float *__restrict__ val, const float *__restrict__ x,
-                                                                        int n, int share, float *__restrict__ xo,
-                                                                        const uint32_t *__restrict__ seen)
+// The same as smooth_gather from the window in LDS.
+template <int U>
+__device__ __forceinline__ void smooth_windowed(const float *win, const uint16_t *place, const int32_t *col, const float *val, const float *x, int n,
+                                                int window, int j, int e, int sub, float &a, float &w)
 {
-    if (!smooth_by_window(seen)) return;
-    extern __shared__ float win[];
-    const int r0 = (int)blockIdx.x * share, r1 = min(n, r0 + share), base = smooth_window(r0, share);
-    for (int i = (int)threadIdx.x; i < SMOOTH_WINDOW; i += SMOOTH_THREADS) win[i] = x[min(max(base + i, 0), n - 1)];
-    __syncthreads();
-    const int sub = (int)(threadIdx.x % 16);
-    constexpr int U = 10;       // entries a lane has on their way: a row of 160 at once
-    for (int row = r0 + (int)threadIdx.x / 16; row < r1; row += SMOOTH_THREADS / 16) {
-        const int s = row_ptr[row], e = row_ptr[row + 1];
-        float a = 0.f, w = 0.f;
-        for (int j0 = s + sub; j0 < e; j0 += 16 * U) {
-            float v[U], xv[U];
-            uint32_t c[U];
-            bool far = false;
+    float v[U], xv[U];
+    uint32_t c[U];
+    bool far = false;
 #pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const int j = j0 + 16 * q;
-                v[q] = j < e ? val[j] : 0.f;
-                c[q] = j < e ? place[j] : 0u;
-            }
+    for (int q = 0; q < U; ++q) {
+        const int i = j + sub + 16 * q;
+        v[q] = i < e ? val[i] : 0.f;
+        c[q] = i < e ? (uint32_t)place[i] : 0u;
+    }
 #pragma unroll
-            for (int q = 0; q < U; ++q) {
-                xv[q] = win[min(c[q], (uint32_t)SMOOTH_WINDOW - 1u)];
-                far |= c[q] == SMOOTH_OUTSIDE;
-            }
-            if (far) {
+    for (int q = 0; q < U; ++q) {
+        xv[q] = win[min(c[q], (uint32_t)window - 1u)];
+        far |= c[q] == SMOOTH_OUTSIDE;
+    }
+    if (far) {          // (all columns, then all values: one after the other they are 2 U round trips to memory)
+        uint32_t at[U];
 #pragma unroll
-                for (int q = 0; q < U; ++q)
-                    if (c[q] == SMOOTH_OUTSIDE) xv[q] = x[min((uint32_t)col[j0 + 16 * q], (uint32_t)n - 1u)];
-            }
-#pragma unroll
-            for (int q = 0; q < U; ++q) {       // (past the end of the row: weight 0)
-                a = fmaf(v[q], xv[q], a);
-                w += v[q];
-            }
+        for (int q = 0; q < U; ++q) {
+            at[q] = 0u;
+            if (c[q] == SMOOTH_OUTSIDE) at[q] = (uint32_t)col[j + sub + 16 * q];
         }
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (c[q] == SMOOTH_OUTSIDE) xv[q] = x[min(at[q], (uint32_t)n - 1u)];
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        a = fmaf(v[q], xv[q], a);
+        w += v[q];
+    }
+}
+
+template <int U>
+__global__ __launch_bounds__(SMOOTH_THREADS, 8) void graph_smooth_window_k(const int32_t *__restrict__ row_ptr,
+                                                                         const uint16_t *__restrict__ place,
+                                                                         const int32_t *__restrict__ col,
+                                                                         const float *__restrict__ val, const float *__restrict__ x,
+                                                                         int n, SmoothShape shape, float *__restrict__ xo,
+                                                                         SmoothSeen seen)
+{
+    extern __shared__ float win[];
+    const int sub = (int)(threadIdx.x % 16);
+    if (seen.count && !smooth_by_window(seen)) return;
+    const int r0 = (int)blockIdx.x * shape.share, r1 = min(n, r0 + shape.share), base = shape.start(r0);
+#pragma unroll 8
+    for (int i = (int)threadIdx.x; i < shape.window; i += SMOOTH_THREADS) win[i] = x[min(max(base + i, 0), n - 1)];
+    __syncthreads();
+    for (int row = r0 + (int)threadIdx.x / 16; row < r1; row += SMOOTH_THREADS / 16) {
+        const int e = row_ptr[row + 1];
+        float a = 0.f, w = 0.f;
+        for (int j = row_ptr[row]; j < e; j += 16 * U) smooth_windowed<U>(win, place, col, val, x, n, shape.window, j, e, sub, a, w);
 #pragma unroll
         for (int o = 8; o > 0; o >>= 1) { a += __shfl_xor(a, o, WAVE); w += __shfl_xor(w, o, WAVE); }
         if (sub == 0) xo[row] = w > 0.f ? a / w : win[row - base];
@@ -499,8 +536,11 @@ __global__ __launch_bounds__(SMOOTH_THREADS) void graph_smooth_window_k(const in
 
 hipError_t graph_smooth_prepare()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&graph_smooth_window_k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               SMOOTH_WINDOW * 4);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&graph_smooth_window_k<4>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMOOTH_WINDOW_MAX * 4);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&graph_smooth_window_k<10>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               SMOOTH_WINDOW_MAX * 4);
 }
 
 // (who: which point x[p] belongs to; null: point p.  Words go to the places of their points, so that the stable sort
@@ -518,9 +558,10 @@ __global__ __launch_bounds__(256) void graph_keys_k(const float *__restrict__ x,
 // Position p of the order of x so far: its point, that point's value and row length, and where the point is now.
 __global__ __launch_bounds__(256) void graph_place_k(const uint64_t *__restrict__ words, int n, const int32_t *__restrict__ row_ptr,
                                                      uint32_t *__restrict__ who, uint32_t *__restrict__ place,
-                                                     float *__restrict__ x, int32_t *__restrict__ len)
+                                                     float *__restrict__ x, int32_t *__restrict__ len, uint32_t *__restrict__ seen)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < 2) seen[p] = 0u;         // (for graph_sample_k)
     if (p >= n) return;
     const uint64_t w = words[p];
     const uint32_t i = min((uint32_t)w, (uint32_t)n - 1u);
@@ -530,31 +571,48 @@ __global__ __launch_bounds__(256) void graph_place_k(const uint64_t *__restrict_
     len[p] = row_ptr[i + 1] - row_ptr[i];
 }
 
+// seen[0] of the seen[1] entries of every 64th sixteen rows of the copy lie outside the window of their row
+constexpr int SMOOTH_SAMPLE = 64;
+__global__ __launch_bounds__(256) void graph_sample_k(const uint32_t *__restrict__ who, const uint32_t *__restrict__ place, int n,
+                                                      const int32_t *__restrict__ urp, const int32_t *__restrict__ ucol, SmoothShape shape,
+                                                      uint32_t *__restrict__ seen)
+{
+    const int p = (int)blockIdx.x * 16 * SMOOTH_SAMPLE + (int)(threadIdx.x / 16);
+    uint32_t outside = 0, all = 0;
+    if (p < n) {
+        const uint32_t u = min(who[p], (uint32_t)n - 1u);
+        const int base = shape.start(p), e = urp[u + 1];
+#pragma unroll 4
+        for (int j = urp[u] + (int)(threadIdx.x % 16); j < e; j += 16) {
+            const int c = (int)place[min((uint32_t)ucol[j], (uint32_t)n - 1u)];
+            outside += c < base || c - base >= shape.window ? 1u : 0u;
+            all += 1u;
+        }
+    }
+    outside = wave_sum(outside);
+    all = wave_sum(all);
+    if (lane_id() == 0) { atomicAdd(seen, outside); atomicAdd(seen + 1, all); }
+}
+
 // 16 lanes copy the row of the point at position p, columns as positions, entries in the caller's order
 __global__ __launch_bounds__(256) void graph_relabel_k(const uint32_t *__restrict__ who, const uint32_t *__restrict__ place, int n,
                                                        const int32_t *__restrict__ urp, const int32_t *__restrict__ ucol,
-                                                       const float *__restrict__ uval, const int32_t *__restrict__ rp, int share,
+                                                       const float *__restrict__ uval, const int32_t *__restrict__ rp, SmoothShape shape,
                                                        int32_t *__restrict__ col, uint16_t *__restrict__ in_window,
-                                                       float *__restrict__ val, uint32_t *__restrict__ seen)
+                                                       float *__restrict__ val, SmoothSeen seen)
 {
     const int p = (int)((blockIdx.x * 256u + threadIdx.x) / 16);
     const int sub = (int)(threadIdx.x % 16);
     if (p >= n) return;
+    const bool by_window = seen.count ? smooth_by_window(seen) : in_window != nullptr;
     const uint32_t u = min(who[p], (uint32_t)n - 1u);
     const int src = urp[u], dst = rp[p], len = rp[p + 1] - dst;
-    const int base = smooth_window(p, share);
-    uint32_t outside = 0;
+    const int base = shape.start(p);
     for (int e = sub; e < len; e += 16) {
         const int c = (int)place[min((uint32_t)ucol[src + e], (uint32_t)n - 1u)];
         col[dst + e] = c;
-        const bool in = c >= base && c - base < SMOOTH_WINDOW;
-        in_window[dst + e] = (uint16_t)(in ? (uint32_t)(c - base) : SMOOTH_OUTSIDE);
-        outside += in ? 0u : 1u;
+        if (by_window) in_window[dst + e] = (uint16_t)(c >= base && c - base < shape.window ? (uint32_t)(c - base) : SMOOTH_OUTSIDE);
         val[dst + e] = uval[src + e];
-    }
-    if ((blockIdx.x & 63u) == 0u) {          // (every 64th sixteen rows)
-        if (outside) atomicAdd(seen, outside);
-        if (sub == 0) atomicAdd(seen + 1, (uint32_t)len);
     }
 }
 
@@ -563,7 +621,7 @@ __global__ __launch_bounds__(256) void graph_relabel_k(const uint32_t *__restric
 // P is copied in the order of the values so far, columns as positions: neighbouring rows then gather the same lines.
 // A row's entries keep their order, so every value, and with it the final order, is to the bit what it would be
 // without the copies.  They are written where the split copy of P goes afterwards and take no memory of their own.
-// Measured for all of set_P and one step at 1,281,167 / 400,000 / 60,000 points in clusters (ms): no copy 96 / - / 4.03;
+// Measured for all of set_P and one step, all passes by gathers, at 1,281,167 / 400,000 / 60,000 points in clusters (ms): no copy 96 / - / 4.03;
 // one copy after 8 passes 75 / - / 3.48, after 16: 57 / 22.9 / 3.41, after 20: 57 / 22.6 / 3.47, after 24: 58 / 22.0 / 3.42;
 // copies after 8 and 20 passes 53 / 22.3 / 3.34, after 10 and 24 52 / 21.2 / 3.24.  A copy costs about three late passes;
 // at 20,000 points, where x fits the first-level caches, it gains nothing.  P without a band (512,000 points in four
@@ -571,6 +629,19 @@ __global__ __launch_bounds__(256) void graph_relabel_k(const uint32_t *__restric
 constexpr int GRAPH_RELABEL_AFTER[2] = {10, 24};
 constexpr int GRAPH_RELABEL_LEFT = 8;        // passes that must still follow a copy
 constexpr int GRAPH_RELABEL_MIN = 32768;     // points
+
+// How the passes on a copy go.  Windows pay where rows are long or x is large, wider ones where P reaches farther; a few entries
+// outside are enough to lose that where some rows are much longer than others (100,000 points in four blobs, k = 90, with up to
+// 5 % instead of 2: 6.2 -> 7.4 ms), and the launch that leaves costs 4 us a pass.  All of set_P and a step, by gathers only / by
+// these rules (ms; clusters of 2000 points where nothing else is said):
+//   up to 64 entries a row (k = 30): up to SMOOTH_ALL points gathers only (by windows 100,000 2.18 -> 2.47, 140,000 2.74 -> 2.85);
+//   beyond, windows of 20,000 values, two workgroups a compute unit, with up to a quarter outside: 400,000 6.5 / 6.3, 1,281,167
+//   24.8 / 22.2;
+//   longer rows (k = 90): windows of 38,912.  Up to SMOOTH_FEW points whatever is outside, which cannot be much: 60,000 2.85 /
+//   2.46, in four blobs 4.37 / 3.39, with all columns random 3.27 / 2.77; up to SMOOTH_ALL with up to 2 % outside: 100,000 3.84 /
+//   3.61, in four blobs (gathers) 6.4 / 6.2, in five clusters 5.7 / 4.5, 200,000 7.2 / 6.3; beyond with up to a quarter: 400,000
+//   17.6 / 12.6, in 25 clusters of 20,000 500,000 36.0 / 24.8, 1,281,167 52.3 / 42.1, 512,000 in four blobs (gathers) 44.1 / 39.2.
+constexpr int SMOOTH_FEW = 65536, SMOOTH_ALL = 262144;
 
 hipError_t launch_graph_order(tsne_ctx *c, hipStream_t s)
 {
@@ -582,25 +653,32 @@ hipError_t launch_graph_order(tsne_ctx *c, hipStream_t s)
     const int32_t *rp = c->user_row_ptr, *col = c->user_col;
     const float *val = c->user_val;
     const uint32_t *who = nullptr;
-    const int share = smooth_share(n, c->num_cu);
-    uint32_t *seen = c->dtot;         // (the sort's, free between two of them)
+    const bool short_rows = c->nnz <= 64 * (int64_t)n, windows = !short_rows || n > SMOOTH_ALL, choose = windows && n > SMOOTH_FEW;
+    const SmoothShape shape = smooth_shape(n, c->num_cu, short_rows ? SMOOTH_WINDOW : SMOOTH_WINDOW_MAX);
+    // (counts in the sort's totals, free between two sorts)
+    const SmoothSeen always = {nullptr, 0u}, seen = {choose ? c->dtot : nullptr, n <= SMOOTH_ALL ? 2u : 25u};
+    const int wblocks = (n + shape.share - 1) / shape.share;
     hipError_t e;
     for (int t = 0; t < iters; ++t) {
         if ((t == GRAPH_RELABEL_AFTER[0] || t == GRAPH_RELABEL_AFTER[1]) && iters - t >= GRAPH_RELABEL_LEFT && n >= GRAPH_RELABEL_MIN) {
             hipLaunchKernelGGL(graph_keys_k, dim3(pblocks), dim3(256), 0, s, xa, n, who, c->words[0]);
             if ((e = launch_sort(c, 32, 32, false, s)) != hipSuccess) return e;
             hipLaunchKernelGGL(graph_place_k, dim3(pblocks), dim3(256), 0, s, c->words[c->sorted_buf], n, c->user_row_ptr,
-                               c->perm, c->inv, xa, c->len_near);
+                               c->perm, c->inv, xa, c->len_near, c->dtot);
             launch_scan(c->len_near, n, nullptr, c->rp_near, c->hist, s);
-            hipLaunchKernelGGL(zero_pair_k, dim3(1), dim3(1), 0, s, seen);
+            if (choose)
+                hipLaunchKernelGGL(graph_sample_k, dim3((unsigned)((n + 16 * SMOOTH_SAMPLE - 1) / (16 * SMOOTH_SAMPLE))), dim3(256), 0, s,
+                                   c->perm, c->inv, n, c->user_row_ptr, c->user_col, shape, c->dtot);
             hipLaunchKernelGGL(graph_relabel_k, dim3(blocks), dim3(256), 0, s, c->perm, c->inv, n, c->user_row_ptr, c->user_col,
-                               c->user_val, c->rp_near, share, c->col_far, c->col_near, c->val_s, seen);
+                               c->user_val, c->rp_near, shape, c->col_far, windows ? c->col_near : (uint16_t *)nullptr, c->val_s, seen);
             rp = c->rp_near; col = c->col_far; val = c->val_s; who = c->perm;
         }
-        if (who)
-            hipLaunchKernelGGL(graph_smooth_window_k, dim3((unsigned)((n + share - 1) / share)), dim3(SMOOTH_THREADS), SMOOTH_WINDOW * 4, s, rp,
-                               c->col_near, col, val, xa, n, share, xb, seen);
-        hipLaunchKernelGGL(graph_smooth_k, dim3(blocks), dim3(256), 0, s, rp, col, val, xa, n, xb, who ? seen : (uint32_t *)nullptr);
+        if (who && windows)
+            hipLaunchKernelGGL(short_rows ? graph_smooth_window_k<4> : graph_smooth_window_k<10>, dim3((unsigned)wblocks), dim3(SMOOTH_THREADS),
+                               shape.window * 4, s, rp, c->col_near, col, val, xa, n, shape, xb, seen);
+        if (!who || !windows || choose)
+            hipLaunchKernelGGL(short_rows ? graph_smooth_k<6> : graph_smooth_k<10>, dim3(blocks), dim3(256), 0, s, rp, col, val, xa, n, xb,
+                               who && choose ? seen : always);
         std::swap(xa, xb);
     }
     hipLaunchKernelGGL(graph_keys_k, dim3(pblocks), dim3(256), 0, s, xa, n, who, c->words[0]);
