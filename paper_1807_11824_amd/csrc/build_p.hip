@@ -3203,7 +3203,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
         const bool resident = dp <= 2 * SLAB && rows >= RESIDENT_MIN_ROWS;
         const int *sched = nullptr;
         int launch = 0;
-        bool listed = ord && resident;
+        bool listed = ord && resident, known = false;      // known: a sweep over all rows that starts with cut-offs
         if (listed) {
             // (as below: a compaction pass behind every second launch, whose own and the one before's appends it has room for)
             const unsigned nqt = (unsigned)((rows + HT - 1) / HT), grid = 8 * ((nqt + 7) / 8);
@@ -3258,6 +3258,13 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
                 hipLaunchKernelGGL(row_norms, wide_grid((size_t)n * WAVE), dim3(256), 0, s, d_X, L.mu, n, d, ord, n, L.norms);
                 split();
                 hipLaunchKernelGGL(knn_reset, dim3((rows + 255) / 256), dim3(256), 0, s, L.tau, L.cnt, rows, L.ccount);
+            } else if (best > ORD_PLAIN * plain) {
+                // (the first block of query rows says little about this one: it is a region of its own)  All rows here too, with
+                // the cut-offs so far; the pairs so far are dropped, as below.
+                listed = false;
+                known = true;
+                limit = alone = 0;
+                hipLaunchKernelGGL(fill_int_k, dim3((rows + 255) / 256), dim3(256), 0, s, L.cnt, 0, rows);
             }
             if (alone > 0) hipLaunchKernelGGL(tile_rest_limit_k, dim3(1), dim3(QB / HT), 0, s, L.rest_count, (int)nqt, limit);
             for (int b = 0; b < (int)nqt && alone > 0; ++b) {
@@ -3295,7 +3302,7 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
         }
         for (int j0 = 0, jend; !listed && j0 < n; j0 = jend, ++launch) {
             jend = j0 + DBC < n ? j0 + DBC : n;
-            const bool dense = j0 == 0;
+            const bool dense = j0 == 0 && !known;
             const int force = jend >= n ? 1 : 0;
             int *cc = L.ccount + (launch & 1), *cc_next = L.ccount + ((launch + 1) & 1);   // two lists take turns
             // (a row that is not listed has room for what two launches can append, so a pass over the rows follows every

@@ -50,3 +50,46 @@ def test_search(case):
         assert count[f"knn_tile_resident<{ns},true,true>"] == 1 and count[f"knn_tile_resident<{ns},false,false>"] > 0
     elif case != "one_row_far_out":
         assert along == 0 and count[f"knn_tile_resident<{ns},false,false>"] > 0
+
+
+@pytest.mark.parametrize("case", ["blobs", "ragged", "uneven", "one_slab_sorted_ties", "later_blocks_touch"])
+def test_every_list(case):
+    """All n lists, those of the query tiles that straddle two groups among them (they are swept by themselves), against the
+    same rows with columns of zeros up to 72, which go another way: no order, half precision first.  Distances are the same to
+    the bit.  later_blocks_touch: a compact group far away comes first in the order, groups that touch after it."""
+    import torch
+    from paper_1807_11824_amd import build_P
+    n, d, k = 196_608, 50, 30
+    if case == "ragged":
+        n, d = 262_145, 64
+    if case in ("one_slab_sorted_ties", "later_blocks_touch"):
+        d = 30 if case == "one_slab_sorted_ties" else 16
+    X, label = _groups(n, d, 3 if case == "ragged" else 4, 10.0, seed=7 * n + d)
+    if case == "uneven":                    # one group of half the rows, one of 300
+        X, label = _groups(n, d, 16, 10.0, seed=5)
+        X[: n // 2] -= X[: n // 2].mean(axis=0) - 30.0
+        X[:n // 2] = np.random.default_rng(1).standard_normal((n // 2, d)) + 30.0
+        X[n // 2: n // 2 + 300] = np.random.default_rng(2).standard_normal((300, d)) - 40.0
+    if case == "one_slab_sorted_ties":
+        X = X[np.argsort(label, kind="stable")]
+        X[1000:1400] = X[1000]
+    if case == "later_blocks_touch":
+        X, _ = _groups(n, d, 60, 10.0, seed=3)
+        X[:66_000] = np.random.default_rng(4).standard_normal((66_000, d)) + 12.0
+        order = np.random.default_rng(6).permutation(n - 1) + 1
+        X[1:] = X[order]                    # (row 0, the first pivot, is in the compact group)
+    X = torch.from_numpy(np.ascontiguousarray(X, np.float32)).to("cuda:0")
+    wide = torch.zeros((n, 72), device="cuda:0")
+    wide[:, :d] = X
+    got, count = launches(lambda: build_P(X, 10.0, k, want_knn=True))
+    want = build_P(wide, 10.0, k, want_knn=True)
+    assert torch.equal(got["knn_idx"], want["knn_idx"]) and torch.equal(got["knn_d2"], want["knn_d2"])
+    ns = 1 if d <= 32 else 2
+    alone = count["knn_tile_mfma<4,false,false,false>"]
+    if case == "later_blocks_touch":
+        assert count[f"knn_tile_resident<{ns},true,true>"] > 1 and count[f"knn_tile_resident<{ns},false,false>"] > 0
+        assert count[f"knn_tile_resident<{ns},true,false>"] == 0
+    elif case != "uneven":                 # (the half of all rows in one group cannot leave enough out)
+        assert count[f"knn_tile_resident<{ns},false,true>"] > 0 and count[f"knn_tile_resident<{ns},false,false>"] == 0
+    if case in ("blobs", "ragged"):
+        assert alone > 0
