@@ -2694,8 +2694,8 @@ int ivf_search_tiles(const float *X, int n, int d, int k, int nlist, int tau, co
     const int nchunks = (max_list + DBC - 1) / DBC;
     const unsigned lb = (unsigned)((nlist + 1 + 255) / 256);
     // As in tsne_build_P: a first sweep with the values in half precision, whose certificate holds for nearly every query
-    // of ordinary data, the three-product tiles for the queries it fails (or for everybody, if it fails half of the first
-    // pass), exact distances for a few.  The copies take turns in L.xs (2 n dph <= 4 n dp bytes from 33 columns on).
+    // of ordinary data, the three-product tiles for the queries it fails (or for all passes that follow one of which it fails
+    // half), exact distances for a few.  The copies take turns in L.xs (2 n dph <= 4 n dp bytes from 33 columns on).
     // (1,281,167 x 2048, four lists a query: tiles of a pass 8.35 -> 1.6 ms, quantizer and lists together 688 -> 360 ms.)
     const int dph = (d + 2 * SLAB - 1) / (2 * SLAB) * (2 * SLAB);
     const float xmax = sqrtf(norm_max) * 1.0001f;      // (no value is larger than its row's norm, whose square is a rounded sum)
@@ -2755,10 +2755,11 @@ int ivf_search_tiles(const float *X, int n, int d, int k, int nlist, int tau, co
         // (three products after all: what those cannot certify goes to the exact pass)
         pass(half, nullptr, q0, rows, half == half_first ? L.fail_count : L.fail2_count, half == half_first ? L.fail_rows : L.fail2_rows);
         HIPCHK(hipGetLastError());
-        if (half && q0 == 0 && rows < n) {
+        if (half && q0 + rows < n) {        // (behind every pass: the lists of one say little about those of the next)
+            const int before = nfail;
             HIPCHK(hipMemcpyAsync(&nfail, L.fail_count, 4, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
-            if (nfail > rows / 2) { half = false; split(); }
+            if (nfail - before > rows / 2) { half = false; split(); }
         }
     }
     HIPCHK(hipMemcpyAsync(&nfail, L.fail_count, 4, hipMemcpyDeviceToHost, s));

@@ -83,3 +83,27 @@ def test_magnitudes(largest, half):
     # (the quantizer rounds its sums of this magnitude like any other)
     got = ivf_train(_dev(lists), 24, 2).cpu().numpy()
     assert np.abs(got - ivf.kmeans_train(lists, 24, 2)[0]).max() <= 1e-6 * np.abs(lists).max()
+
+
+def test_later_passes_that_fail():
+    """Lists of wide groups fill the first pass of 131,072 queries, lists of narrow ones the second: the third goes without half
+    precision, and the second's queries are swept again."""
+    from paper_1807_11824_amd import ivf_knn
+    rng = np.random.default_rng(8)
+    n, d, tau, k, nlist = 270_000, 72, 2, 20, 96
+    narrow = np.arange(n) >= 131_500
+    means = rng.standard_normal((16, d))
+    X = (means[rng.integers(0, 8, n) + 8 * narrow] + np.where(narrow, 0.05, 1.0)[:, None] * rng.standard_normal((n, d))).astype(np.float32)
+    C = np.concatenate([X[rng.choice(131_500, nlist // 2, replace=False)], X[131_500 + rng.choice(n - 131_500, nlist // 2, replace=False)]])
+    name = rng.permutation(n)
+    X = X[name]                             # (the lists are in the order of C whatever the rows')
+    lists = ivf.ivf_lists(X, C)
+    ends = np.cumsum([len(x) for x in lists])
+    assert ends[nlist // 2 - 1] > 128_000
+    (idx, d2), count = launches(lambda: ivf_knn(_dev(X), _dev(C), tau, k))
+    chunks = -(-max(len(x) for x in lists) // 2048)
+    assert count["knn_tile_half_lists"] == 2 * tau * chunks and count["knn_tile_mfma"] > tau * chunks
+    rows = np.concatenate([rng.choice(l, 1) for l in lists if len(l)])
+    want_idx, want_d2 = ivf.ivf_knn(X, C, tau, k, rows=rows)
+    assert np.array_equal(idx[rows.tolist()].cpu().numpy(), want_idx)
+    assert np.allclose(d2[rows.tolist()].cpu().numpy(), want_d2, rtol=1e-13, atol=1e-300)
