@@ -69,3 +69,33 @@ def test_counters_start_at_zero(n, leaf_cap, monkeypatch):
     words = ts.workspace[:ts.workspace.numel() // 256 * 256].cpu().numpy().view(np.int32).reshape(-1, 64)
     assert ((words[:, :17] == 0).all(axis=1) & (words[:, 17:] == -1).all(axis=1)).sum() == 1
     ts.close()
+
+
+@pytest.mark.parametrize("renumber", [False, True])
+def test_rows_in_the_walks_launch_are_the_same_to_the_bit(renumber):
+    """65,536 points, whose rows of the attraction share the walk's launch, and one more point without entries, with which they
+    have launches of their own: the same forces, bit for bit.  The last of the 65,536 points is the corner of the root square
+    and the added one lies on it, so that nothing else moves in the order of the points (renumbered: along the embedding)."""
+    import torch
+    from helpers import launches
+    from paper_1807_11824_amd import Tsne
+    dev = torch.device("cuda:0")
+    n = 65536
+    Y = synth.clustered_embedding(n, n_clusters=20, seed=3)
+    Y[-1] = Y.max(axis=0) + 1.0
+    Y = np.concatenate([Y, Y[-1:]])
+    rp, col, val = random_symmetric_csr(n, 40, seed=4)
+    forces = []
+    for m in (n, n + 1):
+        ts = Tsne(m, max_nnz=len(col) if renumber else 0, graph_order_iters=0, reorder_every=1 if renumber else 0, far_tiles=1, morton_bits=22)
+        ts.set_P(torch.from_numpy(np.concatenate([rp, rp[-1:]])[:m + 1].copy()).to(dev), torch.from_numpy(col).to(dev), torch.from_numpy(val).to(dev))
+        if renumber:
+            ts.step(torch.from_numpy(Y[:m].copy()).to(dev), 0)
+        (A, _, _), count = launches(lambda: ts.gradient(torch.from_numpy(Y[:m].copy()).to(dev)))
+        assert (count["bh_walk_rows"] == 1) == (m == n) and (count["attract_near" if renumber else "attract_csr"] == 1) == (m > n)
+        if renumber:
+            near, far = ts.P_layout()
+            assert near > len(col) // 20 and far > len(col) // 20
+        forces.append(A.cpu().numpy()[:n])
+        ts.close()
+    assert np.abs(forces[0]).max() > 0 and np.array_equal(forces[0], forces[1])
