@@ -388,14 +388,21 @@ __global__ __launch_bounds__(256) void graph_seed_k(float *__restrict__ x, int n
     if (i < n) x[i] = (float)(mix32((uint32_t)i + 0x9e3779b9u) >> 8) * (1.0f / 16777216.0f);
 }
 
-// Whether the passes on a copy go by windows (graph_smooth_window_k): graph_sample_k counts how many entries of a sample of the
-// copy's rows there are and how many of them lie outside, and up to `limit` percent may.  The kernel that is not to run is
-// launched all the same, and leaves.
+// What graph_sample_k and graph_relabel_k find out about a copy (words of SmoothSeen::count).
+enum { SEEN_OUTSIDE, SEEN_ALL, SEEN_CLOSE, SEEN_REACH, SEEN_WORDS };
+constexpr int SMOOTH_CLOSE = 256;
+// Whether the passes on a copy go by windows (graph_smooth_window_k): of the entries of a sample of its rows, up to `outside`
+// percent may lie outside, and up to `close` percent within SMOOTH_CLOSE places of the row, where gathers touch few lines.  The
+// kernel that is not to run is launched all the same, and leaves.
 struct SmoothSeen {
-    const uint32_t *count;      // null: no such choice, the kernel that is launched runs
-    uint32_t limit;
+    uint32_t *count;      // null: no such choice, the kernel that is launched runs
+    uint32_t outside, close;
 };
-__device__ __forceinline__ bool smooth_by_window(const SmoothSeen &s) { return (uint64_t)s.count[0] * 100u <= (uint64_t)s.count[1] * s.limit; }
+__device__ __forceinline__ bool smooth_by_window(const SmoothSeen &s)
+{
+    const uint64_t all = s.count[SEEN_ALL];
+    return (uint64_t)s.count[SEEN_OUTSIDE] * 100u <= all * s.outside && (uint64_t)s.count[SEEN_CLOSE] * 100u <= all * s.close;
+}
 
 // 16 U entries of a row from j on, U of them a lane's.  (Past its end: weight 0, and x of the row itself, which is near.  One
 // value for all would be a cache line that the whole chip asks for: a pass over 200,000 points in four blobs 52 -> 76 us.)
@@ -515,14 +522,16 @@ __global__ __launch_bounds__(SMOOTH_THREADS, 8) void graph_smooth_window_k(const
                                                                          const int32_t *__restrict__ col,
                                                                          const float *__restrict__ val, const float *__restrict__ x,
                                                                          int n, SmoothShape shape, float *__restrict__ xo,
-                                                                         SmoothSeen seen)
+                                                                         SmoothSeen seen, const uint32_t *__restrict__ reach)
 {
     extern __shared__ float win[];
     const int sub = (int)(threadIdx.x % 16);
     if (seen.count && !smooth_by_window(seen)) return;
     const int r0 = (int)blockIdx.x * shape.share, r1 = min(n, r0 + shape.share), base = shape.start(r0);
+    // (no entry that has a place lies farther from its row than this)
+    const int far = (int)min(*reach, (uint32_t)shape.window), first = max(r0 - base - far, 0), last = min(r1 - base + far, shape.window);
 #pragma unroll 8
-    for (int i = (int)threadIdx.x; i < shape.window; i += SMOOTH_THREADS) win[i] = x[min(max(base + i, 0), n - 1)];
+    for (int i = first + (int)threadIdx.x; i < last; i += SMOOTH_THREADS) win[i] = x[min(max(base + i, 0), n - 1)];
     __syncthreads();
     for (int row = r0 + (int)threadIdx.x / 16; row < r1; row += SMOOTH_THREADS / 16) {
         const int e = row_ptr[row + 1];
@@ -561,7 +570,7 @@ __global__ __launch_bounds__(256) void graph_place_k(const uint64_t *__restrict_
                                                      float *__restrict__ x, int32_t *__restrict__ len, uint32_t *__restrict__ seen)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < 2) seen[p] = 0u;         // (for graph_sample_k)
+    if (p < SEEN_WORDS) seen[p] = 0u;
     if (p >= n) return;
     const uint64_t w = words[p];
     const uint32_t i = min((uint32_t)w, (uint32_t)n - 1u);
@@ -571,14 +580,14 @@ __global__ __launch_bounds__(256) void graph_place_k(const uint64_t *__restrict_
     len[p] = row_ptr[i + 1] - row_ptr[i];
 }
 
-// seen[0] of the seen[1] entries of every 64th sixteen rows of the copy lie outside the window of their row
+// Entries of every 64th sixteen rows of the copy: outside the window of their row, close to it, all.
 constexpr int SMOOTH_SAMPLE = 64;
 __global__ __launch_bounds__(256) void graph_sample_k(const uint32_t *__restrict__ who, const uint32_t *__restrict__ place, int n,
                                                       const int32_t *__restrict__ urp, const int32_t *__restrict__ ucol, SmoothShape shape,
                                                       uint32_t *__restrict__ seen)
 {
     const int p = (int)blockIdx.x * 16 * SMOOTH_SAMPLE + (int)(threadIdx.x / 16);
-    uint32_t outside = 0, all = 0;
+    uint32_t outside = 0, close = 0, all = 0;
     if (p < n) {
         const uint32_t u = min(who[p], (uint32_t)n - 1u);
         const int base = shape.start(p), e = urp[u + 1];
@@ -586,12 +595,18 @@ __global__ __launch_bounds__(256) void graph_sample_k(const uint32_t *__restrict
         for (int j = urp[u] + (int)(threadIdx.x % 16); j < e; j += 16) {
             const int c = (int)place[min((uint32_t)ucol[j], (uint32_t)n - 1u)];
             outside += c < base || c - base >= shape.window ? 1u : 0u;
+            close += abs(c - p) <= SMOOTH_CLOSE ? 1u : 0u;
             all += 1u;
         }
     }
     outside = wave_sum(outside);
+    close = wave_sum(close);
     all = wave_sum(all);
-    if (lane_id() == 0) { atomicAdd(seen, outside); atomicAdd(seen + 1, all); }
+    if (lane_id() == 0) {
+        atomicAdd(seen + SEEN_OUTSIDE, outside);
+        atomicAdd(seen + SEEN_CLOSE, close);
+        atomicAdd(seen + SEEN_ALL, all);
+    }
 }
 
 // 16 lanes copy the row of the point at position p, columns as positions, entries in the caller's order
@@ -599,21 +614,32 @@ __global__ __launch_bounds__(256) void graph_relabel_k(const uint32_t *__restric
                                                        const int32_t *__restrict__ urp, const int32_t *__restrict__ ucol,
                                                        const float *__restrict__ uval, const int32_t *__restrict__ rp, SmoothShape shape,
                                                        int32_t *__restrict__ col, uint16_t *__restrict__ in_window,
-                                                       float *__restrict__ val, SmoothSeen seen)
+                                                       float *__restrict__ val, SmoothSeen seen, uint32_t *reach)
 {
     const int p = (int)((blockIdx.x * 256u + threadIdx.x) / 16);
     const int sub = (int)(threadIdx.x % 16);
-    if (p >= n) return;
     const bool by_window = seen.count ? smooth_by_window(seen) : in_window != nullptr;
-    const uint32_t u = min(who[p], (uint32_t)n - 1u);
-    const int src = urp[u], dst = rp[p], len = rp[p + 1] - dst;
-    const int base = shape.start(p);
-    for (int e = sub; e < len; e += 16) {
-        const int c = (int)place[min((uint32_t)ucol[src + e], (uint32_t)n - 1u)];
-        col[dst + e] = c;
-        if (by_window) in_window[dst + e] = (uint16_t)(c >= base && c - base < shape.window ? (uint32_t)(c - base) : SMOOTH_OUTSIDE);
-        val[dst + e] = uval[src + e];
+    uint32_t far = 0u;
+    if (p < n) {
+        const uint32_t u = min(who[p], (uint32_t)n - 1u);
+        const int src = urp[u], dst = rp[p], len = rp[p + 1] - dst;
+        const int base = shape.start(p);
+        for (int e = sub; e < len; e += 16) {
+            const int c = (int)place[min((uint32_t)ucol[src + e], (uint32_t)n - 1u)];
+            col[dst + e] = c;
+            if (by_window) {
+                const bool in = c >= base && c - base < shape.window;
+                in_window[dst + e] = (uint16_t)(in ? (uint32_t)(c - base) : SMOOTH_OUTSIDE);
+                if (in) far = max(far, (uint32_t)abs(c - p));
+            }
+            val[dst + e] = uval[src + e];
+        }
     }
+    if (!by_window) return;
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) far = max(far, (uint32_t)__shfl_xor((int)far, o, WAVE));
+    // (a look first, which may be late: hardly any wave has to add to the queue at the one address)
+    if (lane_id() == 0 && far > __hip_atomic_load(reach, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(reach, far);
 }
 
 // In the caller's numbering a pass is bound by its gathers of x: every entry is a cache line of its own (1.35 ms for
@@ -639,8 +665,9 @@ constexpr int GRAPH_RELABEL_MIN = 32768;     // points
 //   24.8 / 22.2;
 //   longer rows (k = 90): windows of 38,912.  Up to SMOOTH_FEW points whatever is outside, which cannot be much: 60,000 2.85 /
 //   2.46, in four blobs 4.37 / 3.39, with all columns random 3.27 / 2.77; up to SMOOTH_ALL with up to 2 % outside: 100,000 3.84 /
-//   3.61, in four blobs (gathers) 6.4 / 6.2, in five clusters 5.7 / 4.5, 200,000 7.2 / 6.3; beyond with up to a quarter: 400,000
-//   17.6 / 12.6, in 25 clusters of 20,000 500,000 36.0 / 24.8, 1,281,167 52.3 / 42.1, 512,000 in four blobs (gathers) 44.1 / 39.2.
+//   3.57, in four blobs (gathers) 6.4 / 6.2, in five clusters 5.7 / 4.5, 200,000 7.2 / 6.1, unless most entries are close: 100,000 in
+//   clusters of 230 2.61 by gathers, 2.84 by windows; beyond with up to a quarter: 400,000 17.3 / 13.0, in 25 clusters of 20,000
+//   500,000 36.0 / 24.8, 1,281,167 52.3 / 42, 512,000 in four blobs (gathers) 44.1 / 38.8.
 constexpr int SMOOTH_FEW = 65536, SMOOTH_ALL = 262144;
 
 hipError_t launch_graph_order(tsne_ctx *c, hipStream_t s)
@@ -656,7 +683,7 @@ hipError_t launch_graph_order(tsne_ctx *c, hipStream_t s)
     const bool short_rows = c->nnz <= 64 * (int64_t)n, windows = !short_rows || n > SMOOTH_ALL, choose = windows && n > SMOOTH_FEW;
     const SmoothShape shape = smooth_shape(n, c->num_cu, short_rows ? SMOOTH_WINDOW : SMOOTH_WINDOW_MAX);
     // (counts in the sort's totals, free between two sorts)
-    const SmoothSeen always = {nullptr, 0u}, seen = {choose ? c->dtot : nullptr, n <= SMOOTH_ALL ? 2u : 25u};
+    const SmoothSeen always = {nullptr, 0u, 0u}, seen = {choose ? c->dtot : nullptr, n <= SMOOTH_ALL ? 2u : 25u, n <= SMOOTH_ALL ? 60u : 100u};
     const int wblocks = (n + shape.share - 1) / shape.share;
     hipError_t e;
     for (int t = 0; t < iters; ++t) {
@@ -670,12 +697,12 @@ hipError_t launch_graph_order(tsne_ctx *c, hipStream_t s)
                 hipLaunchKernelGGL(graph_sample_k, dim3((unsigned)((n + 16 * SMOOTH_SAMPLE - 1) / (16 * SMOOTH_SAMPLE))), dim3(256), 0, s,
                                    c->perm, c->inv, n, c->user_row_ptr, c->user_col, shape, c->dtot);
             hipLaunchKernelGGL(graph_relabel_k, dim3(blocks), dim3(256), 0, s, c->perm, c->inv, n, c->user_row_ptr, c->user_col,
-                               c->user_val, c->rp_near, shape, c->col_far, windows ? c->col_near : (uint16_t *)nullptr, c->val_s, seen);
+                               c->user_val, c->rp_near, shape, c->col_far, windows ? c->col_near : (uint16_t *)nullptr, c->val_s, seen, c->dtot + SEEN_REACH);
             rp = c->rp_near; col = c->col_far; val = c->val_s; who = c->perm;
         }
         if (who && windows)
             hipLaunchKernelGGL(short_rows ? graph_smooth_window_k<4> : graph_smooth_window_k<10>, dim3((unsigned)wblocks), dim3(SMOOTH_THREADS),
-                               shape.window * 4, s, rp, c->col_near, col, val, xa, n, shape, xb, seen);
+                               shape.window * 4, s, rp, c->col_near, col, val, xa, n, shape, xb, seen, c->dtot + SEEN_REACH);
         if (!who || !windows || choose)
             hipLaunchKernelGGL(short_rows ? graph_smooth_k<6> : graph_smooth_k<10>, dim3(blocks), dim3(256), 0, s, rp, col, val, xa, n, xb,
                                who && choose ? seen : always);
