@@ -173,8 +173,9 @@ int tsne_build_P(const float *d_X, int32_t n, int32_t d, float perplexity, int32
  *   the copy of X grouped by list, 4 n tau, and a scratch of min(8 GiB, 4 n min(n, 4096)) bytes for one
  *   float per (query, candidate); more workspace than asked for is used (up to 8 GiB of scratch) to take
  *   more queries per pass.  Rows of more than 64 coordinates are searched on the matrix cores (candidates from
- *   tiles of split values, exact re-rank, an exact pass where the re-rank cannot vouch for the result): the
- *   figure then also holds a split copy of X (4 n d bytes) and 8 (k + 4176) bytes per query of a pass of 131,072.
+ *   tiles of the values in half precision, exact re-rank; split values for the queries whose result the re-rank
+ *   cannot vouch for, and an exact pass for those left): the figure then also holds a copy of X (4 n d bytes),
+ *   8 (k' + 4160) bytes per query of a pass of 131,072, k' = k + max(k / 2, 32), and some 24 n bytes of norms and row numbers.
  * Limits: nlist <= min(n, 65536), tau <= min(nlist, 32), k <= 1920, d <= 4096, n tau < 2^31.
  * Both calls synchronise the stream before returning.
  */
