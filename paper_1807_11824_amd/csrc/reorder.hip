@@ -479,10 +479,10 @@ static SmoothShape smooth_shape(int n, int num_cu, int window)
     return {by_cu < SMOOTH_ROWS_MAX ? by_cu : SMOOTH_ROWS_MAX, window};
 }
 
-// The same as smooth_gather from the window in LDS.
+// The same as smooth_gather from the window in LDS (own: the place of the row itself).
 template <int U>
 __device__ __forceinline__ void smooth_windowed(const float *win, const uint16_t *place, const int32_t *col, const float *val, const float *x, int n,
-                                                int window, int j, int e, int sub, float &a, float &w)
+                                                int window, int own, int j, int e, int sub, float &a, float &w)
 {
     float v[U], xv[U];
     uint32_t c[U];
@@ -491,7 +491,7 @@ __device__ __forceinline__ void smooth_windowed(const float *win, const uint16_t
     for (int q = 0; q < U; ++q) {
         const int i = j + sub + 16 * q;
         v[q] = i < e ? val[i] : 0.f;
-        c[q] = i < e ? (uint32_t)place[i] : 0u;
+        c[q] = i < e ? (uint32_t)place[i] : (uint32_t)own;      // (a place that is filled: 0 times what LDS held before may be no number)
     }
 #pragma unroll
     for (int q = 0; q < U; ++q) {
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(SMOOTH_THREADS, 8) void graph_smooth_window_k(const
     for (int row = r0 + (int)threadIdx.x / 16; row < r1; row += SMOOTH_THREADS / 16) {
         const int e = row_ptr[row + 1];
         float a = 0.f, w = 0.f;
-        for (int j = row_ptr[row]; j < e; j += 16 * U) smooth_windowed<U>(win, place, col, val, x, n, shape.window, j, e, sub, a, w);
+        for (int j = row_ptr[row]; j < e; j += 16 * U) smooth_windowed<U>(win, place, col, val, x, n, shape.window, row - base, j, e, sub, a, w);
 #pragma unroll
         for (int o = 8; o > 0; o >>= 1) { a += __shfl_xor(a, o, WAVE); w += __shfl_xor(w, o, WAVE); }
         if (sub == 0) xo[row] = w > 0.f ? a / w : win[row - base];

@@ -33,13 +33,16 @@ def _with_zeros(rp, col, val, extra, seed):
             np.insert(val, at, np.zeros(n * extra, np.float32)))
 
 
-def _orders(P, n, iters):
+def _orders(P, n, iters, after=None):
     """The permutations of the points that the context's workspace holds after set_P (the identity, the order, its inverse; where
-    every row has far entries also the list of such rows, which has no order), and the launches of set_P."""
+    every row has far entries also the list of such rows, which has no order), and the launches of set_P.  after: a P that the
+    context is given first."""
     import torch
     from paper_1807_11824_amd import Tsne
     dev = torch.device("cuda:0")
     t = Tsne(n, max_nnz=len(P[1]), graph_order_iters=iters)
+    if after is not None:
+        t.set_P(*[torch.from_numpy(a).to(dev) for a in after])
     P = [torch.from_numpy(a).to(dev) for a in P]
     _, count = launches(lambda: t.set_P(*P))
     words = t.workspace[:t.workspace.numel() // 256 * 256].view(torch.int32)
@@ -72,3 +75,13 @@ def test_same_order(n, k, size, stray, extra, kernels):
         assert c["graph_smooth_window_k"] == (0 if want == "gathers" else 30)
         assert c["graph_sample_k"] == (2 if want == "both" else 0)
     assert len(a & b) == 3
+
+
+@pytest.mark.parametrize("n,k", [(40_001, 48), (100_003, 48), (270_001, 12)])
+def test_nothing_is_left_in_lds(n, k):
+    """Windows are filled as far as entries reach; lanes past the end of a row read nothing else.  P of a context that was given
+    values that are no numbers first (they fill every window) gives the order of a fresh one."""
+    rp, col, val = _graph(n, k, 800, 0.0, seed=n)
+    fresh, count = _orders((rp, col, val), n, 40)
+    used, _ = _orders((rp, col, val), n, 40, after=(rp, col, np.full_like(val, np.nan)))
+    assert count["graph_smooth_window_k"] == 30 and len(fresh & used) == 3
